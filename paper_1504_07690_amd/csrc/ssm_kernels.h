@@ -9,7 +9,6 @@ namespace ssm {
 // Algorithm 1 on the device (coeffs.hip).  c: (degree+1) x ldc doubles.
 hipError_t launch_coefficients(double c0, double hw, double sigma, double inv_norm, const double* t, int nt,
                                int degree, int n_theta, double* c, float* c32, int64_t ldc, hipStream_t stream);
-size_t coefficient_lds_bytes(int n_theta);
 // Proposition 1: nu (2h+1 rows, row stride ldn, columns nt..ldn-1 zero) of the square of
 // sum_{k<=h} mu_k T_k, mu read as rows 0..h of c (row stride ldc).
 hipError_t launch_square_coefficients(const double* mu, int64_t ldc, int nt, int h, double* nu, int64_t ldn,
