@@ -7,9 +7,8 @@
 //
 // i.e. Z (ntb x e, row-major) = C^T (ntb x kc) * Y (kc x e, row-major), where the
 // coefficient table C is stored k-major: C[k*ldc + i].  Both operands are read
-// along their contiguous index, staged in LDS in [k][m] / [k][n] order, and fed to
-// MFMA tiles.  Output tiles are (points x elements); a workgroup's tile pairs one
-// slice of Y with many points, so each Y value fetched from memory serves BM points.
+// along their contiguous index and fed to MFMA tiles (points x elements); a tile pairs
+// one slice of Y with many points, so each Y value fetched from memory serves them all.
 //
 // XCD-aware order: workgroup b runs on XCD b % 8; the remap below gives every XCD
 // a run of consecutive (point-tile, element-tile) pairs with the point tile
@@ -37,211 +36,234 @@ __device__ __forceinline__ void tile_coords(int mt, int nt_tiles, int& m_tile, i
 }
 
 // ---------------------------------------------------------------------------
-// FP32: v_mfma_f32_32x32x2_f32.  Tile 128 points x 128 elements x 16 k, four
-// waves in a 2 x 2 arrangement, each wave 64 x 64 = 2 x 2 MFMA blocks.
-// Operand lanes: a = A[m = lane%32][k = lane/32], b = B[k = lane/32][n = lane%32];
-// result register r of lane l holds D[8(r/4) + 4(l/32) + r%4][l%32].
+// FP32 and FP64: v_mfma_f32_32x32x2_f32 and v_mfma_f64_16x16x4_f64, operands straight from
+// memory, no LDS and no barrier.
+//
+// A wave owns a strip of columns and up to MB blocks of points (MT points each: 32 in FP32,
+// 16 in FP64).  Both instructions take KS consecutive k per step (2 and 4), lane l holding
+// column l % MT of b for k = l / MT.  The wave reads b as 16 bytes per lane, VEC = 4 or 2
+// columns, and element j of that vector is the operand of one MFMA: column l % MT of its
+// result is column VEC (l % MT) + j of the strip (the columns of a product are independent,
+// so only the naming changes), and Z is stored as 16 bytes per lane as well.  A load of b
+// feeds VEC MB MFMAs of 64 cycles; the MB loads of a (the table's row, 128 bytes, shared by
+// all waves and found in the caches) feed NB VEC MFMAs each.  U steps are loaded at a time,
+// one set ahead of the MFMAs that use them, through buffer resources: a wave-uniform row
+// and a 32-bit lane offset that never changes, so the loop holds hardly a vector instruction
+// but loads and MFMAs.  A step's resource ends after its last row below kc, so rows at or past
+// kc read zeros, and sets past the end touch no memory.
+// The blocks of points are dealt evenly to the tiles (MB or MB - 1 each), so 205 points cost
+// 13 blocks of 16, not 16.  Accumulation runs over k in order, as the instruction's k index,
+// so the result does not depend on the tiling.  Columns past e and points past the table load
+// clamped addresses and are not stored.  WIDE (a step's rows span 2^31 bytes or more) keeps
+// 64-bit lane addresses, clamped row by row, and zeroes the rows past kc.
+//
+// What bounds it: the matrix cores for many points, HBM (Y once, Z once) for a few.
+// Measured against the tiles staged through LDS that this replaced (128 points x 128 or 64
+// columns a workgroup, a barrier per 16 degrees), N N_v = 1440468, K_c = 333, 205 points in
+// FP64: 5.03 to 3.51 ms (56 TFLOP/s; the library's square product reaches 72.7); N N_v =
+// 2621440, K_c = 200, 256 points in FP32: 2.66 to 2.27 ms (118 TFLOP/s of 150); 8 points of 32
+// degrees and 16.8 M columns in FP32: 1.58 to 0.49 ms (5.5 TB/s).  Raising the wave's issue
+// priority over the MFMAs gave 1-2% in FP32 and nothing in FP64.
 // ---------------------------------------------------------------------------
-constexpr int F32_BM = 128, F32_BN = 128, F32_BK = 16, F32_PAD = 4;
-
-__global__ void __launch_bounds__(256) sweep_f32_kernel(int64_t e, int kc, int ntb, const float* __restrict__ c,
-                                                        int64_t ldc, int64_t acols, const float* __restrict__ y,
-                                                        float* __restrict__ z, int accumulate, int mt,
-                                                        int nt_tiles) {
-  __shared__ float As[2][F32_BK][F32_BM + F32_PAD];
-  __shared__ float Bs[2][F32_BK][F32_BN + F32_PAD];
-  int m_tile, n_tile;
-  tile_coords(mt, nt_tiles, m_tile, n_tile);
-  if (n_tile < 0) return;
-  const int64_t i0 = (int64_t)m_tile * F32_BM;
-  const int64_t q0 = (int64_t)n_tile * F32_BN;
-  const int tid = threadIdx.x;
-  const int lane = tid & 63;
-  const int wave = tid >> 6;
-  const int wm = wave >> 1, wn = wave & 1;
-
-  // global -> register staging: 2 float4 of A and 2 of B per thread
-  f32x4 ra[2], rb[2];
-  auto load_tile = [&](int k0) {
-#pragma unroll
-    for (int u = 0; u < 2; ++u) {
-      const int idx = tid + 256 * u;
-      const int kk = idx >> 5;
-      const int c4 = (idx & 31) * 4;
-      const int k = k0 + kk;
-      f32x4 va = {0.f, 0.f, 0.f, 0.f}, vb = {0.f, 0.f, 0.f, 0.f};
-      if (k < kc) {
-        if (i0 + c4 < acols) va = *(const f32x4*)(c + (int64_t)k * ldc + i0 + c4);
-        if (q0 + c4 < e) vb = *(const f32x4*)(y + (int64_t)k * e + q0 + c4);
-      }
-      ra[u] = va;
-      rb[u] = vb;
-    }
-  };
-  auto store_tile = [&](int buf) {
-#pragma unroll
-    for (int u = 0; u < 2; ++u) {
-      const int idx = tid + 256 * u;
-      const int kk = idx >> 5;
-      const int c4 = (idx & 31) * 4;
-      *(f32x4*)&As[buf][kk][c4] = ra[u];
-      *(f32x4*)&Bs[buf][kk][c4] = rb[u];
-    }
-  };
-
-  f32x16 acc[2][2];
-#pragma unroll
-  for (int a = 0; a < 2; ++a)
-#pragma unroll
-    for (int b = 0; b < 2; ++b)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[a][b][r] = 0.f;
-
-  const int nk = (kc + F32_BK - 1) / F32_BK;
-  load_tile(0);
-  store_tile(0);
-  __syncthreads();
-  for (int kt = 0; kt < nk; ++kt) {
-    const int buf = kt & 1;
-    if (kt + 1 < nk) load_tile((kt + 1) * F32_BK);
-#pragma unroll
-    for (int kk = 0; kk < F32_BK; kk += 2) {
-      const int kr = kk + (lane >> 5);
-      const float a0 = As[buf][kr][wm * 64 + (lane & 31)];
-      const float a1 = As[buf][kr][wm * 64 + 32 + (lane & 31)];
-      const float b0 = Bs[buf][kr][wn * 64 + (lane & 31)];
-      const float b1 = Bs[buf][kr][wn * 64 + 32 + (lane & 31)];
-      acc[0][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(a0, b0, acc[0][0], 0, 0, 0);
-      acc[0][1] = __builtin_amdgcn_mfma_f32_32x32x2f32(a0, b1, acc[0][1], 0, 0, 0);
-      acc[1][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(a1, b0, acc[1][0], 0, 0, 0);
-      acc[1][1] = __builtin_amdgcn_mfma_f32_32x32x2f32(a1, b1, acc[1][1], 0, 0, 0);
-    }
-    if (kt + 1 < nk) store_tile(buf ^ 1);
-    __syncthreads();
+template <typename T>
+struct SweepOp;
+template <>
+struct SweepOp<float> {
+  typedef f32x4 V;
+  typedef f32x16 Acc;
+  static constexpr int MT = 32, KS = 2, VEC = 4, NB = 1, NR = 16;
+  static __device__ __forceinline__ Acc mfma(float a, float b, Acc c) {
+    return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0);
   }
+  // result register r of lane l is row out_row(l, r), column l % MT
+  static __device__ __forceinline__ int out_row(int lane, int r) { return 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3); }
+};
+template <>
+struct SweepOp<double> {
+  typedef f64x2 V;
+  typedef f64x4 Acc;
+  static constexpr int MT = 16, KS = 4, VEC = 2, NB = 2, NR = 4;
+  static __device__ __forceinline__ Acc mfma(double a, double b, Acc c) {
+    return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
+  }
+  static __device__ __forceinline__ int out_row(int lane, int r) { return (lane >> 4) + 4 * r; }
+};
 
+// steps per set of loads: about 4096 matrix cycles ahead where a wave holds many points, and
+// enough bytes in flight where it holds few
+template <typename T, int MB>
+constexpr int sweep_steps() {
+  return sizeof(T) == 4 ? (MB == 1 ? 8 : 4) : (MB >= 4 ? 2 : 4);
+}
+
+template <typename T, int MB>
+constexpr int sweep_waves() {  // waves per SIMD the registers are limited for
+  return sizeof(T) == 4 ? (MB == 1 ? 3 : 2) : (MB == 1 ? 4 : 2);
+}
+
+template <typename V>
+__device__ __forceinline__ V sweep_load(__amdgpu_buffer_rsrc_t r, uint32_t off);
+template <>
+__device__ __forceinline__ float sweep_load<float>(__amdgpu_buffer_rsrc_t r, uint32_t off) {
+  return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, (int)off, 0, 0));
+}
+template <>
+__device__ __forceinline__ double sweep_load<double>(__amdgpu_buffer_rsrc_t r, uint32_t off) {
+  return __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(r, (int)off, 0, 0));
+}
+template <>
+__device__ __forceinline__ f32x4 sweep_load<f32x4>(__amdgpu_buffer_rsrc_t r, uint32_t off) {
+  return __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(r, (int)off, 0, 0));
+}
+template <>
+__device__ __forceinline__ f64x2 sweep_load<f64x2>(__amdgpu_buffer_rsrc_t r, uint32_t off) {
+  return __builtin_bit_cast(f64x2, __builtin_amdgcn_raw_buffer_load_b128(r, (int)off, 0, 0));
+}
+
+// points i0 .. i0 + MB MT - 1, columns from q0 (both wave-uniform)
+template <typename T, int MB, int U, bool WIDE>
+__device__ __forceinline__ void sweep_strip(int64_t e, int kc, int ntb, const T* __restrict__ c, int64_t ldc,
+                                            int64_t acols, const T* __restrict__ y, T* __restrict__ z, int accumulate,
+                                            int64_t i0, int64_t q0) {
+  using Op = SweepOp<T>;
+  using V = typename Op::V;
+  constexpr int MT = Op::MT, KS = Op::KS, VEC = Op::VEC, NB = Op::NB;
+  constexpr int64_t ES = sizeof(T);
+  const int lane = threadIdx.x & 63;
+  const int kl = lane / MT;  // the lane's k of a step
+  const int cl = lane % MT;
+  // columns of each strip (from q0) and points (from i0), clamped
+  int qo[NB], io[MB];
 #pragma unroll
-  for (int a = 0; a < 2; ++a)
+  for (int s = 0; s < NB; ++s) {
+    const int64_t q = q0 + s * VEC * MT + cl * VEC;
+    qo[s] = (int)((q < e ? q : e - VEC) - q0);
+  }
 #pragma unroll
-    for (int b = 0; b < 2; ++b) {
-      const int64_t col = q0 + wn * 64 + b * 32 + (lane & 31);
-      if (col >= e) continue;
+  for (int m = 0; m < MB; ++m) {
+    const int64_t i = i0 + m * MT + cl;
+    io[m] = (int)((i < acols ? i : acols - 1) - i0);
+  }
+  uint32_t yoff[NB], aoff[MB];  // byte offsets from the row of a step
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int64_t row = i0 + wm * 64 + a * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-        if (row < ntb) {
-          float* p = z + row * e + col;
-          *p = accumulate ? *p + acc[a][b][r] : acc[a][b][r];
-        }
+  for (int s = 0; s < NB; ++s) yoff[s] = (uint32_t)(kl * e * ES + qo[s] * ES);
+#pragma unroll
+  for (int m = 0; m < MB; ++m) aoff[m] = (uint32_t)(kl * ldc * ES + io[m] * ES);
+  const uint32_t yrow = (uint32_t)(e * ES), arow = (uint32_t)(ldc * ES);
+  const uint32_t ylast = (uint32_t)((e - q0) * ES), alast = (uint32_t)((acols - i0) * ES);
+  struct Set {
+    T a[U][MB];
+    V b[U][NB];
+  };
+  Set S0, S1;
+  auto load = [&](Set& S, int k0) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int ks = k0 + KS * u;
+      if constexpr (WIDE) {
+        const int k = ks + kl < kc ? ks + kl : kc - 1;
+        const T* yr = y + k * e + q0;
+        const T* ar = c + k * ldc + i0;
+#pragma unroll
+        for (int s = 0; s < NB; ++s) S.b[u][s] = *(const V*)(yr + qo[s]);
+#pragma unroll
+        for (int m = 0; m < MB; ++m) S.a[u][m] = ar[io[m]];
+      } else {
+        const int rows = ks + KS <= kc ? KS : kc - ks;  // of this step
+        const int64_t k = ks < kc ? ks : 0;
+        const auto ry = __builtin_amdgcn_make_buffer_rsrc((void*)(y + k * e + q0), (short)0,
+                                                          rows > 0 ? (int)((rows - 1) * yrow + ylast) : 0, 0x00020000);
+        const auto ra = __builtin_amdgcn_make_buffer_rsrc((void*)(c + k * ldc + i0), (short)0,
+                                                          rows > 0 ? (int)((rows - 1) * arow + alast) : 0, 0x00020000);
+#pragma unroll
+        for (int s = 0; s < NB; ++s) S.b[u][s] = sweep_load<V>(ry, yoff[s]);
+#pragma unroll
+        for (int m = 0; m < MB; ++m) S.a[u][m] = sweep_load<T>(ra, aoff[m]);
+      }
+    }
+  };
+  typename Op::Acc acc[MB][NB][VEC];
+#pragma unroll
+  for (int m = 0; m < MB; ++m)
+#pragma unroll
+    for (int s = 0; s < NB; ++s)
+#pragma unroll
+      for (int j = 0; j < VEC; ++j)
+#pragma unroll
+        for (int r = 0; r < Op::NR; ++r) acc[m][s][j][r] = (T)0;
+  auto multiply = [&](Set& S, int k0) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const bool in = k0 + KS * u + kl < kc;
+#pragma unroll
+      for (int m = 0; m < MB; ++m)
+#pragma unroll
+        for (int s = 0; s < NB; ++s)
+#pragma unroll
+          for (int j = 0; j < VEC; ++j) {
+            const T av = !WIDE || in ? S.a[u][m] : (T)0, bv = !WIDE || in ? S.b[u][s][j] : (T)0;
+            acc[m][s][j] = Op::mfma(av, bv, acc[m][s][j]);
+          }
+    }
+  };
+  constexpr int KSET = KS * U;
+  load(S0, 0);
+  int k0 = 0;
+  for (; k0 + KSET < kc; k0 += 2 * KSET) {
+    load(S1, k0 + KSET);
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_setprio(1);
+    multiply(S0, k0);
+    __builtin_amdgcn_s_setprio(0);
+    __builtin_amdgcn_sched_barrier(0);
+    load(S0, k0 + 2 * KSET);
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_setprio(1);
+    multiply(S1, k0 + KSET);
+    __builtin_amdgcn_s_setprio(0);
+    __builtin_amdgcn_sched_barrier(0);
+  }
+  if (k0 < kc) multiply(S0, k0);
+#pragma unroll
+  for (int m = 0; m < MB; ++m)
+#pragma unroll
+    for (int r = 0; r < Op::NR; ++r) {
+      const int64_t row = i0 + m * MT + Op::out_row(lane, r);
+      if (row >= ntb) continue;
+#pragma unroll
+      for (int s = 0; s < NB; ++s) {
+        const int64_t q = q0 + (int64_t)s * VEC * MT + cl * VEC;
+        if (q >= e) continue;
+        V v;
+#pragma unroll
+        for (int j = 0; j < VEC; ++j) v[j] = acc[m][s][j][r];
+        V* p = (V*)(z + row * e + q);
+        if (accumulate) v = *p + v;
+        __builtin_nontemporal_store(v, p);
       }
     }
 }
 
-// ---------------------------------------------------------------------------
-// FP64: v_mfma_f64_16x16x4_f64.  Tile 128 points x 64 elements x 16 k, four
-// waves stacked along the points, each wave 32 x 64 = 2 x 4 MFMA blocks.
-// Operand lanes: a = A[m = lane%16][k = lane/16], b = B[k = lane/16][n = lane%16];
-// result register r of lane l holds D[l/16 + 4r][l%16].
-// ---------------------------------------------------------------------------
-constexpr int F64_BM = 128, F64_BN = 64, F64_BK = 16, F64_PAD = 2;
-
-__global__ void __launch_bounds__(256) sweep_f64_kernel(int64_t e, int kc, int ntb, const double* __restrict__ c,
-                                                        int64_t ldc, int64_t acols, const double* __restrict__ y,
-                                                        double* __restrict__ z, int accumulate, int mt,
-                                                        int nt_tiles) {
-  __shared__ double As[2][F64_BK][F64_BM + F64_PAD];
-  __shared__ double Bs[2][F64_BK][F64_BN + F64_PAD];
+template <typename T, int MB, bool WIDE>
+__global__ void __launch_bounds__(256, (sweep_waves<T, MB>()))
+    sweep_kernel(int64_t e, int kc, int ntb, const T* __restrict__ c, int64_t ldc, int64_t acols,
+                 const T* __restrict__ y, T* __restrict__ z, int accumulate, int mt, int nt_tiles) {
+  using Op = SweepOp<T>;
+  constexpr int U = sweep_steps<T, MB>();
   int m_tile, n_tile;
   tile_coords(mt, nt_tiles, m_tile, n_tile);
   if (n_tile < 0) return;
-  const int64_t i0 = (int64_t)m_tile * F64_BM;
-  const int64_t q0 = (int64_t)n_tile * F64_BN;
-  const int tid = threadIdx.x;
-  const int lane = tid & 63;
-  const int wave = tid >> 6;
-
-  f64x2 ra[4], rb[2];
-  auto load_tile = [&](int k0) {
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {  // A: 16 x 128 doubles = 1024 double2
-      const int idx = tid + 256 * u;
-      const int kk = idx >> 6;
-      const int c2 = (idx & 63) * 2;
-      const int k = k0 + kk;
-      f64x2 v = {0.0, 0.0};
-      if (k < kc && i0 + c2 < acols) v = *(const f64x2*)(c + (int64_t)k * ldc + i0 + c2);
-      ra[u] = v;
-    }
-#pragma unroll
-    for (int u = 0; u < 2; ++u) {  // B: 16 x 64 doubles = 512 double2
-      const int idx = tid + 256 * u;
-      const int kk = idx >> 5;
-      const int c2 = (idx & 31) * 2;
-      const int k = k0 + kk;
-      f64x2 v = {0.0, 0.0};
-      if (k < kc && q0 + c2 < e) v = *(const f64x2*)(y + (int64_t)k * e + q0 + c2);
-      rb[u] = v;
-    }
-  };
-  auto store_tile = [&](int buf) {
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const int idx = tid + 256 * u;
-      *(f64x2*)&As[buf][idx >> 6][(idx & 63) * 2] = ra[u];
-    }
-#pragma unroll
-    for (int u = 0; u < 2; ++u) {
-      const int idx = tid + 256 * u;
-      *(f64x2*)&Bs[buf][idx >> 5][(idx & 31) * 2] = rb[u];
-    }
-  };
-
-  f64x4 acc[2][4];
-#pragma unroll
-  for (int a = 0; a < 2; ++a)
-#pragma unroll
-    for (int b = 0; b < 4; ++b) acc[a][b] = (f64x4){0.0, 0.0, 0.0, 0.0};
-
-  const int nk = (kc + F64_BK - 1) / F64_BK;
-  load_tile(0);
-  store_tile(0);
-  __syncthreads();
-  for (int kt = 0; kt < nk; ++kt) {
-    const int buf = kt & 1;
-    if (kt + 1 < nk) load_tile((kt + 1) * F64_BK);
-#pragma unroll
-    for (int kk = 0; kk < F64_BK; kk += 4) {
-      const int kr = kk + (lane >> 4);
-      double av[2], bv[4];
-#pragma unroll
-      for (int a = 0; a < 2; ++a) av[a] = As[buf][kr][wave * 32 + a * 16 + (lane & 15)];
-#pragma unroll
-      for (int b = 0; b < 4; ++b) bv[b] = Bs[buf][kr][b * 16 + (lane & 15)];
-#pragma unroll
-      for (int a = 0; a < 2; ++a)
-#pragma unroll
-        for (int b = 0; b < 4; ++b)
-          acc[a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[a], bv[b], acc[a][b], 0, 0, 0);
-    }
-    if (kt + 1 < nk) store_tile(buf ^ 1);
-    __syncthreads();
-  }
-
-#pragma unroll
-  for (int a = 0; a < 2; ++a)
-#pragma unroll
-    for (int b = 0; b < 4; ++b) {
-      const int64_t col = q0 + b * 16 + (lane & 15);
-      if (col >= e) continue;
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int64_t row = i0 + wave * 32 + a * 16 + (lane >> 4) + 4 * r;
-        if (row < ntb) {
-          double* p = z + row * e + col;
-          *p = accumulate ? *p + acc[a][b][r] : acc[a][b][r];
-        }
-      }
-    }
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int nb = (ntb + Op::MT - 1) / Op::MT;
+  const int b0 = (int)((int64_t)m_tile * nb / mt);
+  const int count = (int)((int64_t)(m_tile + 1) * nb / mt) - b0;  // MB or MB - 1
+  const int64_t i0 = (int64_t)b0 * Op::MT;
+  const int64_t q0 = ((int64_t)n_tile * 4 + wave) * (Op::NB * Op::VEC * Op::MT);
+  if (q0 >= e) return;  // uniform over the wave; the kernel has no barrier
+  if (MB == 1 || count == MB)
+    sweep_strip<T, MB, U, WIDE>(e, kc, ntb, c, ldc, acols, y, z, accumulate, i0, q0);
+  else
+    sweep_strip<T, MB == 1 ? 1 : MB - 1, U, WIDE>(e, kc, ntb, c, ldc, acols, y, z, accumulate, i0, q0);
 }
 
 // ---------------------------------------------------------------------------
@@ -727,14 +749,75 @@ hipError_t launch_tiles(K kernel, int bm, int bn, int64_t e, int kc, int ntb, co
 
 }  // namespace
 
+namespace {
+
+// Tiles of points: the count mt that makes the busiest SIMD's share smallest.  A launch has
+// strips x mt waves of ceil(nb / mt) blocks' matrix work (nb blocks of MT points in all) on
+// 1024 SIMDs.  While a SIMD gets only a few waves, whole waves count; with many, the mean
+// does.  + 0.5 stands for the loads of a wave that do not grow with its blocks.
+template <int MAXB>
+int sweep_tiles(int64_t strips, int nb) {
+  int best = nb;
+  double cost = 0.0;
+  for (int mt = (nb + MAXB - 1) / MAXB; mt <= nb; ++mt) {
+    const int mb = (nb + mt - 1) / mt;
+    const int64_t per_simd = (strips * mt + 1023) / 1024;
+    const double c = per_simd <= 6 ? (double)per_simd * (mb + 0.5) : (double)strips * (nb + 0.5 * mt) / 1024.0;
+    if (cost == 0.0 || c < cost) {
+      cost = c;
+      best = mt;
+    }
+  }
+  return best;
+}
+
+template <typename T, int MB, int MAXB, bool WIDE>
+hipError_t launch_sweep_mb(int mb, int mt, int64_t e, int kc, int ntb, const T* c, int64_t ldc, int64_t acols,
+                           const T* y, T* z, int accumulate, hipStream_t stream) {
+  using Op = SweepOp<T>;
+  if (mb == MB) {
+    const int64_t bn = 4 * Op::NB * Op::VEC * Op::MT;
+    const int64_t ntiles = (e + bn - 1) / bn;
+    const int64_t blocks = (int64_t)mt * ((ntiles + 7) / 8 * 8);
+    if (blocks > 0x7FFFFFFF) return hipErrorInvalidValue;
+    hipLaunchKernelGGL((sweep_kernel<T, MB, WIDE>), dim3((unsigned)blocks), dim3(256), 0, stream, e, kc, ntb, c, ldc,
+                       acols, y, z, accumulate, mt, (int)ntiles);
+    return hipGetLastError();
+  }
+  if constexpr (MB < MAXB)
+    return launch_sweep_mb<T, MB + 1, MAXB, WIDE>(mb, mt, e, kc, ntb, c, ldc, acols, y, z, accumulate, stream);
+  return hipErrorInvalidValue;
+}
+
+template <typename T, int MAXB>
+hipError_t launch_sweep_any(int64_t e, int kc, int ntb, const T* c, int64_t ldc, int64_t acols, const T* y, T* z,
+                            int accumulate, hipStream_t stream) {
+  using Op = SweepOp<T>;
+  // 16-byte loads of Y and stores of Z (which need no more than the element's alignment)
+  if (e < Op::VEC || e % Op::VEC || kc < 1 || ntb < 1 || acols < ntb) return hipErrorInvalidValue;
+  const int64_t strip = Op::NB * Op::VEC * Op::MT;
+  const int nb = (ntb + Op::MT - 1) / Op::MT;
+  const int64_t es = sizeof(T), limit = (int64_t)1 << 31;
+  const bool wide = Op::KS * e * es >= limit || Op::KS * ldc * es >= limit;
+  if (wide) {  // the widest tile only
+    const int mt = (nb + MAXB - 1) / MAXB;
+    return launch_sweep_mb<T, MAXB, MAXB, true>(MAXB, mt, e, kc, ntb, c, ldc, acols, y, z, accumulate, stream);
+  }
+  const int mt = sweep_tiles<MAXB>((e + strip - 1) / strip, nb);
+  return launch_sweep_mb<T, 1, MAXB, false>((nb + mt - 1) / mt, mt, e, kc, ntb, c, ldc, acols, y, z, accumulate,
+                                            stream);
+}
+
+}  // namespace
+
 hipError_t launch_sweep_f32(int64_t e, int kc, int ntb, const float* c, int64_t ldc, int64_t acols, const float* y,
                             float* z, int accumulate, hipStream_t stream) {
-  return launch_tiles(sweep_f32_kernel, F32_BM, F32_BN, e, kc, ntb, c, ldc, acols, y, z, accumulate, stream);
+  return launch_sweep_any<float, 2>(e, kc, ntb, c, ldc, acols, y, z, accumulate, stream);
 }
 
 hipError_t launch_sweep_f64(int64_t e, int kc, int ntb, const double* c, int64_t ldc, int64_t acols,
                             const double* y, double* z, int accumulate, hipStream_t stream) {
-  return launch_tiles(sweep_f64_kernel, F64_BM, F64_BN, e, kc, ntb, c, ldc, acols, y, z, accumulate, stream);
+  return launch_sweep_any<double, 4>(e, kc, ntb, c, ldc, acols, y, z, accumulate, stream);
 }
 
 size_t sweep_bf16x3_lds_bytes() { return (size_t)2 * 4 * X3_TILE * sizeof(__bf16); }
