@@ -9,14 +9,27 @@
 // the upper ones.  This is one symmetric completion of the computed W^T Z; (W^T Z +
 // Z^T W)/2 is another, with the same value in exact arithmetic and one more product.
 //
-// Work split (N_v <= 96): one workgroup per (sweep point, row segment); each of its
-// four waves walks a contiguous quarter of the segment, four rows per MFMA step (the
-// MFMA's k).  A wave keeps every upper 16x16 block (a <= b) of Z^T Z and of W^T Z in
-// registers, so its operands come straight from memory: lane l reads column
-// 16a + l%16 of row r + l/16 for each column block a, for Z_i and W (a 4-row slab is
-// contiguous), two steps ahead of the MFMAs that consume them.  Each wave writes its
-// partial blocks to scratch; a second kernel adds the partials in a fixed order and
-// completes the symmetric matrices (deterministic).
+// Work split.  N_v <= 96: a wave keeps every upper 16x16 block (a <= b) of Z^T Z and of W^T Z
+// of one point in registers.  Above, the block grid is cut into tiles of 4 x 4 blocks (ti <= tj)
+// and a wave keeps one tile's (the upper ten of a diagonal tile: with all sixteen a quarter of
+// the matrix work at N_v = 128 went into blocks that are never read).  The pairs (tile, point)
+// are items of n rows each.  The items of a kind (diagonal or not), laid end to end, are cut into
+// equal parts, one per wave, for as many waves as are resident on the 1024 SIMDs (the two kinds
+// sharing them by their matrix work), so that no last round is half empty: 125 points in 9
+// segments of 4 waves were 4.4 rounds of 1024 waves, 12% idle.  A wave walks its part eight rows at
+// a time (two MFMA steps of four rows), writes its partial blocks to scratch at each item's end,
+// and a second kernel adds the partials of an item in order and completes the symmetric
+// matrices (deterministic).  Where the caller's scratch (4 nseg partials per point) or the number
+// of items is too small for that, every item is cut into 4 nseg parts.
+//
+// What bounds it: the FP64 matrix cores.  Operands come straight from memory, two steps ahead of
+// the MFMAs that consume them: lane l reads column 16a + l%16 of row r + l/16 for each column
+// block a, for Z_i and W (a 4-row slab is contiguous).
+// Measured (FP32 blocks, with the reduction): N = 262144, N_v = 80, 125 points 9.39 to 8.07 ms;
+// N_v = 128, 151 points 34.0 to 25.4 ms (51 TFLOP/s on 2 N N_v^2 a point, of 72.7 for the
+// library's square product); N_v = 256, 20 points 19.5 to 12.8 ms.
+#include <algorithm>
+
 #include "ssm_kernels.h"
 
 namespace ssm {
@@ -24,20 +37,37 @@ namespace {
 
 typedef double f64x4 __attribute__((ext_vector_type(4)));
 
-constexpr int GR_WAVES = 4;
+constexpr int GR_WAVES = 4;   // waves per workgroup, and scratch slots per segment
+constexpr int GT_B = 4;       // blocks per side of a tile (N_v above 96)
+constexpr int GR_ROWS = 8;    // rows per unit of work
 
-template <int T>
-struct GramTiles {
-  static constexpr int NPAIR = T * (T + 1) / 2;  // upper 16x16 blocks (a <= b)
+// The items of one kind (nz tiles x ntb points, item it = z ntb + i) and the waves that share
+// them.  parts > 0: every item in `parts` equal pieces, one per wave; else wave w takes q units
+// (GR_ROWS rows), and one more if w < rem, of the items' units laid end to end.
+struct GramShare {
+  int64_t units;  // per item
+  int64_t items, q, rem;
+  int waves, parts;
+
+  __host__ __device__ int64_t start(int64_t w) const { return w * q + (w < rem ? w : rem); }
+  // the wave that holds unit u of the line
+  __host__ __device__ int64_t owner(int64_t u) const {
+    const int64_t b = rem * (q + 1);
+    return u < b ? u / (q + 1) : rem + (u - b) / q;
+  }
+  __host__ __device__ int slots(int64_t it) const {
+    return parts ? parts : (int)(owner((it + 1) * units - 1) - owner(it * units) + 1);
+  }
 };
 
-template <int T, typename In>
-struct GramStep {
-  In z[T], w[T];
+struct GramPlan {
+  GramShare diag, off;  // N_v <= 96: one diagonal tile holding every block
+  int64_t n;
+  int ntb, ntile;       // points, tiles per side
 };
 
 // Operand loads are buffer loads over the wave's own rows: the resource's byte range
-// ends at the last row of the wave, and the hardware returns 0 for reads past it, so
+// ends at the last row of the piece, and the hardware returns 0 for reads past it, so
 // the rows of the last partial step arrive as zeros with no clamping, masking or
 // branching.  Columns 16a + l%16 >= N_v of a row inside the range read the next row;
 // they only feed output entries that are never stored.  Unpredicated loads whose
@@ -56,310 +86,328 @@ __device__ __forceinline__ double buffer_load<double>(__amdgpu_buffer_rsrc_t r, 
 
 constexpr int kBufferWord3 = 0x00020000;  // raw 32-bit buffer access (gfx9 family)
 
-template <int T, typename In>
-__device__ __forceinline__ void gram_load(GramStep<T, In>& st, __amdgpu_buffer_rsrc_t rz, __amdgpu_buffer_rsrc_t rw,
-                                          int rel_row, int nv, const int (&lane_off)[T]) {
-  const int base = rel_row * nv * (int)sizeof(In);
-#pragma unroll
-  for (int a = 0; a < T; ++a) {
-    st.z[a] = buffer_load<In>(rz, base + lane_off[a]);
-    st.w[a] = buffer_load<In>(rw, base + lane_off[a]);
-  }
-}
-
-template <int T, typename In>
-__global__ void __launch_bounds__(256) gram_kernel(int64_t n, int nv, int ntb, const In* __restrict__ w,
-                                                   int64_t w_stride, const In* __restrict__ z, int64_t z_stride,
-                                                   int64_t rows_per_seg, double* __restrict__ part) {
-  using G = GramTiles<T>;
-  const int i = blockIdx.x;
-  const int seg = blockIdx.y;
-  const int lane = threadIdx.x & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // uniform: the buffer resources stay scalar
-  const int64_t s_begin = (int64_t)seg * rows_per_seg;
-  const int64_t s_end = (s_begin + rows_per_seg < n) ? s_begin + rows_per_seg : n;
-  // contiguous quarter of the segment, a multiple of 4 rows
-  int64_t q = (s_end - s_begin + GR_WAVES - 1) / GR_WAVES;
-  q = (q + 3) / 4 * 4;
-  const int64_t r_begin = s_begin + wave * q;
-  const int64_t r_end = (r_begin + q < s_end) ? r_begin + q : s_end;
-  const In* zi = z + (int64_t)i * z_stride;
-  const In* wi = w + (int64_t)i * w_stride;
-  const int rows = (int)((r_end > r_begin) ? r_end - r_begin : 0);
-  const __amdgpu_buffer_rsrc_t rz = __builtin_amdgcn_make_buffer_rsrc(
-      (void*)(zi + (r_end > r_begin ? r_begin : 0) * nv), (short)0, rows * nv * (int)sizeof(In), kBufferWord3);
-  const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc(
-      (void*)(wi + (r_end > r_begin ? r_begin : 0) * nv), (short)0, rows * nv * (int)sizeof(In), kBufferWord3);
-  int lane_off[T];
-#pragma unroll
-  for (int a = 0; a < T; ++a) lane_off[a] = ((lane >> 4) * nv + 16 * a + (lane & 15)) * (int)sizeof(In);
-
-  f64x4 acc_zz[G::NPAIR], acc_wz[G::NPAIR];
-#pragma unroll
-  for (int p = 0; p < G::NPAIR; ++p) {
-    acc_zz[p] = (f64x4){0.0, 0.0, 0.0, 0.0};
-    acc_wz[p] = (f64x4){0.0, 0.0, 0.0, 0.0};
-  }
-
-  // two load buffers in rotation: each is refilled right after it is consumed with
-  // the rows two steps (8 rows) ahead
-  GramStep<T, In> buf0, buf1;
-  // issue order buf0 then buf1, as in the loop, so the wait counts match on entry
-  gram_load<T, In>(buf0, rz, rw, 0, nv, lane_off);
-  __builtin_amdgcn_sched_barrier(0);
-  gram_load<T, In>(buf1, rz, rw, 4, nv, lane_off);
-  __builtin_amdgcn_sched_barrier(0);
-  auto step = [&](GramStep<T, In>& b, int rr) {
-    double zf[T], wf[T];
-#pragma unroll
-    for (int a = 0; a < T; ++a) {
-      zf[a] = (double)b.z[a];
-      wf[a] = (double)b.w[a];
-    }
-    gram_load<T, In>(b, rz, rw, rr + 8, nv, lane_off);
-    // pair p = (a, b), a <= b, numbered row by row; fully unrolled, so every
-    // operand and accumulator index is a compile-time constant
-#pragma unroll
-    for (int a = 0; a < T; ++a)
-#pragma unroll
-      for (int bb = a; bb < T; ++bb) {
-        const int p = a * T - a * (a - 1) / 2 + (bb - a);
-        acc_zz[p] = __builtin_amdgcn_mfma_f64_16x16x4f64(zf[a], zf[bb], acc_zz[p], 0, 0, 0);
-      }
-#pragma unroll
-    for (int a = 0; a < T; ++a)
-#pragma unroll
-      for (int bb = a; bb < T; ++bb) {
-        const int p = a * T - a * (a - 1) / 2 + (bb - a);
-        acc_wz[p] = __builtin_amdgcn_mfma_f64_16x16x4f64(wf[a], zf[bb], acc_wz[p], 0, 0, 0);
-      }
-    __builtin_amdgcn_sched_barrier(0);  // keep steps apart: their operands need not be live together
-  };
-#pragma clang loop unroll(disable)
-  for (int rr = 0; rr < rows; rr += 8) {
-    step(buf0, rr);
-    step(buf1, rr + 4);
-  }
-
-  // partial blocks -> scratch slot (seg, wave):
-  // part[((slot*ntb + i)*2 + {0: ZZ, 1: WZ+ZW}) * nv*nv + row*nv + col]
-  const int64_t nn = (int64_t)nv * nv;
-  const int slot = seg * GR_WAVES + wave;
-  double* pz = part + ((int64_t)slot * ntb + i) * 2 * nn;
-  double* pw = pz + nn;
-#pragma unroll
-  for (int a = 0; a < T; ++a)
-#pragma unroll
-    for (int b = a; b < T; ++b) {
-      const int p = a * T - a * (a - 1) / 2 + (b - a);
-      const int col = 16 * b + (lane & 15);
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int row = 16 * a + (lane >> 4) + 4 * r;  // FP64 result layout: D[l/16 + 4r][l%16]
-        if (row < nv && col < nv) {
-          pz[(int64_t)row * nv + col] = acc_zz[p][r];
-          pw[(int64_t)row * nv + col] = acc_wz[p][r];
-        }
-      }
-    }
-}
-
-// N_v above 96: the block grid is cut into tiles of 4 x 4 column blocks, (ti, tj) with
-// ti <= tj, one tile per blockIdx.z; each wave keeps the 16 Z^T Z and 16 W^T Z
-// blocks of its tile (on a diagonal tile the lower blocks are computed and not stored).
-constexpr int GT_B = 4;
-
-template <typename In>
-struct GramTileStep {
-  In za[GT_B], wa[GT_B], zb[GT_B];
+// The blocks a wave keeps: A columns ca .. ca + TA - 1 of Z and W against TB columns of Z from
+// cb; UPPER: TA = TB and ca = cb, blocks a <= b only (and one set of Z columns).
+template <int TA, int TB, bool UPPER>
+struct GramShape {
+  static constexpr int NP = UPPER ? TA * (TA + 1) / 2 : TA * TB;
+  static __device__ constexpr int index(int a, int b) { return UPPER ? a * TA - a * (a - 1) / 2 + (b - a) : a * TB + b; }
 };
 
-template <typename In>
-__device__ __forceinline__ void gram_tile_load(GramTileStep<In>& st, __amdgpu_buffer_rsrc_t rz,
-                                               __amdgpu_buffer_rsrc_t rw, int rel_row, int nv,
-                                               const int (&off_a)[GT_B], const int (&off_b)[GT_B]) {
-  const int base = rel_row * nv * (int)sizeof(In);
+template <int TA, int TB, bool UPPER, typename In>
+__device__ __forceinline__ void gram_rows(const In* __restrict__ z, const In* __restrict__ w, int64_t r_begin,
+                                          int rows, int nv, int ca, int cb,
+                                          f64x4 (&acc_zz)[GramShape<TA, TB, UPPER>::NP],
+                                          f64x4 (&acc_wz)[GramShape<TA, TB, UPPER>::NP]) {
+  using G = GramShape<TA, TB, UPPER>;
+  const int lane = threadIdx.x & 63;
+  const int es = (int)sizeof(In);
+  int off_a[TA], off_b[TB];
 #pragma unroll
-  for (int a = 0; a < GT_B; ++a) {
-    st.za[a] = buffer_load<In>(rz, base + off_a[a]);
-    st.wa[a] = buffer_load<In>(rw, base + off_a[a]);
-    st.zb[a] = buffer_load<In>(rz, base + off_b[a]);
+  for (int a = 0; a < TA; ++a) off_a[a] = ((lane >> 4) * nv + 16 * (ca + a) + (lane & 15)) * es;
+#pragma unroll
+  for (int b = 0; b < TB; ++b) off_b[b] = ((lane >> 4) * nv + 16 * (cb + b) + (lane & 15)) * es;
+  struct Raw {
+    In za[TA], wa[TA], zb[TB];
+  };
+  const __amdgpu_buffer_rsrc_t rz =
+      __builtin_amdgcn_make_buffer_rsrc((void*)(z + r_begin * nv), (short)0, rows * nv * es, kBufferWord3);
+  const __amdgpu_buffer_rsrc_t rw =
+      __builtin_amdgcn_make_buffer_rsrc((void*)(w + r_begin * nv), (short)0, rows * nv * es, kBufferWord3);
+  auto load = [&](Raw& r, int row) {
+    const int base = row * nv * es;
+#pragma unroll
+    for (int a = 0; a < TA; ++a) {
+      r.za[a] = buffer_load<In>(rz, base + off_a[a]);
+      r.wa[a] = buffer_load<In>(rw, base + off_a[a]);
+    }
+    if constexpr (!UPPER) {
+#pragma unroll
+      for (int b = 0; b < TB; ++b) r.zb[b] = buffer_load<In>(rz, base + off_b[b]);
+    }
+  };
+  struct Op {
+    double za[TA], wa[TA], zb[TB];
+  };
+  auto widen = [&](Op& o, const Raw& r) {
+#pragma unroll
+    for (int a = 0; a < TA; ++a) {
+      o.za[a] = (double)r.za[a];
+      o.wa[a] = (double)r.wa[a];
+    }
+#pragma unroll
+    for (int b = 0; b < TB; ++b) o.zb[b] = UPPER ? o.za[b] : (double)r.zb[b];
+  };
+  auto multiply_zz = [&](const Op& o) {
+#pragma unroll
+    for (int a = 0; a < TA; ++a)
+#pragma unroll
+      for (int b = UPPER ? a : 0; b < TB; ++b) {
+        const int p = G::index(a, b);
+        acc_zz[p] = __builtin_amdgcn_mfma_f64_16x16x4f64(o.za[a], o.zb[b], acc_zz[p], 0, 0, 0);
+      }
+  };
+  auto multiply_wz = [&](const Op& o) {
+#pragma unroll
+    for (int a = 0; a < TA; ++a)
+#pragma unroll
+      for (int b = UPPER ? a : 0; b < TB; ++b) {
+        const int p = G::index(a, b);
+        acc_wz[p] = __builtin_amdgcn_mfma_f64_16x16x4f64(o.wa[a], o.zb[b], acc_wz[p], 0, 0, 0);
+      }
+  };
+  // A step widens its rows, refills their buffer with the rows two steps ahead and runs its
+  // MFMAs; scheduling barriers keep steps apart, so that their operands need not be live
+  // together.  At T = 5 (one wave per SIMD, registers to spare) the next step's rows are widened
+  // between the two halves of this step's MFMAs instead, 3% faster (8.33 to 8.07 ms at N =
+  // 262144, N_v = 80, 125 points); elsewhere that was 0-2% slower, and spilled at T = 6.
+  constexpr bool AHEAD = TA == 5;
+  Raw r0, r1;
+  load(r0, 0);
+  __builtin_amdgcn_sched_barrier(0);
+  load(r1, 4);
+  __builtin_amdgcn_sched_barrier(0);
+  if constexpr (AHEAD) {
+    Op c0, c1;
+    widen(c0, r0);
+    load(r0, 8);
+    __builtin_amdgcn_sched_barrier(0);
+    auto step = [&](const Op& cur, Op& nxt, Raw& raw, int row) {
+      multiply_zz(cur);
+      widen(nxt, raw);
+      load(raw, row);
+      __builtin_amdgcn_sched_barrier(0);
+      multiply_wz(cur);
+      __builtin_amdgcn_sched_barrier(0);
+    };
+#pragma clang loop unroll(disable)
+    for (int rr = 0; rr < rows; rr += 8) {
+      step(c0, c1, r1, rr + 12);
+      step(c1, c0, r0, rr + 16);
+    }
+  } else {
+    auto step = [&](Raw& raw, int row) {
+      Op o;
+      widen(o, raw);
+      load(raw, row);
+      multiply_zz(o);
+      multiply_wz(o);
+      __builtin_amdgcn_sched_barrier(0);
+    };
+#pragma clang loop unroll(disable)
+    for (int rr = 0; rr < rows; rr += 8) {
+      step(r0, rr + 8);
+      step(r1, rr + 12);
+    }
   }
 }
 
-template <typename In>
-__global__ void __launch_bounds__(256) gram_tiled_kernel(int64_t n, int nv, int ntb, const In* __restrict__ w,
-                                                         int64_t w_stride, const In* __restrict__ z,
-                                                         int64_t z_stride, int64_t rows_per_seg, int ntile,
-                                                         double* __restrict__ part) {
-  const int i = blockIdx.x;
-  const int seg = blockIdx.y;
-  // tile index -> (ti, tj), ti <= tj, row by row
-  int ti = 0, rem = blockIdx.z;
-  while (rem >= ntile - ti) {
-    rem -= ntile - ti;
-    ++ti;
-  }
-  const int tj = ti + rem;
+template <int TA, int TB, bool UPPER>
+__device__ __forceinline__ void gram_store(double* __restrict__ pz, int nv, int ca, int cb,
+                                           const f64x4 (&acc_zz)[GramShape<TA, TB, UPPER>::NP],
+                                           const f64x4 (&acc_wz)[GramShape<TA, TB, UPPER>::NP]) {
   const int lane = threadIdx.x & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int64_t s_begin = (int64_t)seg * rows_per_seg;
-  const int64_t s_end = (s_begin + rows_per_seg < n) ? s_begin + rows_per_seg : n;
-  int64_t q = (s_end - s_begin + GR_WAVES - 1) / GR_WAVES;
-  q = (q + 3) / 4 * 4;
-  const int64_t r_begin = s_begin + wave * q;
-  const int64_t r_end = (r_begin + q < s_end) ? r_begin + q : s_end;
-  const In* zi = z + (int64_t)i * z_stride;
-  const In* wi = w + (int64_t)i * w_stride;
-  const int rows = (int)((r_end > r_begin) ? r_end - r_begin : 0);
-  const __amdgpu_buffer_rsrc_t rz = __builtin_amdgcn_make_buffer_rsrc(
-      (void*)(zi + (r_end > r_begin ? r_begin : 0) * nv), (short)0, rows * nv * (int)sizeof(In), kBufferWord3);
-  const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc(
-      (void*)(wi + (r_end > r_begin ? r_begin : 0) * nv), (short)0, rows * nv * (int)sizeof(In), kBufferWord3);
-  int off_a[GT_B], off_b[GT_B];
+  double* pw = pz + (int64_t)nv * nv;
+  int cols = nv;  // opaque: the bounds tests are made here, not kept in registers over the row loop
+  asm volatile("" : "+s"(cols));
 #pragma unroll
-  for (int a = 0; a < GT_B; ++a) {
-    off_a[a] = ((lane >> 4) * nv + 16 * (GT_B * ti + a) + (lane & 15)) * (int)sizeof(In);
-    off_b[a] = ((lane >> 4) * nv + 16 * (GT_B * tj + a) + (lane & 15)) * (int)sizeof(In);
-  }
-  f64x4 acc_zz[GT_B * GT_B], acc_wz[GT_B * GT_B];
+  for (int a = 0; a < TA; ++a)
 #pragma unroll
-  for (int p = 0; p < GT_B * GT_B; ++p) {
-    acc_zz[p] = (f64x4){0.0, 0.0, 0.0, 0.0};
-    acc_wz[p] = (f64x4){0.0, 0.0, 0.0, 0.0};
-  }
-  GramTileStep<In> buf0, buf1;
-  gram_tile_load<In>(buf0, rz, rw, 0, nv, off_a, off_b);
-  __builtin_amdgcn_sched_barrier(0);
-  gram_tile_load<In>(buf1, rz, rw, 4, nv, off_a, off_b);
-  __builtin_amdgcn_sched_barrier(0);
-  auto step = [&](GramTileStep<In>& b, int rr) {
-    double za[GT_B], wa[GT_B], zb[GT_B];
-#pragma unroll
-    for (int a = 0; a < GT_B; ++a) {
-      za[a] = (double)b.za[a];
-      wa[a] = (double)b.wa[a];
-      zb[a] = (double)b.zb[a];
-    }
-    gram_tile_load<In>(b, rz, rw, rr + 8, nv, off_a, off_b);
-#pragma unroll
-    for (int a = 0; a < GT_B; ++a)
-#pragma unroll
-      for (int bb = 0; bb < GT_B; ++bb) {
-        const int p = a * GT_B + bb;
-        acc_zz[p] = __builtin_amdgcn_mfma_f64_16x16x4f64(za[a], zb[bb], acc_zz[p], 0, 0, 0);
-        acc_wz[p] = __builtin_amdgcn_mfma_f64_16x16x4f64(wa[a], zb[bb], acc_wz[p], 0, 0, 0);
-      }
-    __builtin_amdgcn_sched_barrier(0);
-  };
-#pragma clang loop unroll(disable)
-  for (int rr = 0; rr < rows; rr += 8) {
-    step(buf0, rr);
-    step(buf1, rr + 4);
-  }
-  const int64_t nn = (int64_t)nv * nv;
-  const int slot = seg * GR_WAVES + wave;
-  double* pz = part + ((int64_t)slot * ntb + i) * 2 * nn;
-  double* pw = pz + nn;
-#pragma unroll
-  for (int a = 0; a < GT_B; ++a)
-#pragma unroll
-    for (int bb = 0; bb < GT_B; ++bb) {
-      const int ab = GT_B * ti + a, bbl = GT_B * tj + bb;
-      if (ab > bbl) continue;  // lower blocks of a diagonal tile
-      const int p = a * GT_B + bb;
-      const int col = 16 * bbl + (lane & 15);
+    for (int b = UPPER ? a : 0; b < TB; ++b) {
+      const int p = GramShape<TA, TB, UPPER>::index(a, b);
+      const int col = 16 * (cb + b) + (lane & 15);
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        const int row = 16 * ab + (lane >> 4) + 4 * r;
-        if (row < nv && col < nv) {
-          pz[(int64_t)row * nv + col] = acc_zz[p][r];
-          pw[(int64_t)row * nv + col] = acc_wz[p][r];
+        const int row = 16 * (ca + a) + (lane >> 4) + 4 * r;  // FP64 result layout: D[l/16 + 4r][l%16]
+        if (row < cols && col < cols) {
+          pz[(int64_t)row * cols + col] = acc_zz[p][r];
+          pw[(int64_t)row * cols + col] = acc_wz[p][r];
         }
       }
     }
 }
 
-// K(i)[r][c] = sum over segments of the stored upper block entry; the lower blocks
-// mirror the upper ones; the diagonal blocks are averaged with their transpose (off the
-// diagonal blocks o1 = o2, so the factor 1/2 leaves the entry as stored).
-__global__ void __launch_bounds__(256) gram_reduce_kernel(int nv, int ntb, int nseg, const double* __restrict__ part,
+// A wave's part of the items of one kind.  locate(zt, ca, cb) gives the first columns of tile zt.
+template <int TA, int TB, bool UPPER, typename In, typename F>
+__device__ __forceinline__ void gram_share(const GramShare& sh, int64_t wv, int64_t n, int ntb, int nv,
+                                           const In* __restrict__ w, int64_t w_stride, const In* __restrict__ z,
+                                           int64_t z_stride, double* __restrict__ part, F locate) {
+  using G = GramShape<TA, TB, UPPER>;
+  const int64_t nn = (int64_t)nv * nv;
+  int64_t it, u, left;  // item, first unit in it, units left to do
+  if (sh.parts) {
+    it = wv / sh.parts;
+    const int64_t k = wv - it * sh.parts;
+    u = k * sh.units / sh.parts;
+    left = (k + 1) * sh.units / sh.parts - u;
+  } else {
+    const int64_t s0 = sh.start(wv);
+    it = s0 / sh.units;
+    u = s0 - it * sh.units;
+    left = sh.start(wv + 1) - s0;
+  }
+#pragma unroll 1
+  while (left > 0) {
+    const int64_t take = left < sh.units - u ? left : sh.units - u;
+    const int zt = (int)(it / ntb);
+    const int i = (int)(it - (int64_t)zt * ntb);
+    const int64_t slot = sh.parts ? wv - it * sh.parts : wv - sh.owner(it * sh.units);
+    int ca, cb;
+    locate(zt, ca, cb);
+    const int64_t r0 = u * GR_ROWS;
+    const int64_t r1 = r0 + take * GR_ROWS < n ? r0 + take * GR_ROWS : n;
+    f64x4 acc_zz[G::NP], acc_wz[G::NP];
+#pragma unroll
+    for (int p = 0; p < G::NP; ++p) {
+      acc_zz[p] = (f64x4){0.0, 0.0, 0.0, 0.0};
+      acc_wz[p] = (f64x4){0.0, 0.0, 0.0, 0.0};
+    }
+    gram_rows<TA, TB, UPPER, In>(z + (int64_t)i * z_stride, w + (int64_t)i * w_stride, r0, (int)(r1 - r0), nv, ca, cb,
+                                 acc_zz, acc_wz);
+    gram_store<TA, TB, UPPER>(part + (slot * ntb + i) * 2 * nn, nv, ca, cb, acc_zz, acc_wz);
+    left -= take;
+    ++it;
+    u = 0;
+  }
+}
+
+// T >= 1: one tile of T x T blocks (upper); T = 0: 4 x 4-block tiles
+template <int T>
+constexpr int gram_occupancy() {  // waves per SIMD (16 T (T + 1) accumulator registers, or 256)
+  return T == 0 || T >= 5 ? 1 : T == 4 ? 2 : T == 3 ? 3 : T == 2 ? 5 : 8;
+}
+
+template <int T, typename In>
+__global__ void __launch_bounds__(64 * GR_WAVES, (gram_occupancy<T>()))
+    gram_kernel(GramPlan pl, int nv, const In* __restrict__ w, int64_t w_stride, const In* __restrict__ z,
+                int64_t z_stride, double* __restrict__ part) {
+  const int64_t wv = (int64_t)blockIdx.x * GR_WAVES + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  constexpr int D = T ? T : GT_B;
+  if (wv < pl.diag.waves) {  // uniform over the wave; the kernel has no barrier
+    gram_share<D, D, true, In>(pl.diag, wv, pl.n, pl.ntb, nv, w, w_stride, z, z_stride, part,
+                               [](int zt, int& ca, int& cb) { ca = cb = GT_B * zt; });
+  } else if (T == 0 && wv < pl.diag.waves + pl.off.waves) {
+    const int side = pl.ntile;
+    if constexpr (T == 0)
+      gram_share<GT_B, GT_B, false, In>(pl.off, wv - pl.diag.waves, pl.n, pl.ntb, nv, w, w_stride, z, z_stride, part,
+                                        [side](int zt, int& ca, int& cb) {
+                                          int ti = 0;  // tiles (ti, tj), ti < tj, row by row
+                                          while (zt >= side - 1 - ti) zt -= side - 1 - ti++;
+                                          ca = GT_B * ti;
+                                          cb = GT_B * (ti + 1 + zt);
+                                        });
+  }
+}
+
+// K(i)[r][c] = sum over an item's partials of the stored upper block entry; the lower blocks
+// mirror the upper ones; the diagonal blocks are averaged with their transpose.
+__global__ void __launch_bounds__(256) gram_reduce_kernel(GramPlan pl, int nv, const double* __restrict__ part,
                                                           double* __restrict__ k_w, double* __restrict__ k_z) {
   const int64_t nn = (int64_t)nv * nv;
   const int64_t gid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (gid >= (int64_t)ntb * nn) return;
+  if (gid >= (int64_t)pl.ntb * nn) return;
   const int i = (int)(gid / nn);
   const int rc = (int)(gid - (int64_t)i * nn);
   const int r = rc / nv, c = rc % nv;
-  const bool upper = (r >> 4) <= (c >> 4);
-  const int64_t o1 = upper ? (int64_t)r * nv + c : (int64_t)c * nv + r;
-  const bool lower = (c >> 4) <= (r >> 4);
-  const int64_t o2 = lower ? (int64_t)c * nv + r : (int64_t)r * nv + c;
+  const int lo = (r < c ? r : c) >> 4, hi = (r < c ? c : r) >> 4;
+  const bool both = lo == hi;  // a diagonal block: (r, c) and (c, r) are stored
+  const int64_t o1 = lo == r >> 4 ? (int64_t)r * nv + c : (int64_t)c * nv + r;
+  const int64_t o2 = (int64_t)c * nv + r;
+  const int ti = pl.ntile ? lo / GT_B : 0, tj = pl.ntile ? hi / GT_B : 0;
+  const int zt = ti * (pl.ntile - 1) - ti * (ti - 1) / 2 + (tj - ti - 1);
+  const int ns = ti == tj ? pl.diag.slots((int64_t)ti * pl.ntb + i) : pl.off.slots((int64_t)zt * pl.ntb + i);
   double sz1 = 0.0, sw1 = 0.0, sz2 = 0.0, sw2 = 0.0;
-  for (int s = 0; s < nseg; ++s) {
-    const double* pz = part + ((int64_t)s * ntb + i) * 2 * nn;
+#pragma unroll 2
+  for (int s = 0; s < ns; ++s) {
+    const double* pz = part + ((int64_t)s * pl.ntb + i) * 2 * nn;
     const double* pw = pz + nn;
     sz1 += pz[o1];
     sw1 += pw[o1];
-    sz2 += pz[o2];
-    sw2 += pw[o2];
+    if (both) {
+      sz2 += pz[o2];
+      sw2 += pw[o2];
+    }
   }
-  k_z[gid] = 0.5 * (sz1 + sz2);
-  k_w[gid] = 0.5 * (sw1 + sw2);
+  k_z[gid] = both ? 0.5 * (sz1 + sz2) : sz1;
+  k_w[gid] = both ? 0.5 * (sw1 + sw2) : sw1;
 }
 
-int64_t rows_per_segment(int64_t n, int nseg) {
-  int64_t rps = (n + nseg - 1) / nseg;
-  return (rps + 4 * GR_WAVES - 1) / (4 * GR_WAVES) * (4 * GR_WAVES);
+// `waves` equal shares of the items, if there is work for them (64 rows each), an item's
+// partials (at most its units over a wave's, and one) fit `slots`, and a wave's rows of an item
+// fit `max_rows`
+bool share_evenly(GramShare& sh, int64_t waves, int slots, int64_t max_rows) {
+  const int64_t total = sh.items * sh.units;
+  if (waves < 1 || total < 8 * waves) return false;
+  sh.parts = 0;
+  sh.waves = (int)waves;
+  sh.q = total / waves;
+  sh.rem = total % waves;
+  return (sh.units + sh.q - 1) / sh.q + 1 <= slots && std::min(sh.q + 1, sh.units) * GR_ROWS <= max_rows;
+}
+
+// every item in as many parts as the scratch has slots
+bool share_parts(GramShare& sh, int slots, int64_t max_rows) {
+  sh.parts = (int)std::min<int64_t>(slots, sh.units);
+  if (sh.items * sh.parts > 0x3FFFFFFF) return false;
+  sh.waves = (int)(sh.items * sh.parts);
+  return ((sh.units + sh.parts - 1) / sh.parts) * GR_ROWS <= max_rows;
 }
 
 template <int T>
-hipError_t launch_t(int is_f32, int64_t n, int nv, int ntb, const void* w, int64_t ws, const void* z, int64_t zs,
-                    int64_t rps, int segs, double* scratch, hipStream_t stream) {
-  dim3 grid(ntb, segs);
+hipError_t launch_t(int is_f32, GramPlan& pl, int nv, int nseg, const void* w, int64_t ws, const void* z, int64_t zs,
+                    double* scratch, hipStream_t stream) {
+  const int slots = nseg * GR_WAVES;
+  // a wave's rows, with the prefetch's overrun, must be addressable by 32-bit byte offsets
+  const int64_t max_rows = (((int64_t)1 << 31) - 1) / ((int64_t)nv * (is_f32 ? 4 : 8)) - 16;
+  const int64_t resident = 1024 * (int64_t)gram_occupancy<T>();
+  const GramPlan whole = pl;
+  // matrix work of a row: 20 MFMAs a step on a diagonal tile, 32 off it
+  const int64_t dw = pl.diag.items * 20, ow = pl.off.items * 32;
+  const int64_t wd = ow ? std::max<int64_t>(1, resident * dw / (dw + ow)) : resident;
+  const bool fits = (pl.diag.items + pl.off.items) * slots > resident && share_evenly(pl.diag, wd, slots, max_rows) &&
+                    (!ow || share_evenly(pl.off, resident - wd, slots, max_rows));
+  if (!fits) {
+    pl = whole;
+    if (!share_parts(pl.diag, slots, max_rows) || (ow && !share_parts(pl.off, slots, max_rows)))
+      return hipErrorInvalidValue;
+  }
+  const int64_t waves = (int64_t)pl.diag.waves + pl.off.waves;
+  const dim3 grid((unsigned)((waves + GR_WAVES - 1) / GR_WAVES)), block(64 * GR_WAVES);
   if (is_f32)
-    hipLaunchKernelGGL((gram_kernel<T, float>), grid, dim3(64 * GR_WAVES), 0, stream, n, nv, ntb, (const float*)w, ws,
-                       (const float*)z, zs, rps, scratch);
+    hipLaunchKernelGGL((gram_kernel<T, float>), grid, block, 0, stream, pl, nv, (const float*)w, ws, (const float*)z,
+                       zs, scratch);
   else
-    hipLaunchKernelGGL((gram_kernel<T, double>), grid, dim3(64 * GR_WAVES), 0, stream, n, nv, ntb,
-                       (const double*)w, ws, (const double*)z, zs, rps, scratch);
+    hipLaunchKernelGGL((gram_kernel<T, double>), grid, block, 0, stream, pl, nv, (const double*)w, ws,
+                       (const double*)z, zs, scratch);
   return hipGetLastError();
 }
 
 // Point i reads W at w + i * ws and Z at z + i * zs (elements).
 hipError_t launch_strided(int is_f32, int64_t n, int nv, int ntb, const void* w, int64_t ws, const void* z,
                           int64_t zs, double* k_w, double* k_z, int nseg, double* scratch, hipStream_t stream) {
-  // the number of segments actually used can drop when rows are rounded up
-  const int64_t rps = rows_per_segment(n, nseg);
-  const int segs = (int)((n + rps - 1) / rps);
   const int t = (nv + 15) / 16;
-  // a wave's rows (plus the 8-row prefetch overrun) must be addressable by 32-bit byte offsets
-  if ((rps / GR_WAVES + 16) * (int64_t)nv * (is_f32 ? 4 : 8) >= (int64_t)1 << 31) return hipErrorInvalidValue;
+  if (t > 16) return hipErrorInvalidValue;
+  GramPlan pl{};
+  pl.n = n;
+  pl.ntb = ntb;
+  pl.ntile = t <= 6 ? 0 : (t + GT_B - 1) / GT_B;
+  pl.diag.units = pl.off.units = (n + GR_ROWS - 1) / GR_ROWS;
+  pl.diag.items = (int64_t)ntb * std::max(1, pl.ntile);
+  pl.off.items = (int64_t)ntb * (pl.ntile * (pl.ntile - 1) / 2);
   hipError_t err;
-  switch (t) {
-    case 1: err = launch_t<1>(is_f32, n, nv, ntb, w, ws, z, zs, rps, segs, scratch, stream); break;
-    case 2: err = launch_t<2>(is_f32, n, nv, ntb, w, ws, z, zs, rps, segs, scratch, stream); break;
-    case 3: err = launch_t<3>(is_f32, n, nv, ntb, w, ws, z, zs, rps, segs, scratch, stream); break;
-    case 4: err = launch_t<4>(is_f32, n, nv, ntb, w, ws, z, zs, rps, segs, scratch, stream); break;
-    case 5: err = launch_t<5>(is_f32, n, nv, ntb, w, ws, z, zs, rps, segs, scratch, stream); break;
-    case 6: err = launch_t<6>(is_f32, n, nv, ntb, w, ws, z, zs, rps, segs, scratch, stream); break;
-    default: {
-      if (t > 16) return hipErrorInvalidValue;
-      const int ntile = (t + GT_B - 1) / GT_B;
-      dim3 grid(ntb, segs, ntile * (ntile + 1) / 2);
-      if (is_f32)
-        hipLaunchKernelGGL(gram_tiled_kernel<float>, grid, dim3(64 * GR_WAVES), 0, stream, n, nv, ntb,
-                           (const float*)w, ws, (const float*)z, zs, rps, ntile, scratch);
-      else
-        hipLaunchKernelGGL(gram_tiled_kernel<double>, grid, dim3(64 * GR_WAVES), 0, stream, n, nv, ntb,
-                           (const double*)w, ws, (const double*)z, zs, rps, ntile, scratch);
-      err = hipGetLastError();
-    }
+  switch (pl.ntile ? 0 : t) {
+    case 1: err = launch_t<1>(is_f32, pl, nv, nseg, w, ws, z, zs, scratch, stream); break;
+    case 2: err = launch_t<2>(is_f32, pl, nv, nseg, w, ws, z, zs, scratch, stream); break;
+    case 3: err = launch_t<3>(is_f32, pl, nv, nseg, w, ws, z, zs, scratch, stream); break;
+    case 4: err = launch_t<4>(is_f32, pl, nv, nseg, w, ws, z, zs, scratch, stream); break;
+    case 5: err = launch_t<5>(is_f32, pl, nv, nseg, w, ws, z, zs, scratch, stream); break;
+    case 6: err = launch_t<6>(is_f32, pl, nv, nseg, w, ws, z, zs, scratch, stream); break;
+    default: err = launch_t<0>(is_f32, pl, nv, nseg, w, ws, z, zs, scratch, stream);
   }
   if (err != hipSuccess) return err;
-  const int64_t total = (int64_t)ntb * nv * nv;
-  hipLaunchKernelGGL(gram_reduce_kernel, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, stream, nv, ntb,
-                     segs * GR_WAVES, scratch, k_w, k_z);
+  const int64_t blocks = ((int64_t)ntb * nv * nv + 255) / 256;
+  if (blocks > 0x7FFFFFFF) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(gram_reduce_kernel, dim3((unsigned)blocks), dim3(256), 0, stream, pl, nv, scratch, k_w, k_z);
   return hipGetLastError();
 }
 
