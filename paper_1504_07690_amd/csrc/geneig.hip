@@ -886,87 +886,98 @@ __global__ void __launch_bounds__(GT_TH) geneig_tri_reduce_kernel(int nv, const 
   }
 }
 
-// 1/sqrt(x) for normal x > 0: the hardware estimate and two Newton steps
-// y <- y (3 - x y^2) / 2 (each at least doubles the correct bits).
-__device__ __forceinline__ double gt_rsqrt(double x) {
-  double y = __builtin_amdgcn_rsq(x);
-  double h = 0.5 * x;
-  y = y * fma(-h * y, y, 1.5);
-  y = y * fma(-h * y, y, 1.5);
-  return y;
-}
-
 // b. Implicit QL with Wilkinson shifts on T: it finds the next unreduced block [l, m]
 // (|e_m| <= eps (|d_m| + |d_m+1|) splits it), takes one shifted iteration on it and
 // records the iteration's rotations (c_i, s_i), i = m-1 down to i0, in the stream pt.rec,
 // with (m, i0) in pt.hdr.  The rotations are to be applied, in record order, to the
 // columns (i, i+1) of Z: z_i+1 <- s z_i + c z_i+1, z_i <- c z_i - s z_i+1.
 // Status 1 when the iterations exceed GT_MAX_QL n, or the record its capacity.
-// The iteration is one serial chain per point.  Every lane of the wave runs it on the
-// same values (each LDS write then stores the same value from every lane), and lane 0
-// alone writes the record: with a single lane active, a dependent FP64 chain measured
-// 40 cycles per operation with one such wave per point on the GPU, against 13 with the
-// wave's 64 lanes active.
-__global__ void __launch_bounds__(64) geneig_tri_ql_kernel(int nv, double* __restrict__ scratch, int64_t stride) {
-  __shared__ double d[GE_MAX_NV], e[GE_MAX_NV];
-  __shared__ double d0[GE_MAX_NV], e0[GE_MAX_NV];  // the block's entries before an iteration
+//
+// The iteration is one serial chain per point, run by all 64 lanes of a wave on the same
+// values (with a single lane active, a dependent FP64 chain measured 40 cycles per operation
+// with one such wave per point on the GPU, against 13 with the wave's 64 lanes active).  What
+// bounds it is the chain and the instructions issued beside it, so a rotation holds little
+// else: one LDS read of (d, e), one ahead; one write each of (d, e) and (c, s), by lane 0 (the
+// other lanes' address is a slot of their own, so no lane is masked); the record is written
+// at an iteration's end, 64 rotations at a time.  With inv = (f^2 + g^2)^-1/2, by the hardware
+// estimate y (about 23 bits) and one third-order step y + y r (1/2 + 3/8 r), r = 1 - (f^2 +
+// g^2) y^2, the next diagonal's correction is taken as ((d_i - g') f + 2 g b) inv, whose first
+// factor does not wait for inv.  The split search tests 64 entries at once.  Four points share
+// a workgroup: its four waves land on the four SIMDs of a CU, where single-wave workgroups
+// doubled up on some and left others idle.
+// MEASURED_QL
+constexpr int GT_QW = 4;  // points per workgroup
+typedef double gt_f64x2 __attribute__((ext_vector_type(2)));
+
+template <int S>
+__global__ void __launch_bounds__(64 * GT_QW) geneig_tri_ql_kernel(int nv, int np, double* __restrict__ scratch,
+                                                                   int64_t stride) {
+  constexpr int N = 64 * S;
+  __shared__ gt_f64x2 lds[GT_QW][2 * N + 64];
   const int n = nv;
-  const bool lead = threadIdx.x == 0;
-  TriPoint pt(scratch + blockIdx.x * stride, n);
-  for (int j = threadIdx.x; j < n; j += 64) {
-    d[j] = pt.d[j];
-    e[j] = pt.e[j];
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int point = blockIdx.x * GT_QW + wave;
+  if (point >= np) return;  // uniform over the wave; the kernel has no barrier
+  const bool lead = lane == 0;
+  TriPoint pt(scratch + point * stride, n);
+  gt_f64x2* de = lds[wave];     // (d_j, e_j)
+  gt_f64x2* cs = de + N;        // (c, s) of plane j
+  gt_f64x2* own = de + 2 * N;   // a slot per lane, (d, e) and (c, s) of the lanes whose writes are not wanted
+  auto sync = [] { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); };
+#pragma unroll
+  for (int q = 0; q < S; ++q) {
+    const int j = 64 * q + lane;
+    de[j] = j < n ? (gt_f64x2){pt.d[j], j < n - 1 ? pt.e[j] : 0.0} : (gt_f64x2){0.0, 0.0};
   }
-  __syncthreads();
+  sync();
   const int64_t cap = (int64_t)GT_REC_NN * n * n;
   double* rec = pt.rec;
   int64_t pos = 0;
   int l = 0, iters = 0, nrec = 0;
   bool ok = true;
-  // first m >= from with |e_m| <= eps (|d_m| + |d_m+1|), n - 1 if none (e_{n-1} = 0): the
-  // entries are read GT_U at a time (clamped to the arrays), then tested in order
-  auto split_at = [&](int from) {
-    for (int m0 = from; m0 < n - 1; m0 += GT_U) {
-      double ev[GT_U], dv[GT_U + 1];
-#pragma unroll
-      for (int u = 0; u < GT_U; ++u) ev[u] = e[min(m0 + u, n - 1)];
-#pragma unroll
-      for (int u = 0; u <= GT_U; ++u) dv[u] = d[min(m0 + u, n - 1)];
-#pragma unroll
-      for (int u = 0; u < GT_U; ++u)
-        if (m0 + u >= n - 1 || fabs(ev[u]) <= GT_EPS * (fabs(dv[u]) + fabs(dv[u + 1]))) return min(m0 + u, n - 1);
-    }
-    return n - 1;
-  };
   for (;;) {
-    int mm = -1;
-    while (l < n) {
-      const int m = l < n - 1 ? split_at(l) : l;
-      if (m == l) {
-        ++l;
-        continue;
+    // first j >= l that does not split, then the first m > j that does: bit j of neg is
+    // |e_j| <= eps (|d_j| + |d_j+1|), set from n - 1 on
+    int mm = n;
+    bool open = true;  // no block found yet
+#pragma unroll
+    for (int q = 0; q < S; ++q) {
+      if (64 * q + 63 < l || mm < n) continue;
+      const int j = 64 * q + lane;
+      const gt_f64x2 x = de[j], y = de[j + 1 < n ? j + 1 : j];
+      uint64_t neg = __ballot(j >= n - 1 || fabs(x.y) <= GT_EPS * (fabs(x.x) + fabs(y.x)));
+      const int lo = l - 64 * q;
+      uint64_t from = lo > 0 ? ~(uint64_t)0 << lo : ~(uint64_t)0;
+      if (open) {
+        const uint64_t w = ~neg & from;
+        if (!w) continue;
+        const int b = __builtin_ctzll(w);
+        l = 64 * q + b;
+        open = false;
+        from = ~(uint64_t)0 << b;
       }
-      mm = m;
-      break;
+      neg &= from;
+      if (neg) mm = 64 * q + __builtin_ctzll(neg);
     }
-    if (mm < 0) break;
+    if (open) break;
+    mm = mm < n - 1 ? mm : n - 1;
     if (++iters > GT_MAX_QL * n || nrec >= GT_REC_IT * n || pos + 2 * (mm - l) > cap) {
       ok = false;
       break;
     }
     // shift: the eigenvalue of the leading 2 x 2 block nearer d_l
-    double g = (d[l + 1] - d[l]) / (2.0 * e[l]);
+    const gt_f64x2 el = de[l], el1 = de[l + 1], em = de[mm];
+    double g = (el1.x - el.x) / (2.0 * el.y);
     double r = sqrt(g * g + 1.0);
-    const double gs = d[mm] - d[l] + e[l] / (g + (g >= 0.0 ? r : -r));
-    // The iteration's rotations run without the split test (ss = 0: the block splits at
+    const double gs = em.x - el.x + el.y / (g + (g >= 0.0 ? r : -r));
+    // The iteration's rotations run without the split test (f^2 + g^2 = 0: the block splits at
     // i + 1), which as a branch in the chain cost a fifth of the kernel's time.  A split
     // leaves NaN in the chain from there on, so a NaN g at the end sends the iteration back
     // to the block's entries as they were and through the loop that tests every step.
-    for (int j = l + (int)threadIdx.x; j <= mm; j += 64) {
-      d0[j] = d[j];
-      e0[j] = e[j];
-    }
-    const int64_t pos0 = pos;
+    gt_f64x2 keep[S];
+#pragma unroll
+    for (int q = 0; q < S; ++q) keep[q] = de[64 * q + lane];
     double s, c, p;
     int i;
     auto iterate = [&](auto tested) {
@@ -975,68 +986,88 @@ __global__ void __launch_bounds__(64) geneig_tri_ql_kernel(int nv, double* __res
       s = 1.0;
       c = 1.0;
       p = 0.0;
-      pos = pos0;
       i = mm - 1;
-      double ei = e[i], di = d[i], di1 = d[i + 1];  // entries the step reads, loaded one step ahead
+      gt_f64x2* out = lead ? de + mm : own + lane;  // entry i + 1 (lane 0)
+      const int step = lead ? 1 : 0;
+      const int csoff = lead ? N - 1 : 0;  // from entry i + 1 of de to plane i of cs
+      gt_f64x2 x = de[i];
+      double di1 = em.x;
       for (; i >= l; --i) {
-        const double en = e[i > 0 ? i - 1 : 0], dn = d[i > 0 ? i - 1 : 0];  // unconditional loads
-        const double f = s * ei, b = c * ei;
-        const double ss = f * f + g * g;
-        if (TESTED && ss == 0.0) {  // the block splits at i + 1: drop the shift and redo the block
-          e[i + 1] = 0.0;
-          d[i + 1] = di1 - p;
-          e[mm] = 0.0;
+        const gt_f64x2 xn = de[i > 0 ? i - 1 : 0];  // unconditional load
+        const double f = s * x.y;
+        const double ss = fma(f, f, g * g);
+        if (TESTED && __builtin_amdgcn_readfirstlane(ss == 0.0 ? 1 : 0)) {
+          // the block splits at i + 1: drop the shift and redo the block
+          sync();
+          if (lead) {
+            de[i + 1] = (gt_f64x2){di1 - p, 0.0};
+            de[mm].y = 0.0;
+          }
+          sync();
           break;
         }
-        const double inv = gt_rsqrt(ss);
-        r = ss * inv;
-        e[i + 1] = r;
-        s = f * inv;
+        const double y = __builtin_amdgcn_rsq(ss);
+        const double b = c * x.y;
+        const double a = di1 - p;
+        const double h = fma(2.0 * g, b, (x.x - a) * f);
+        const double er = fma(-(ss * y), y, 1.0);
+        const double inv = fma(y * er, fma(0.375, er, 0.5), y);
         c = g * inv;
-        g = di1 - p;
-        r = (di - g) * s + 2.0 * c * b;
-        p = s * r;
-        d[i + 1] = g + p;
-        g = c * r - b;
-        if (lead) {
-          rec[pos] = c;
-          rec[pos + 1] = s;
-        }
-        pos += 2;
-        ei = en;
-        di1 = di;
-        di = dn;
+        s = f * inv;
+        const double t = h * inv;
+        g = fma(c, t, -b);
+        p = s * t;
+        *out = (gt_f64x2){fma(s, t, a), ss * inv};
+        out[csoff] = (gt_f64x2){c, s};
+        out -= step;
+        di1 = x.x;
+        x = xn;
       }
     };
     iterate(std::false_type{});
+    sync();
     if (__builtin_amdgcn_readfirstlane(g != g ? 1 : 0)) {  // every lane holds the same g
-      __syncthreads();
-      for (int j = l + (int)threadIdx.x; j <= mm; j += 64) {
-        d[j] = d0[j];
-        e[j] = e0[j];
-      }
-      __syncthreads();
+#pragma unroll
+      for (int q = 0; q < S; ++q) de[64 * q + lane] = keep[q];
+      sync();
       iterate(std::true_type{});
+      sync();
     }
     if (i + 1 < mm) {
+      for (int j = i + 1 + lane; j < mm; j += 64) *(gt_f64x2*)(rec + pos + 2 * (mm - 1 - j)) = cs[j];
+      pos += 2 * (mm - 1 - i);
       if (lead) {
         pt.hdr[2 * nrec] = mm;
         pt.hdr[2 * nrec + 1] = i + 1;
       }
       ++nrec;
     }
-    if (i < l) {
-      d[l] -= p;
-      e[l] = g;
-      e[mm] = 0.0;
+    if (i < l && lead) {
+      de[l] = (gt_f64x2){de[l].x - p, g};
+      de[mm].y = 0.0;
     }
+    sync();
   }
-  for (int j = threadIdx.x; j < n; j += 64) pt.eig[j] = d[j];
+#pragma unroll
+  for (int q = 0; q < S; ++q)
+    if (64 * q + lane < n) pt.eig[64 * q + lane] = de[64 * q + lane].x;
   if (lead) {
     pt.status[1] = nrec;
     pt.status[2] = (double)(pos / 2);
     pt.status[0] = ok ? 0.0 : 1.0;
   }
+}
+
+// S: the groups of 64 entries that T takes
+hipError_t launch_ql(int np, int n, double* scratch, int64_t stride, hipStream_t stream) {
+  const dim3 grid((np + GT_QW - 1) / GT_QW), block(64 * GT_QW);
+  if (n <= 64)
+    hipLaunchKernelGGL(geneig_tri_ql_kernel<1>, grid, block, 0, stream, n, np, scratch, stride);
+  else if (n <= 128)
+    hipLaunchKernelGGL(geneig_tri_ql_kernel<2>, grid, block, 0, stream, n, np, scratch, stride);
+  else
+    hipLaunchKernelGGL(geneig_tri_ql_kernel<4>, grid, block, 0, stream, n, np, scratch, stride);
+  return hipGetLastError();
 }
 
 // c. Rows of U = Q Y, 64 per workgroup, one per lane (in LDS as L[j][lane], so a wave's
@@ -1916,7 +1947,7 @@ hipError_t launch_geneig_backward(int nv, int ntb, const double* k_w, const doub
     for (int pass = 0; pass < 2; ++pass) {
       hipLaunchKernelGGL(geneig_tri_reduce_kernel, dim3(np), dim3(GT_TH), 0, stream, nv, pass ? nullptr : kw,
                          scratch, stride);
-      hipLaunchKernelGGL(geneig_tri_ql_kernel, dim3(np), dim3(64), 0, stream, nv, scratch, stride);
+      launch_ql(np, nv, scratch, stride, stream);
       hipLaunchKernelGGL(geneig_tri_vectors_kernel, dim3(tri_vectors_groups(np, nv)), dim3(64 * (GT_VW + 1)), vec_lds, stream,
                          nv, np, scratch, stride);
       if (pass == 0)
@@ -1957,7 +1988,7 @@ hipError_t launch_geneig_trace(int nv, int ntb, const double* k_w, const double*
     int32_t* rk = ranks ? ranks + i0 : nullptr;
     const double* sf = s_floor ? s_floor + i0 : nullptr;
     hipLaunchKernelGGL(geneig_tri_reduce_kernel, dim3(np), dim3(GT_TH), 0, stream, nv, kw, scratch, stride);
-    hipLaunchKernelGGL(geneig_tri_ql_kernel, dim3(np), dim3(64), 0, stream, nv, scratch, stride);
+    launch_ql(np, nv, scratch, stride, stream);
     hipLaunchKernelGGL(geneig_tri_vectors_kernel, dim3(tri_vectors_groups(np, nv)), dim3(64 * (GT_VW + 1)), vec_lds, stream, nv,
                        np, scratch, stride);
     if (nvh == 0) {
@@ -1972,7 +2003,7 @@ hipError_t launch_geneig_trace(int nv, int ntb, const double* k_w, const double*
                          trw + i0, dos + i0, rk, rank_stride, scratch, stride, hs, sf);
       hipLaunchKernelGGL(geneig_tri_reduce_kernel, dim3(np), dim3(GT_TH), 0, stream, nv, (const double*)nullptr,
                          scratch, stride);
-      hipLaunchKernelGGL(geneig_tri_ql_kernel, dim3(np), dim3(64), 0, stream, nv, scratch, stride);
+      launch_ql(np, nv, scratch, stride, stream);
       hipLaunchKernelGGL(geneig_tri_vectors_kernel, dim3(tri_vectors_groups(np, nv)), dim3(64 * (GT_VW + 1)), vec_lds, stream,
                          nv, np, scratch, stride);
       hipLaunchKernelGGL(geneig_tri_hyb_finish_kernel, dim3(np), dim3(GT_TH), 0, stream, nv, nvh, g_max, rho,
