@@ -644,6 +644,7 @@ constexpr int GT_TH = 256;           // one lane per matrix row or column (n <= 
 constexpr int GT_MAX_QL = 30;        // QL iterations allowed per eigenvalue, on average
 constexpr double GT_EPS = 0x1p-52;   // deflation and bisection tolerance unit
 constexpr int GT_U = 8;              // loads a lane issues before it uses the first
+constexpr int GT_REG_NV = 128;       // largest N_v whose matrices sit in a workgroup's registers
 
 struct TriShared {
   double d[GE_MAX_NV];
@@ -803,27 +804,172 @@ __device__ __forceinline__ void tri_reduce(double* A, int n, int ld, TriShared& 
   __syncthreads();
 }
 
-// Eigenvalue j (ascending) of T = (sh.d, sh.e), n x n, by bisection: the count of
-// eigenvalues below x is the number of negative pivots of the LDL^T factorisation of
-// T - x I (Sturm), pivots of magnitude <= pivmin replaced by -pivmin.  The search runs
+// The same reduction for n <= 16 T <= 128 with the matrix in registers: the 256 lanes form a 16 x
+// 16 grid, lane (tr, tc) holding the entries (tr + 16 a, tc + 16 b) of both triangles (zero
+// past n).  A step broadcasts its column through LDS, takes the reflector from it (every group
+// of 16 lanes sums the whole column: lane tc has the entries tc + 16 b), forms A v by lane
+// partial sums added over the 16 lanes of a row of the grid, exchanges A v through LDS and
+// updates the block: two barriers.  The loop over k is unrolled by blocks of 16, so that finished
+// blocks drop out.  REFL: v_k goes to row k of `refl` (row stride n), as tri_reduce leaves it.
+// What bounds it: the steps' chain of LDS round trips, two sums over lanes, a square root and two
+// divisions, about 2000 cycles; from global scratch (tri_reduce) each step also waited for the
+// trailing block's trip through the L2, 1.99 ms for 1000 points of N_v = 128.
+// Measured: 0.44 ms.
+template <int CTRL>
+__device__ __forceinline__ double gt_dpp(double v) {
+  const int64_t b = __builtin_bit_cast(int64_t, v);
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)b, CTRL, 0xF, 0xF, true);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(b >> 32), CTRL, 0xF, 0xF, true);
+  return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
+// sum over the 16 lanes of a DPP row, in every one of them
+__device__ __forceinline__ double gt_sum16(double v) {
+  v += gt_dpp<0xB1>(v);   // quad_perm 1,0,3,2
+  v += gt_dpp<0x4E>(v);   // quad_perm 2,3,0,1
+  v += gt_dpp<0x141>(v);  // row_half_mirror
+  v += gt_dpp<0x140>(v);  // row_mirror
+  return v;
+}
+
+struct RegShared {
+  double x[GT_REG_NV];  // a step's column
+  double p[GT_REG_NV];  // A v
+  double d[GT_REG_NV], e[GT_REG_NV], tau[GT_REG_NV];
+};
+
+template <int T, bool REFL, int kb>
+__device__ __forceinline__ void reg_reduce_from(double (&A)[T][T], int n, double* __restrict__ refl, RegShared& sh) {
+  const int tr = threadIdx.x >> 4, tc = threadIdx.x & 15;
+  const int kend = n - 2 - 16 * kb < 16 ? n - 2 - 16 * kb : 16;
+#pragma unroll 1
+  for (int kk = 0; kk < kend; ++kk) {
+    const int k = 16 * kb + kk;
+    if (tc == kk) {
+#pragma unroll
+      for (int a = kb; a < T; ++a) sh.x[tr + 16 * a] = A[a][kb];
+      if (tr == kk) sh.d[k] = A[kb][kb];
+    }
+    __syncthreads();
+    double vr[T], vc[T];
+    double s2 = 0.0;
+#pragma unroll
+    for (int b = kb; b < T; ++b) {
+      vr[b] = sh.x[tr + 16 * b];
+      vc[b] = sh.x[tc + 16 * b];
+      const double t = tc + 16 * b > k + 1 ? vc[b] : 0.0;
+      s2 = fma(t, t, s2);
+    }
+    const double alpha = sh.x[k + 1];
+    s2 = gt_sum16(s2);
+    double tau = 0.0, beta = alpha, scl = 0.0;
+    if (s2 > 0.0) {  // uniform over the workgroup
+      const double nrm = sqrt(fma(alpha, alpha, s2));
+      beta = alpha >= 0.0 ? -nrm : nrm;
+      tau = (beta - alpha) / beta;
+      scl = 1.0 / (alpha - beta);
+    }
+#pragma unroll
+    for (int b = kb; b < T; ++b) {
+      const int r = tr + 16 * b, c = tc + 16 * b;
+      vr[b] = r > k + 1 ? vr[b] * scl : r == k + 1 ? 1.0 : 0.0;
+      vc[b] = c > k + 1 ? vc[b] * scl : c == k + 1 ? 1.0 : 0.0;
+    }
+    if (threadIdx.x == 0) {
+      sh.e[k] = beta;
+      sh.tau[k] = tau;
+    }
+    if (REFL && tr == 0) {
+#pragma unroll
+      for (int b = kb; b < T; ++b) {
+        const int c = tc + 16 * b;
+        if (c > k && c < n) refl[(int64_t)k * n + c] = vc[b];
+      }
+    }
+    if (tau == 0.0) {  // H = I (uniform)
+      __syncthreads();
+      continue;
+    }
+    double pr[T];
+#pragma unroll
+    for (int a = kb; a < T; ++a) {
+      double t = 0.0;
+#pragma unroll
+      for (int b = kb; b < T; ++b) t = fma(A[a][b], vc[b], t);
+      pr[a] = gt_sum16(t);
+    }
+    if (tc == 0) {
+#pragma unroll
+      for (int a = kb; a < T; ++a) sh.p[tr + 16 * a] = pr[a];
+    }
+    __syncthreads();
+    double pc[T], dot = 0.0;
+#pragma unroll
+    for (int b = kb; b < T; ++b) {
+      pc[b] = sh.p[tc + 16 * b];
+      dot = fma(vc[b], pc[b], dot);
+    }
+    const double h = 0.5 * tau * tau * gt_sum16(dot);
+    // w = tau A v - h v on the rows and columns past k, 0 before
+#pragma unroll
+    for (int b = kb; b < T; ++b) {
+      pr[b] = tr + 16 * b > k ? fma(-h, vr[b], tau * pr[b]) : 0.0;
+      pc[b] = tc + 16 * b > k ? fma(-h, vc[b], tau * pc[b]) : 0.0;
+    }
+#pragma unroll
+    for (int a = kb; a < T; ++a)
+#pragma unroll
+      for (int b = kb; b < T; ++b) A[a][b] = fma(-pr[a], vc[b], fma(-vr[a], pc[b], A[a][b]));
+  }
+  if constexpr (kb + 1 < T) reg_reduce_from<T, REFL, kb + 1>(A, n, refl, sh);
+}
+
+template <int T, bool REFL>
+__device__ __forceinline__ void reg_reduce(double (&A)[T][T], int n, double* __restrict__ refl, RegShared& sh) {
+  const int tr = threadIdx.x >> 4, tc = threadIdx.x & 15;
+  reg_reduce_from<T, REFL, 0>(A, n, refl, sh);
+  // the last 2 x 2 block
+#pragma unroll
+  for (int a = 0; a < T; ++a)
+#pragma unroll
+    for (int b = 0; b < T; ++b) {
+      const int r = tr + 16 * a, c = tc + 16 * b;
+      if (r == c && r < n && r >= n - 2) sh.d[r] = A[a][b];
+      if (r == n - 1 && c == n - 2) sh.e[c] = A[a][b];
+    }
+  if (threadIdx.x == 0) {
+    sh.e[n - 1] = 0.0;
+    sh.tau[n - 1] = 0.0;
+    if (n >= 2) sh.tau[n - 2] = 0.0;
+  }
+  __syncthreads();
+}
+
+// Sturm count: the eigenvalues of T = (d, e) below x, as the negative pivots of the LDL^T
+// factorisation of T - x I, pivots of magnitude <= pivmin replaced by -pivmin.
+__device__ __forceinline__ int tri_count(int n, const double* d, const double* e2, double x, double pivmin) {
+  double q = d[0] - x;
+  if (fabs(q) <= pivmin) q = -pivmin;
+  int cnt = q < 0.0;
+  for (int i = 1; i < n; ++i) {
+    q = (d[i] - x) - e2[i - 1] / q;
+    if (fabs(q) <= pivmin) q = -pivmin;
+    cnt += q < 0.0;
+  }
+  return cnt;
+}
+
+// Eigenvalue j (ascending) of T = (d, e), n x n, by bisection on the counts.  The search runs
 // from the Gershgorin interval until its width is <= 2 eps ||T|| (the midpoint is
-// returned).  sh.w[0] must hold e_i^2, and e2max their maximum.
-__device__ __forceinline__ double tri_bisect(int j, int n, const TriShared& sh, double glo, double ghi, double e2max) {
+// returned).  e2 holds e_i^2, and e2max is their maximum.
+__device__ __forceinline__ double tri_bisect(int j, int n, const double* d, const double* e2, double glo, double ghi,
+                                             double e2max) {
   const double tn = fmax(fabs(glo), fabs(ghi));
   const double tol = fmax(2.0 * GT_EPS * tn, 1e-300);
   const double pivmin = 0x1p-1022 * fmax(1.0, e2max);
   double a = glo - tol, b = ghi + tol;
   for (int it = 0; it < 128 && b - a > tol; ++it) {
     const double x = 0.5 * (a + b);
-    double q = sh.d[0] - x;
-    if (fabs(q) <= pivmin) q = -pivmin;
-    int cnt = q < 0.0;
-    for (int i = 1; i < n; ++i) {
-      q = (sh.d[i] - x) - sh.w[0][i - 1] / q;
-      if (fabs(q) <= pivmin) q = -pivmin;
-      cnt += q < 0.0;
-    }
-    if (cnt > j)
+    if (tri_count(n, d, e2, x, pivmin) > j)
       b = x;
     else
       a = x;
@@ -886,6 +1032,37 @@ __global__ void __launch_bounds__(GT_TH) geneig_tri_reduce_kernel(int nv, const 
   }
 }
 
+// a, for N_v <= 128, in registers
+template <int T>
+constexpr int reg_waves() {  // waves per SIMD: 2 T^2 registers for the matrix, about 10 T beside it
+  return T <= 4 ? 4 : T <= 6 ? 3 : 2;
+}
+
+template <int T>
+__global__ void __launch_bounds__(GT_TH, reg_waves<T>())
+    geneig_reg_reduce_kernel(int nv, const double* __restrict__ k_w, double* __restrict__ scratch, int64_t stride) {
+  __shared__ RegShared sh;
+  const int n = nv;
+  const int tid = threadIdx.x, tr = tid >> 4, tc = tid & 15;
+  TriPoint pt(scratch + blockIdx.x * stride, n);
+  double A[T][T];
+  const double* src = k_w ? k_w + blockIdx.x * (int64_t)n * n : pt.a;
+#pragma unroll
+  for (int a = 0; a < T; ++a)
+#pragma unroll
+    for (int b = 0; b < T; ++b) {
+      const int r = tr + 16 * a, c = tc + 16 * b;
+      A[a][b] = r < n && c < n ? 0.5 * (src[(int64_t)r * n + c] + src[(int64_t)c * n + r]) : 0.0;
+    }
+  __syncthreads();  // pt.a, which the reflectors overwrite, is read
+  reg_reduce<T, true>(A, n, pt.a, sh);
+  for (int j = tid; j < n; j += GT_TH) {
+    pt.d[j] = sh.d[j];
+    pt.e[j] = sh.e[j];
+    pt.tau[j] = sh.tau[j];
+  }
+}
+
 // b. Implicit QL with Wilkinson shifts on T: it finds the next unreduced block [l, m]
 // (|e_m| <= eps (|d_m| + |d_m+1|) splits it), takes one shifted iteration on it and
 // records the iteration's rotations (c_i, s_i), i = m-1 down to i0, in the stream pt.rec,
@@ -905,7 +1082,10 @@ __global__ void __launch_bounds__(GT_TH) geneig_tri_reduce_kernel(int nv, const 
 // factor does not wait for inv.  The split search tests 64 entries at once.  Four points share
 // a workgroup: its four waves land on the four SIMDs of a CU, where single-wave workgroups
 // doubled up on some and left others idle.
-// MEASURED_QL
+// Measured: 4.09 to 2.08 ms for 1000 points of N_v = 128 (d and e in separate LDS arrays written
+// by all lanes, lane 0 storing each rotation to global memory, and 15 dependent operations a
+// rotation instead of nine).  Holding T in lanes (v_readlane, v_cndmask) took 3.87 ms: 50
+// vector instructions a rotation against 28.
 constexpr int GT_QW = 4;  // points per workgroup
 typedef double gt_f64x2 __attribute__((ext_vector_type(2)));
 
@@ -1070,7 +1250,143 @@ hipError_t launch_ql(int np, int n, double* scratch, int64_t stride, hipStream_t
   return hipGetLastError();
 }
 
-// c. Rows of U = Q Y, 64 per workgroup, one per lane (in LDS as L[j][lane], so a wave's
+// c. Rows of U = Q Y for N_v <= 128, one row per lane and in its registers: row r starts as
+// e_r, takes x <- x H_k for k = 0..n-3 (x - tau (x.v) v^T), then the recorded rotations, and is
+// written to Z^T[.][r].  A wave takes 64 rows of one point; four waves to a workgroup, no
+// barrier.  Reflectors and rotations are the same for every lane: the wave loads the next one
+// (a reflector, or an iteration's rotations) while it applies this one, and leaves it in LDS by
+// entry (by plane), zeros (identity rotations) where it has none, for the lanes to read
+// together.  The row's entries are register names, so the loops run over chunks of eight
+// entries unrolled, skipping those out of range.
+// What bounds it: the vector units, four FP64 operations a rotation, and the LDS reads of (c, s);
+// held in LDS instead, the 64 rows of a wave fill 64 KB at N_v = 128, two waves a CU.
+// Measured at N_v = 128, 1000 points: 1.41 ms, from 5.3 ms with the rows in LDS; (c, s) through the
+// scalar cache instead of LDS left a wait at every eight rotations, 5.0 ms.
+template <int T>
+constexpr int vec_waves() {  // waves per SIMD that the row's 32 T registers leave room for
+  return T <= 1 ? 4 : T <= 6 ? 2 : 1;
+}
+
+template <int T>
+__global__ void __launch_bounds__(256, vec_waves<T>())
+    geneig_tri_rows_kernel(int nv, int items, double* __restrict__ scratch, int64_t stride) {
+  constexpr int NP = 16 * T, NC = NP / 8, S = (NP + 63) / 64;
+  __shared__ gt_f64x2 lds[4][2][NP];
+  const int n = nv;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int item = blockIdx.x * 4 + wave;
+  if (item >= items) return;  // uniform over the wave; the kernel has no barrier
+  const int nch = (n + 63) / 64;
+  const int point = item / nch;
+  const int r = (item - point * nch) * 64 + lane;
+  TriPoint pt(scratch + point * stride, n);
+  if (pt.status[0] != 0.0) return;
+  const int nit = (int)pt.status[1];
+  auto sync = [] { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); };
+  double x[NP];
+#pragma unroll
+  for (int j = 0; j < NP; ++j) x[j] = j == r ? 1.0 : 0.0;
+  // reflectors: entries k + 1 .. n - 1 of row k
+  {
+    double nx[S], nt = n > 2 ? pt.tau[0] : 0.0;
+    auto fetch = [&](int k) {
+#pragma unroll
+      for (int q = 0; q < S; ++q) {
+        const int j = 64 * q + lane;
+        nx[q] = pt.a[(int64_t)k * n + (j < n ? j : n - 1)];
+      }
+      nt = pt.tau[k];
+    };
+    if (n > 2) fetch(0);
+    for (int k = 0; k + 2 < n; ++k) {
+      double* v = (double*)lds[wave][k & 1];
+      const double tk = nt;
+#pragma unroll
+      for (int q = 0; q < S; ++q) {
+        const int j = 64 * q + lane;
+        if (j < NP) v[j] = j > k && j < n ? nx[q] : 0.0;
+      }
+      if (k + 3 < n) fetch(k + 1);
+      sync();
+      double acc[4] = {};
+#pragma unroll
+      for (int c = 0; c < NC; ++c) {
+        if (8 * c + 7 <= k) continue;
+        double vv[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) vv[u] = v[8 * c + u];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) acc[u & 3] = fma(x[8 * c + u], vv[u], acc[u & 3]);
+      }
+      const double y = -tk * ((acc[0] + acc[1]) + (acc[2] + acc[3]));
+#pragma unroll
+      for (int c = 0; c < NC; ++c) {
+        if (8 * c + 7 <= k) continue;
+        double vv[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) vv[u] = v[8 * c + u];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) x[8 * c + u] = fma(y, vv[u], x[8 * c + u]);
+      }
+      sync();
+    }
+  }
+  // rotations of plane i (columns i, i + 1), i = mm - 1 down to i0 in each iteration
+  if (nit > 0) {
+    int mm = pt.hdr[0], i0 = pt.hdr[1];
+    int mm2 = nit > 1 ? pt.hdr[2] : mm, i02 = nit > 1 ? pt.hdr[3] : i0;  // of the next iteration
+    const gt_f64x2* rec = (const gt_f64x2*)pt.rec;  // of this iteration
+    gt_f64x2 nx[S];
+    auto fetch = [&](const gt_f64x2* rc, int m, int lo) {
+#pragma unroll
+      for (int q = 0; q < S; ++q) {
+        const int i = 64 * q + lane;
+        nx[q] = rc[i >= lo && i < m ? m - 1 - i : 0];
+      }
+    };
+    fetch(rec, mm, i0);
+    for (int it = 0; it < nit; ++it) {
+      gt_f64x2* cs = lds[wave][it & 1];
+#pragma unroll
+      for (int q = 0; q < S; ++q) {
+        const int i = 64 * q + lane;
+        if (i < NP) cs[i] = i >= i0 && i < mm ? nx[q] : (gt_f64x2){1.0, 0.0};
+      }
+      rec += mm - i0;
+      if (it + 1 < nit) fetch(rec, mm2, i02);
+      const int mm3 = it + 2 < nit ? pt.hdr[2 * it + 4] : 0, i03 = it + 2 < nit ? pt.hdr[2 * it + 5] : 0;
+      sync();
+#pragma unroll
+      for (int c = NC - 1; c >= 0; --c) {
+        if (8 * c >= mm || 8 * c + 7 < i0) continue;
+        gt_f64x2 w[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) w[u] = cs[8 * c + 7 - u];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+          const int i = 8 * c + 7 - u;
+          if (i + 1 >= NP) continue;
+          const double hi = x[i + 1], lo = x[i];
+          x[i + 1] = fma(w[u].y, lo, w[u].x * hi);
+          x[i] = fma(w[u].x, lo, -(w[u].y * hi));
+        }
+      }
+      sync();
+      mm = mm2;
+      i0 = i02;
+      mm2 = mm3;
+      i02 = i03;
+    }
+  }
+  if (r < n) {
+#pragma unroll
+    for (int j = 0; j < NP; ++j)
+      if (j < n) pt.zt[(int64_t)j * n + r] = x[j];
+  }
+}
+
+// c. The same above N_v = 128, 64 rows per workgroup, one per lane (in LDS as L[j][lane], so a wave's
 // accesses are contiguous): row r starts as e_r, takes x <- x H_k for k = 0..n-3
 // (x - tau (x.v) v^T), then the recorded rotations, and is written to Z^T[.][r].  The
 // reflector steps are shared by waves 0..GT_VW-1, each owning the entries j of every row in
@@ -1439,7 +1755,7 @@ __global__ void __launch_bounds__(GT_TH) geneig_tri_trace_kernel(int nv, const d
   for (int j = 0; j + 1 < r1; ++j) e2max = fmax(e2max, sh.e[j] * sh.e[j]);
   for (int j = tid; j + 1 < r1; j += GT_TH) sh.w[0][j] = sh.e[j] * sh.e[j];
   __syncthreads();
-  for (int j = tid; j < r1; j += GT_TH) sh.s[j] = tri_bisect(j, r1, sh, glo, ghi, e2max);
+  for (int j = tid; j < r1; j += GT_TH) sh.s[j] = tri_bisect(j, r1, sh.d, sh.w[0], glo, ghi, e2max);
   __syncthreads();
 
   // 4. range filter and trace, ascending order
@@ -1462,6 +1778,210 @@ __global__ void __launch_bounds__(GT_TH) geneig_tri_trace_kernel(int nv, const d
   }
 }
 
+
+// d, for N_v <= 128.  The two products run on v_mfma_f64_16x16x4_f64, operands from memory:
+// T1 = K_Z^T U~ S~^-1/2 (K_Z^T for K_Z: B becomes B^T, which the symmetrisation takes to the same
+// matrix), then the blocks a <= b of B = (U~ S~^-1/2)^T T1; wave w takes the block columns b = w,
+// w + 4.  B is reduced in registers.  Where two Sturm counts find every xi inside [0, (1 + rho)
+// g_max], the usual case, the trace is that of the tridiagonal matrix; else every xi is bisected.
+// What bounds it: the reduction's chain (reg_reduce).  With eight eigenvectors at a time against
+// lane-per-column products, the reduction in global scratch and 53 counts per xi, 1000 points
+// of N_v = 128 took 3.38 ms.
+// Measured: 0.66 ms.
+template <int T>
+__global__ void __launch_bounds__(GT_TH, reg_waves<T>())
+    geneig_reg_trace_kernel(int nv, const double* __restrict__ k_z, double g_max, double tau, double rho,
+                            double* __restrict__ dos, int32_t* __restrict__ ranks, int rank_stride,
+                            double* __restrict__ scratch, int64_t stride, const double* __restrict__ s_floor) {
+  typedef double f64x4 __attribute__((ext_vector_type(4)));
+  __shared__ RegShared sh;
+  __shared__ double scale[GT_REG_NV];
+  __shared__ int kidx[GT_REG_NV];
+  __shared__ double red[GT_TH / 64];
+  __shared__ int misc[3];
+  const int n = nv;
+  const int i = blockIdx.x;
+  const int tid = threadIdx.x, tr = tid >> 4, tc = tid & 15;
+  const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  TriPoint pt(scratch + i * stride, n);
+  if (*pt.status != 0.0) return;  // the Jacobi kernel writes this point
+  const double* kz = k_z + i * (int64_t)n * n;
+  // 2. truncation: wave 0, 64 eigenvalues at a time
+  if (wave == 0) {
+    double smax = -INFINITY;
+    for (int j = lane; j < n; j += 64) smax = fmax(smax, pt.eig[j]);
+    for (int o = 32; o > 0; o >>= 1) smax = fmax(smax, __shfl_xor(smax, o));
+    const double thr = s_floor ? fmax(tau * smax, s_floor[i]) : tau * smax;
+    int r1 = 0;
+    for (int j0 = 0; j0 < n; j0 += 64) {
+      const int j = j0 + lane;
+      const double sj = j < n ? pt.eig[j] : -INFINITY;
+      const bool keep = j < n && smax > 0.0 && sj >= thr;
+      const uint64_t m = __ballot(keep);
+      if (keep) {
+        const int at = r1 + __builtin_popcountll(m & (((uint64_t)1 << lane) - 1));
+        kidx[at] = j;
+        scale[at] = 1.0 / sqrt(sj);
+      }
+      r1 += __builtin_popcountll(m);
+    }
+    if (lane == 0) misc[0] = r1;
+  }
+  __syncthreads();
+  const int r1 = __builtin_amdgcn_readfirstlane(misc[0]);
+  if (r1 == 0) {
+    if (tid == 0) {
+      dos[i] = 0.0;
+      if (ranks) {
+        ranks[i] = 0;
+        ranks[rank_stride + i] = 0;
+      }
+    }
+    return;
+  }
+  // 3. the products, KB steps of four k at a time: their loads are issued together
+  constexpr int KB = T >= 7 ? 2 : 4;
+  const int nb = (r1 + 15) / 16, ldq = 16 * nb;
+  const int lm = lane & 15, lk = lane >> 4;
+  double* q = pt.rec;  // T1, n x ldq
+  int uo[T];           // eigenvector 16 a + lm's row of Z^T
+  double us[T];
+#pragma unroll
+  for (int a = 0; a < T; ++a) {
+    const int m = 16 * a + lm;
+    uo[a] = kidx[m < r1 ? m : 0] * n;
+    us[a] = m < r1 ? scale[m] : 0.0;
+  }
+#pragma unroll
+  for (int g = 0; g < (T + 3) / 4; ++g) {
+    const int b = wave + 4 * g;
+    if (b >= nb) continue;  // uniform over the wave
+    f64x4 acc[T];
+#pragma unroll
+    for (int a = 0; a < T; ++a) acc[a] = (f64x4){0.0, 0.0, 0.0, 0.0};
+    const int j = 16 * b + lm;
+    const double* u = pt.zt + (int64_t)kidx[j < r1 ? j : 0] * n;
+    const double sc = j < r1 ? scale[j] : 0.0;
+#pragma unroll 1
+    for (int k0 = 0; k0 < n; k0 += 4 * KB) {
+      double av[KB][T], bv[KB];
+#pragma unroll
+      for (int s = 0; s < KB; ++s) {
+        const int k = k0 + 4 * s + lk, kc = k < n ? k : n - 1;
+        bv[s] = u[kc];
+#pragma unroll
+        for (int a = 0; a < T; ++a) {
+          const int r = 16 * a + lm;
+          av[s][a] = kz[kc * n + (r < n ? r : n - 1)];
+        }
+      }
+#pragma unroll
+      for (int s = 0; s < KB; ++s) {
+        const double bb = k0 + 4 * s + lk < n ? bv[s] * sc : 0.0;
+#pragma unroll
+        for (int a = 0; a < T; ++a) acc[a] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[s][a], bb, acc[a], 0, 0, 0);
+      }
+    }
+#pragma unroll
+    for (int a = 0; a < T; ++a)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int r = 16 * a + lk + 4 * e;
+        if (r < n) q[r * ldq + j] = acc[a][e];
+      }
+  }
+  __threadfence_block();
+  __syncthreads();
+#pragma unroll
+  for (int g = 0; g < (T + 3) / 4; ++g) {
+    const int b = wave + 4 * g;
+    if (b >= nb) continue;
+    f64x4 acc[T];
+#pragma unroll
+    for (int a = 0; a < T; ++a) acc[a] = (f64x4){0.0, 0.0, 0.0, 0.0};
+    const int j = 16 * b + lm;
+#pragma unroll 1
+    for (int k0 = 0; k0 < n; k0 += 4 * KB) {
+      double av[KB][T], bv[KB];
+#pragma unroll
+      for (int s = 0; s < KB; ++s) {
+        const int k = k0 + 4 * s + lk, kc = k < n ? k : n - 1;
+        bv[s] = q[kc * ldq + j];
+#pragma unroll
+        for (int a = 0; a < T; ++a)
+          if (a <= b) av[s][a] = pt.zt[uo[a] + kc];
+      }
+#pragma unroll
+      for (int s = 0; s < KB; ++s) {
+        const double bb = k0 + 4 * s + lk < n ? bv[s] : 0.0;
+#pragma unroll
+        for (int a = 0; a < T; ++a)
+          if (a <= b) acc[a] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[s][a] * us[a], bb, acc[a], 0, 0, 0);
+      }
+    }
+#pragma unroll
+    for (int a = 0; a < T; ++a)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int r = 16 * a + lk + 4 * e;
+        if (a <= b && r < r1 && j < r1) pt.a[r * n + j] = acc[a][e];
+      }
+  }
+  __threadfence_block();
+  __syncthreads();
+  double A[T][T];
+#pragma unroll
+  for (int a = 0; a < T; ++a)
+#pragma unroll
+    for (int b = 0; b < T; ++b) {
+      const int r = tr + 16 * a, c = tc + 16 * b;
+      double v = 0.0;
+      if (r < r1 && c < r1)
+        v = a < b   ? pt.a[(int64_t)r * n + c]
+            : a > b ? pt.a[(int64_t)c * n + r]
+                    : 0.5 * (pt.a[(int64_t)r * n + c] + pt.a[(int64_t)c * n + r]);
+      A[a][b] = v;
+    }
+  reg_reduce<T, false>(A, r1, nullptr, sh);
+  // 4. range filter and trace
+  double* e2 = sh.x;
+  for (int j = tid; j + 1 < r1; j += GT_TH) e2[j] = sh.e[j] * sh.e[j];
+  __syncthreads();
+  double e2max = 0.0, glo = INFINITY, ghi = -INFINITY;
+  for (int j = 0; j + 1 < r1; ++j) e2max = fmax(e2max, e2[j]);
+  const double pivmin = 0x1p-1022 * fmax(1.0, e2max);
+  const double hi = (1.0 + rho) * g_max;
+  if (tid < 2) misc[1 + tid] = tri_count(r1, sh.d, e2, tid ? hi : 0.0, pivmin);
+  __syncthreads();
+  double part = 0.0;
+  int in = 0;
+  if (misc[1] == 0 && misc[2] == r1) {
+    if (tid < r1) part = sh.d[tid];
+    in = tid < r1;
+  } else {
+    for (int j = 0; j < r1; ++j) {
+      const double rad = (j > 0 ? fabs(sh.e[j - 1]) : 0.0) + (j + 1 < r1 ? fabs(sh.e[j]) : 0.0);
+      glo = fmin(glo, sh.d[j] - rad);
+      ghi = fmax(ghi, sh.d[j] + rad);
+    }
+    if (tid < r1) {
+      const double xi = tri_bisect(tid, r1, sh.d, e2, glo, ghi, e2max);
+      if (xi >= 0.0 && xi <= hi) {
+        part = xi;
+        in = 1;
+      }
+    }
+  }
+  const double tr_in = gt_sum(part, red);
+  const int r2 = __syncthreads_count(in);
+  if (tid == 0) {
+    dos[i] = tr_in;
+    if (ranks) {
+      ranks[i] = r1;
+      ranks[rank_stride + i] = r2;
+    }
+  }
+}
 
 // ---------------------------------------------------------------------------
 // Backward of Algorithm 4 on the tridiagonal path (N_v > 48), per group of points:
@@ -1859,6 +2379,78 @@ size_t geneig_lds_bytes(int nv) {
          (GE_MAX_NV + GE_MAX_NV + 4) * sizeof(int);
 }
 
+template <int T>
+hipError_t launch_rows_t(int np, int n, double* scratch, int64_t stride, hipStream_t stream) {
+  const int items = np * ((n + 63) / 64);
+  hipLaunchKernelGGL(geneig_tri_rows_kernel<T>, dim3((items + 3) / 4), dim3(256), 0, stream, n, items, scratch, stride);
+  return hipGetLastError();
+}
+
+template <int T>
+hipError_t launch_reduce_t(int np, int n, const double* kw, double* scratch, int64_t stride, hipStream_t stream) {
+  if ((n + 15) / 16 == T) {
+    hipLaunchKernelGGL(geneig_reg_reduce_kernel<T>, dim3(np), dim3(GT_TH), 0, stream, n, kw, scratch, stride);
+    return hipGetLastError();
+  }
+  if constexpr (T < GT_REG_NV / 16) return launch_reduce_t<T + 1>(np, n, kw, scratch, stride, stream);
+  return hipErrorInvalidValue;
+}
+
+// T of np points (kw null: of the matrices in their scratch): in registers up to N_v = 128
+hipError_t launch_reduce(int np, int n, const double* kw, double* scratch, int64_t stride, hipStream_t stream) {
+  if (n <= GT_REG_NV) return launch_reduce_t<1>(np, n, kw, scratch, stride, stream);
+  hipLaunchKernelGGL(geneig_tri_reduce_kernel, dim3(np), dim3(GT_TH), 0, stream, n, kw, scratch, stride);
+  return hipGetLastError();
+}
+
+template <int T>
+hipError_t launch_reg_trace_t(int np, int n, const double* kz, double g_max, double tau, double rho, double* dos,
+                              int32_t* ranks, int rank_stride, double* scratch, int64_t stride, const double* s_floor,
+                              hipStream_t stream) {
+  if ((n + 15) / 16 == T) {
+    hipLaunchKernelGGL(geneig_reg_trace_kernel<T>, dim3(np), dim3(GT_TH), 0, stream, n, kz, g_max, tau, rho, dos,
+                       ranks, rank_stride, scratch, stride, s_floor);
+    return hipGetLastError();
+  }
+  if constexpr (T < GT_REG_NV / 16)
+    return launch_reg_trace_t<T + 1>(np, n, kz, g_max, tau, rho, dos, ranks, rank_stride, scratch, stride, s_floor,
+                                     stream);
+  return hipErrorInvalidValue;
+}
+
+// steps 2-4 of np points
+hipError_t launch_tri_trace(int np, int n, const double* kz, double g_max, double tau, double rho, double* dos,
+                            int32_t* ranks, int rank_stride, double* scratch, int64_t stride, const double* s_floor,
+                            hipStream_t stream) {
+  if (n <= GT_REG_NV)
+    return launch_reg_trace_t<1>(np, n, kz, g_max, tau, rho, dos, ranks, rank_stride, scratch, stride, s_floor, stream);
+  hipLaunchKernelGGL(geneig_tri_trace_kernel, dim3(np), dim3(GT_TH), 0, stream, n, kz, g_max, tau, rho, dos, ranks,
+                     rank_stride, scratch, stride, s_floor);
+  return hipGetLastError();
+}
+
+// U of np points: rows in registers up to N_v = 128, in LDS above
+hipError_t launch_vectors(int np, int n, double* scratch, int64_t stride, hipStream_t stream) {
+  switch ((n + 15) / 16) {
+    case 1: return launch_rows_t<1>(np, n, scratch, stride, stream);
+    case 2: return launch_rows_t<2>(np, n, scratch, stride, stream);
+    case 3: return launch_rows_t<3>(np, n, scratch, stride, stream);
+    case 4: return launch_rows_t<4>(np, n, scratch, stride, stream);
+    case 5: return launch_rows_t<5>(np, n, scratch, stride, stream);
+    case 6: return launch_rows_t<6>(np, n, scratch, stride, stream);
+    case 7: return launch_rows_t<7>(np, n, scratch, stride, stream);
+    case 8: return launch_rows_t<8>(np, n, scratch, stride, stream);
+    default: break;
+  }
+  const size_t lds = tri_vectors_lds_doubles(n) * sizeof(double);
+  hipError_t err = hipFuncSetAttribute((const void*)geneig_tri_vectors_kernel,
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  if (err != hipSuccess) return err;
+  hipLaunchKernelGGL(geneig_tri_vectors_kernel, dim3(tri_vectors_groups(np, n)), dim3(64 * (GT_VW + 1)), lds, stream, n,
+                     np, scratch, stride);
+  return hipGetLastError();
+}
+
 template <int TH>
 hipError_t launch_backward_t(int nv, int ntb, const double* k_w, const double* k_z, double g_max, double tau,
                              double rho, const double* phibar, double* kw_bar, double* kz_bar, double* scratch,
@@ -1932,10 +2524,7 @@ hipError_t launch_geneig_backward(int nv, int ntb, const double* k_w, const doub
   const int64_t stride = geneig_tri_bwd_point_doubles(nv);
   const int64_t nn = (int64_t)nv * nv;
   const int64_t state_off = geneig_tri_point_doubles(nv) + 2 * nn + 3 * (int64_t)nv;  // TriBwd::state
-  const size_t vec_lds = tri_vectors_lds_doubles(nv) * sizeof(double);
-  hipError_t err = hipFuncSetAttribute((const void*)geneig_tri_vectors_kernel,
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)vec_lds);
-  if (err != hipSuccess) return err;
+  hipError_t err = hipSuccess;
   for (int i0 = 0; i0 < ntb; i0 += kGeTriChunk) {
     const int np = std::min(kGeTriChunk, ntb - i0);
     const double* kw = k_w + i0 * nn;
@@ -1945,11 +2534,9 @@ hipError_t launch_geneig_backward(int nv, int ntb, const double* k_w, const doub
     double* kzb = kz_bar + i0 * nn;
     const double* sf = s_floor ? s_floor + i0 : nullptr;
     for (int pass = 0; pass < 2; ++pass) {
-      hipLaunchKernelGGL(geneig_tri_reduce_kernel, dim3(np), dim3(GT_TH), 0, stream, nv, pass ? nullptr : kw,
-                         scratch, stride);
-      launch_ql(np, nv, scratch, stride, stream);
-      hipLaunchKernelGGL(geneig_tri_vectors_kernel, dim3(tri_vectors_groups(np, nv)), dim3(64 * (GT_VW + 1)), vec_lds, stream,
-                         nv, np, scratch, stride);
+      if ((err = launch_reduce(np, nv, pass ? nullptr : kw, scratch, stride, stream)) != hipSuccess) return err;
+      if ((err = launch_ql(np, nv, scratch, stride, stream)) != hipSuccess) return err;
+      if ((err = launch_vectors(np, nv, scratch, stride, stream)) != hipSuccess) return err;
       if (pass == 0)
         hipLaunchKernelGGL(geneig_tri_bwd_form_kernel, dim3(np), dim3(GT_TH), 0, stream, nv, kz, tau, pb, kwb, kzb,
                            scratch, stride, sf);
@@ -1977,23 +2564,18 @@ hipError_t launch_geneig_trace(int nv, int ntb, const double* k_w, const double*
   // the tridiagonal path, kGeTriChunk points at a time through the same scratch
   const int64_t stride = geneig_tri_point_doubles(nv);
   const int64_t nn = (int64_t)nv * nv;
-  const size_t vec_lds = tri_vectors_lds_doubles(nv) * sizeof(double);
-  hipError_t err = hipFuncSetAttribute((const void*)geneig_tri_vectors_kernel,
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)vec_lds);
-  if (err != hipSuccess) return err;
+  hipError_t err = hipSuccess;
   for (int i0 = 0; i0 < ntb; i0 += kGeTriChunk) {
     const int np = std::min(kGeTriChunk, ntb - i0);
     const double* kw = k_w + i0 * nn;
     const double* kz = k_z + i0 * nn;
     int32_t* rk = ranks ? ranks + i0 : nullptr;
     const double* sf = s_floor ? s_floor + i0 : nullptr;
-    hipLaunchKernelGGL(geneig_tri_reduce_kernel, dim3(np), dim3(GT_TH), 0, stream, nv, kw, scratch, stride);
-    launch_ql(np, nv, scratch, stride, stream);
-    hipLaunchKernelGGL(geneig_tri_vectors_kernel, dim3(tri_vectors_groups(np, nv)), dim3(64 * (GT_VW + 1)), vec_lds, stream, nv,
-                       np, scratch, stride);
+    if ((err = launch_reduce(np, nv, kw, scratch, stride, stream)) != hipSuccess) return err;
+    if ((err = launch_ql(np, nv, scratch, stride, stream)) != hipSuccess) return err;
+    if ((err = launch_vectors(np, nv, scratch, stride, stream)) != hipSuccess) return err;
     if (nvh == 0) {
-      hipLaunchKernelGGL(geneig_tri_trace_kernel, dim3(np), dim3(GT_TH), 0, stream, nv, kz, g_max, tau, rho,
-                         dos + i0, rk, rank_stride, scratch, stride, sf);
+      if ((err = launch_tri_trace(np, nv, kz, g_max, tau, rho, dos + i0, rk, rank_stride, scratch, stride, sf, stream)) != hipSuccess) return err;
       err = launch_jacobi_trace(nv, np, kw, kz, g_max, tau, rho, dos + i0, rk, scratch, 0, nullptr, nullptr, nullptr,
                                 sf, rank_stride, stream, stride, scratch + 6 * nn + 4 * nv);
     } else {  // B through the same kernels, then the trace and the hybrid term
@@ -2001,11 +2583,9 @@ hipError_t launch_geneig_trace(int nv, int ntb, const double* k_w, const double*
       double* hs = hscr + (int64_t)i0 * nvh * nv;
       hipLaunchKernelGGL(geneig_tri_hyb_form_kernel, dim3(np), dim3(GT_TH), 0, stream, nv, nvh, kz, kc, tau,
                          trw + i0, dos + i0, rk, rank_stride, scratch, stride, hs, sf);
-      hipLaunchKernelGGL(geneig_tri_reduce_kernel, dim3(np), dim3(GT_TH), 0, stream, nv, (const double*)nullptr,
-                         scratch, stride);
-      launch_ql(np, nv, scratch, stride, stream);
-      hipLaunchKernelGGL(geneig_tri_vectors_kernel, dim3(tri_vectors_groups(np, nv)), dim3(64 * (GT_VW + 1)), vec_lds, stream,
-                         nv, np, scratch, stride);
+      if ((err = launch_reduce(np, nv, nullptr, scratch, stride, stream)) != hipSuccess) return err;
+      if ((err = launch_ql(np, nv, scratch, stride, stream)) != hipSuccess) return err;
+      if ((err = launch_vectors(np, nv, scratch, stride, stream)) != hipSuccess) return err;
       hipLaunchKernelGGL(geneig_tri_hyb_finish_kernel, dim3(np), dim3(GT_TH), 0, stream, nv, nvh, g_max, rho,
                          trw + i0, dos + i0, rk, rank_stride, scratch, stride, hs);
       err = launch_jacobi_trace(nv, np, kw, kz, g_max, tau, rho, dos + i0, rk, scratch, nvh, kc, trw + i0, hs, sf,
