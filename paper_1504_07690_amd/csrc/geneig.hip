@@ -7,10 +7,11 @@
 //   4. keep xi in [0, (1 + rho) g_max], g_max = 1/(N sqrt(2 pi sigma^2))
 //   trace = sum of kept xi, r1 = |kept s|, r2 = |kept xi|.
 //
-// Two eigensolvers.  Above N_v = 48 the trace (with or without the hybrid term of
-// Algorithm 6) and its backward go through a tridiagonal matrix (Householder reduction;
-// implicit QL for step 1, bisection or QL for step 3), in kernels per group of points
-// (see geneig_tri_*).  At or below 48, and for points the QL gives up, one workgroup per
+// Two eigensolvers.  The trace (with or without the hybrid term of Algorithm 6) goes through a
+// tridiagonal matrix (Householder reduction; implicit QL for step 1, Sturm counts, bisection or QL
+// for step 3): up to N_v = 48 in one kernel (geneig_small_kernel), above in kernels per group
+// of points (geneig_tri_*), as does its backward above 48.  For the backward at or below 48, and
+// for points that these give up, one workgroup per
 // point runs parallel cyclic Jacobi: sweeps in round-robin (tournament) order, so each round
 // rotates N_v/2 disjoint index pairs at once: the pair angles are computed first
 // (Golub & Van Loan, symmetric 2x2 Schur), then the rows of every pair are rotated,
@@ -810,7 +811,7 @@ __device__ __forceinline__ void tri_reduce(double* A, int n, int ld, TriShared& 
 // of 16 lanes sums the whole column: lane tc has the entries tc + 16 b), forms A v by lane
 // partial sums added over the 16 lanes of a row of the grid, exchanges A v through LDS and
 // updates the block: two barriers.  The loop over k is unrolled by blocks of 16, so that finished
-// blocks drop out.  REFL: v_k goes to row k of `refl` (row stride n), as tri_reduce leaves it.
+// blocks drop out.  REFL: v_k goes to row k of `refl` (row stride ldr), as tri_reduce leaves it.
 // What bounds it: the steps' chain of LDS round trips, two sums over lanes, a square root and two
 // divisions, about 2000 cycles; from global scratch (tri_reduce) each step also waited for the
 // trailing block's trip through the L2, 1.99 ms for 1000 points of N_v = 128.
@@ -838,7 +839,8 @@ struct RegShared {
 };
 
 template <int T, bool REFL, int kb>
-__device__ __forceinline__ void reg_reduce_from(double (&A)[T][T], int n, double* __restrict__ refl, RegShared& sh) {
+__device__ __forceinline__ void reg_reduce_from(double (&A)[T][T], int n, double* __restrict__ refl, int ldr,
+                                                RegShared& sh) {
   const int tr = threadIdx.x >> 4, tc = threadIdx.x & 15;
   const int kend = n - 2 - 16 * kb < 16 ? n - 2 - 16 * kb : 16;
 #pragma unroll 1
@@ -882,7 +884,7 @@ __device__ __forceinline__ void reg_reduce_from(double (&A)[T][T], int n, double
 #pragma unroll
       for (int b = kb; b < T; ++b) {
         const int c = tc + 16 * b;
-        if (c > k && c < n) refl[(int64_t)k * n + c] = vc[b];
+        if (c > k && c < n) refl[(int64_t)k * ldr + c] = vc[b];
       }
     }
     if (tau == 0.0) {  // H = I (uniform)
@@ -920,13 +922,13 @@ __device__ __forceinline__ void reg_reduce_from(double (&A)[T][T], int n, double
 #pragma unroll
       for (int b = kb; b < T; ++b) A[a][b] = fma(-pr[a], vc[b], fma(-vr[a], pc[b], A[a][b]));
   }
-  if constexpr (kb + 1 < T) reg_reduce_from<T, REFL, kb + 1>(A, n, refl, sh);
+  if constexpr (kb + 1 < T) reg_reduce_from<T, REFL, kb + 1>(A, n, refl, ldr, sh);
 }
 
 template <int T, bool REFL>
-__device__ __forceinline__ void reg_reduce(double (&A)[T][T], int n, double* __restrict__ refl, RegShared& sh) {
+__device__ __forceinline__ void reg_reduce(double (&A)[T][T], int n, double* __restrict__ refl, int ldr, RegShared& sh) {
   const int tr = threadIdx.x >> 4, tc = threadIdx.x & 15;
-  reg_reduce_from<T, REFL, 0>(A, n, refl, sh);
+  reg_reduce_from<T, REFL, 0>(A, n, refl, ldr, sh);
   // the last 2 x 2 block
 #pragma unroll
   for (int a = 0; a < T; ++a)
@@ -1055,7 +1057,7 @@ __global__ void __launch_bounds__(GT_TH, reg_waves<T>())
       A[a][b] = r < n && c < n ? 0.5 * (src[(int64_t)r * n + c] + src[(int64_t)c * n + r]) : 0.0;
     }
   __syncthreads();  // pt.a, which the reflectors overwrite, is read
-  reg_reduce<T, true>(A, n, pt.a, sh);
+  reg_reduce<T, true>(A, n, pt.a, n, sh);
   for (int j = tid; j < n; j += GT_TH) {
     pt.d[j] = sh.d[j];
     pt.e[j] = sh.e[j];
@@ -1089,6 +1091,119 @@ __global__ void __launch_bounds__(GT_TH, reg_waves<T>())
 constexpr int GT_QW = 4;  // points per workgroup
 typedef double gt_f64x2 __attribute__((ext_vector_type(2)));
 
+// a wave's LDS writes before its lanes' reads of each other's
+__device__ __forceinline__ void wave_sync() { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); }
+
+// The first j >= l that does not split, then the first m > j that does (at most n - 1): true and
+// [l, mm], or false when T is diagonal from l on.  de_j = (d_j, e_j); n <= 64 S.
+template <int S>
+__device__ __forceinline__ bool ql_block(const gt_f64x2* de, int n, int lane, int& l, int& mm) {
+  mm = n;
+  bool open = true;  // no block found yet
+#pragma unroll
+  for (int q = 0; q < S; ++q) {
+    if (64 * q + 63 < l || mm < n) continue;
+    const int j = 64 * q + lane;
+    const gt_f64x2 x = de[j], y = de[j + 1 < n ? j + 1 : j];
+    // bit j: |e_j| <= eps (|d_j| + |d_j+1|), set from n - 1 on
+    uint64_t neg = __ballot(j >= n - 1 || fabs(x.y) <= GT_EPS * (fabs(x.x) + fabs(y.x)));
+    const int lo = l - 64 * q;
+    uint64_t from = lo > 0 ? ~(uint64_t)0 << lo : ~(uint64_t)0;
+    if (open) {
+      const uint64_t w = ~neg & from;
+      if (!w) continue;
+      const int b = __builtin_ctzll(w);
+      l = 64 * q + b;
+      open = false;
+      from = ~(uint64_t)0 << b;
+    }
+    neg &= from;
+    if (neg) mm = 64 * q + __builtin_ctzll(neg);
+  }
+  mm = mm < n - 1 ? mm : n - 1;
+  return !open;
+}
+
+// One shifted iteration on the block [l, mm]: its rotations of planes i0 .. mm - 1 go to cs.
+// Returns i0.  own: a slot per lane, which takes what the lanes but 0 write.
+template <int S>
+__device__ __forceinline__ int ql_iterate(gt_f64x2* de, gt_f64x2* cs, gt_f64x2* own, int lane, int l, int mm) {
+  const bool lead = lane == 0;
+  // shift: the eigenvalue of the leading 2 x 2 block nearer d_l
+  const gt_f64x2 el = de[l], el1 = de[l + 1], em = de[mm];
+  double g = (el1.x - el.x) / (2.0 * el.y);
+  double r = sqrt(g * g + 1.0);
+  const double gs = em.x - el.x + el.y / (g + (g >= 0.0 ? r : -r));
+  // The iteration's rotations run without the split test (f^2 + g^2 = 0: the block splits at
+  // i + 1), which as a branch in the chain cost a fifth of the kernel's time.  A split
+  // leaves NaN in the chain from there on, so a NaN g at the end sends the iteration back
+  // to the block's entries as they were and through the loop that tests every step.
+  gt_f64x2 keep[S];
+#pragma unroll
+  for (int q = 0; q < S; ++q) keep[q] = de[64 * q + lane];
+  double s, c, p;
+  int i;
+  auto iterate = [&](auto tested) {
+    constexpr bool TESTED = decltype(tested)::value;
+    g = gs;
+    s = 1.0;
+    c = 1.0;
+    p = 0.0;
+    i = mm - 1;
+    gt_f64x2* out = lead ? de + mm : own + lane;        // entry i + 1 (lane 0)
+    const int step = lead ? 1 : 0;
+    const int csoff = lead ? (int)(cs - de) - 1 : 0;    // from entry i + 1 of de to plane i of cs
+    gt_f64x2 x = de[i];
+    double di1 = em.x;
+    for (; i >= l; --i) {
+      const gt_f64x2 xn = de[i > 0 ? i - 1 : 0];  // unconditional load
+      const double f = s * x.y;
+      const double ss = fma(f, f, g * g);
+      if (TESTED && __builtin_amdgcn_readfirstlane(ss == 0.0 ? 1 : 0)) {
+        // the block splits at i + 1: drop the shift and redo the block
+        wave_sync();
+        if (lead) {
+          de[i + 1] = (gt_f64x2){di1 - p, 0.0};
+          de[mm].y = 0.0;
+        }
+        wave_sync();
+        break;
+      }
+      const double y = __builtin_amdgcn_rsq(ss);
+      const double b = c * x.y;
+      const double a = di1 - p;
+      const double h = fma(2.0 * g, b, (x.x - a) * f);
+      const double er = fma(-(ss * y), y, 1.0);
+      const double inv = fma(y * er, fma(0.375, er, 0.5), y);
+      c = g * inv;
+      s = f * inv;
+      const double t = h * inv;
+      g = fma(c, t, -b);
+      p = s * t;
+      *out = (gt_f64x2){fma(s, t, a), ss * inv};
+      out[csoff] = (gt_f64x2){c, s};
+      out -= step;
+      di1 = x.x;
+      x = xn;
+    }
+  };
+  iterate(std::false_type{});
+  wave_sync();
+  if (__builtin_amdgcn_readfirstlane(g != g ? 1 : 0)) {  // every lane holds the same g
+#pragma unroll
+    for (int q = 0; q < S; ++q) de[64 * q + lane] = keep[q];
+    wave_sync();
+    iterate(std::true_type{});
+    wave_sync();
+  }
+  if (i < l && lead) {
+    de[l] = (gt_f64x2){de[l].x - p, g};
+    de[mm].y = 0.0;
+  }
+  wave_sync();
+  return i + 1;
+}
+
 template <int S>
 __global__ void __launch_bounds__(64 * GT_QW) geneig_tri_ql_kernel(int nv, int np, double* __restrict__ scratch,
                                                                    int64_t stride) {
@@ -1099,139 +1214,41 @@ __global__ void __launch_bounds__(64 * GT_QW) geneig_tri_ql_kernel(int nv, int n
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int point = blockIdx.x * GT_QW + wave;
   if (point >= np) return;  // uniform over the wave; the kernel has no barrier
-  const bool lead = lane == 0;
   TriPoint pt(scratch + point * stride, n);
   gt_f64x2* de = lds[wave];     // (d_j, e_j)
   gt_f64x2* cs = de + N;        // (c, s) of plane j
-  gt_f64x2* own = de + 2 * N;   // a slot per lane, (d, e) and (c, s) of the lanes whose writes are not wanted
-  auto sync = [] { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); };
+  gt_f64x2* own = de + 2 * N;
 #pragma unroll
   for (int q = 0; q < S; ++q) {
     const int j = 64 * q + lane;
     de[j] = j < n ? (gt_f64x2){pt.d[j], j < n - 1 ? pt.e[j] : 0.0} : (gt_f64x2){0.0, 0.0};
   }
-  sync();
+  wave_sync();
   const int64_t cap = (int64_t)GT_REC_NN * n * n;
-  double* rec = pt.rec;
   int64_t pos = 0;
-  int l = 0, iters = 0, nrec = 0;
+  int l = 0, mm = 0, iters = 0, nrec = 0;
   bool ok = true;
-  for (;;) {
-    // first j >= l that does not split, then the first m > j that does: bit j of neg is
-    // |e_j| <= eps (|d_j| + |d_j+1|), set from n - 1 on
-    int mm = n;
-    bool open = true;  // no block found yet
-#pragma unroll
-    for (int q = 0; q < S; ++q) {
-      if (64 * q + 63 < l || mm < n) continue;
-      const int j = 64 * q + lane;
-      const gt_f64x2 x = de[j], y = de[j + 1 < n ? j + 1 : j];
-      uint64_t neg = __ballot(j >= n - 1 || fabs(x.y) <= GT_EPS * (fabs(x.x) + fabs(y.x)));
-      const int lo = l - 64 * q;
-      uint64_t from = lo > 0 ? ~(uint64_t)0 << lo : ~(uint64_t)0;
-      if (open) {
-        const uint64_t w = ~neg & from;
-        if (!w) continue;
-        const int b = __builtin_ctzll(w);
-        l = 64 * q + b;
-        open = false;
-        from = ~(uint64_t)0 << b;
-      }
-      neg &= from;
-      if (neg) mm = 64 * q + __builtin_ctzll(neg);
-    }
-    if (open) break;
-    mm = mm < n - 1 ? mm : n - 1;
+  while (ql_block<S>(de, n, lane, l, mm)) {
     if (++iters > GT_MAX_QL * n || nrec >= GT_REC_IT * n || pos + 2 * (mm - l) > cap) {
       ok = false;
       break;
     }
-    // shift: the eigenvalue of the leading 2 x 2 block nearer d_l
-    const gt_f64x2 el = de[l], el1 = de[l + 1], em = de[mm];
-    double g = (el1.x - el.x) / (2.0 * el.y);
-    double r = sqrt(g * g + 1.0);
-    const double gs = em.x - el.x + el.y / (g + (g >= 0.0 ? r : -r));
-    // The iteration's rotations run without the split test (f^2 + g^2 = 0: the block splits at
-    // i + 1), which as a branch in the chain cost a fifth of the kernel's time.  A split
-    // leaves NaN in the chain from there on, so a NaN g at the end sends the iteration back
-    // to the block's entries as they were and through the loop that tests every step.
-    gt_f64x2 keep[S];
-#pragma unroll
-    for (int q = 0; q < S; ++q) keep[q] = de[64 * q + lane];
-    double s, c, p;
-    int i;
-    auto iterate = [&](auto tested) {
-      constexpr bool TESTED = decltype(tested)::value;
-      g = gs;
-      s = 1.0;
-      c = 1.0;
-      p = 0.0;
-      i = mm - 1;
-      gt_f64x2* out = lead ? de + mm : own + lane;  // entry i + 1 (lane 0)
-      const int step = lead ? 1 : 0;
-      const int csoff = lead ? N - 1 : 0;  // from entry i + 1 of de to plane i of cs
-      gt_f64x2 x = de[i];
-      double di1 = em.x;
-      for (; i >= l; --i) {
-        const gt_f64x2 xn = de[i > 0 ? i - 1 : 0];  // unconditional load
-        const double f = s * x.y;
-        const double ss = fma(f, f, g * g);
-        if (TESTED && __builtin_amdgcn_readfirstlane(ss == 0.0 ? 1 : 0)) {
-          // the block splits at i + 1: drop the shift and redo the block
-          sync();
-          if (lead) {
-            de[i + 1] = (gt_f64x2){di1 - p, 0.0};
-            de[mm].y = 0.0;
-          }
-          sync();
-          break;
-        }
-        const double y = __builtin_amdgcn_rsq(ss);
-        const double b = c * x.y;
-        const double a = di1 - p;
-        const double h = fma(2.0 * g, b, (x.x - a) * f);
-        const double er = fma(-(ss * y), y, 1.0);
-        const double inv = fma(y * er, fma(0.375, er, 0.5), y);
-        c = g * inv;
-        s = f * inv;
-        const double t = h * inv;
-        g = fma(c, t, -b);
-        p = s * t;
-        *out = (gt_f64x2){fma(s, t, a), ss * inv};
-        out[csoff] = (gt_f64x2){c, s};
-        out -= step;
-        di1 = x.x;
-        x = xn;
-      }
-    };
-    iterate(std::false_type{});
-    sync();
-    if (__builtin_amdgcn_readfirstlane(g != g ? 1 : 0)) {  // every lane holds the same g
-#pragma unroll
-      for (int q = 0; q < S; ++q) de[64 * q + lane] = keep[q];
-      sync();
-      iterate(std::true_type{});
-      sync();
-    }
-    if (i + 1 < mm) {
-      for (int j = i + 1 + lane; j < mm; j += 64) *(gt_f64x2*)(rec + pos + 2 * (mm - 1 - j)) = cs[j];
-      pos += 2 * (mm - 1 - i);
-      if (lead) {
+    const int i0 = ql_iterate<S>(de, cs, own, lane, l, mm);
+    if (i0 < mm) {
+      for (int j = i0 + lane; j < mm; j += 64) *(gt_f64x2*)(pt.rec + pos + 2 * (mm - 1 - j)) = cs[j];
+      pos += 2 * (mm - i0);
+      if (lane == 0) {
         pt.hdr[2 * nrec] = mm;
-        pt.hdr[2 * nrec + 1] = i + 1;
+        pt.hdr[2 * nrec + 1] = i0;
       }
       ++nrec;
     }
-    if (i < l && lead) {
-      de[l] = (gt_f64x2){de[l].x - p, g};
-      de[mm].y = 0.0;
-    }
-    sync();
+    wave_sync();
   }
 #pragma unroll
   for (int q = 0; q < S; ++q)
     if (64 * q + lane < n) pt.eig[64 * q + lane] = de[64 * q + lane].x;
-  if (lead) {
+  if (lane == 0) {
     pt.status[1] = nrec;
     pt.status[2] = (double)(pos / 2);
     pt.status[0] = ok ? 0.0 : 1.0;
@@ -1267,10 +1284,55 @@ constexpr int vec_waves() {  // waves per SIMD that the row's 32 T registers lea
   return T <= 1 ? 4 : T <= 6 ? 2 : 1;
 }
 
+// x <- x (I - tau v v^T), v (16 T entries in LDS) zero up to entry k
+template <int T>
+__device__ __forceinline__ void rows_reflect(double (&x)[16 * T], const double* v, double tau, int k) {
+  double acc[4] = {};
+#pragma unroll
+  for (int c = 0; c < 2 * T; ++c) {
+    if (8 * c + 7 <= k) continue;
+    double vv[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) vv[u] = v[8 * c + u];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) acc[u & 3] = fma(x[8 * c + u], vv[u], acc[u & 3]);
+  }
+  const double y = -tau * ((acc[0] + acc[1]) + (acc[2] + acc[3]));
+#pragma unroll
+  for (int c = 0; c < 2 * T; ++c) {
+    if (8 * c + 7 <= k) continue;
+    double vv[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) vv[u] = v[8 * c + u];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) x[8 * c + u] = fma(y, vv[u], x[8 * c + u]);
+  }
+}
+
+// the rotations of planes mm - 1 down to i0, (c, s) of plane i at cs[i] (identity outside)
+template <int T>
+__device__ __forceinline__ void rows_rotate(double (&x)[16 * T], const gt_f64x2* cs, int mm, int i0) {
+#pragma unroll
+  for (int c = 2 * T - 1; c >= 0; --c) {
+    if (8 * c >= mm || 8 * c + 7 < i0) continue;
+    gt_f64x2 w[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) w[u] = cs[8 * c + 7 - u];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      const int i = 8 * c + 7 - u;
+      if (i + 1 >= 16 * T) continue;
+      const double hi = x[i + 1], lo = x[i];
+      x[i + 1] = fma(w[u].y, lo, w[u].x * hi);
+      x[i] = fma(w[u].x, lo, -(w[u].y * hi));
+    }
+  }
+}
+
 template <int T>
 __global__ void __launch_bounds__(256, vec_waves<T>())
     geneig_tri_rows_kernel(int nv, int items, double* __restrict__ scratch, int64_t stride) {
-  constexpr int NP = 16 * T, NC = NP / 8, S = (NP + 63) / 64;
+  constexpr int NP = 16 * T, S = (NP + 63) / 64;
   __shared__ gt_f64x2 lds[4][2][NP];
   const int n = nv;
   const int lane = threadIdx.x & 63;
@@ -1283,7 +1345,6 @@ __global__ void __launch_bounds__(256, vec_waves<T>())
   TriPoint pt(scratch + point * stride, n);
   if (pt.status[0] != 0.0) return;
   const int nit = (int)pt.status[1];
-  auto sync = [] { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); };
   double x[NP];
 #pragma unroll
   for (int j = 0; j < NP; ++j) x[j] = j == r ? 1.0 : 0.0;
@@ -1308,28 +1369,9 @@ __global__ void __launch_bounds__(256, vec_waves<T>())
         if (j < NP) v[j] = j > k && j < n ? nx[q] : 0.0;
       }
       if (k + 3 < n) fetch(k + 1);
-      sync();
-      double acc[4] = {};
-#pragma unroll
-      for (int c = 0; c < NC; ++c) {
-        if (8 * c + 7 <= k) continue;
-        double vv[8];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) vv[u] = v[8 * c + u];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) acc[u & 3] = fma(x[8 * c + u], vv[u], acc[u & 3]);
-      }
-      const double y = -tk * ((acc[0] + acc[1]) + (acc[2] + acc[3]));
-#pragma unroll
-      for (int c = 0; c < NC; ++c) {
-        if (8 * c + 7 <= k) continue;
-        double vv[8];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) vv[u] = v[8 * c + u];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) x[8 * c + u] = fma(y, vv[u], x[8 * c + u]);
-      }
-      sync();
+      wave_sync();
+      rows_reflect<T>(x, v, tk, k);
+      wave_sync();
     }
   }
   // rotations of plane i (columns i, i + 1), i = mm - 1 down to i0 in each iteration
@@ -1356,23 +1398,9 @@ __global__ void __launch_bounds__(256, vec_waves<T>())
       rec += mm - i0;
       if (it + 1 < nit) fetch(rec, mm2, i02);
       const int mm3 = it + 2 < nit ? pt.hdr[2 * it + 4] : 0, i03 = it + 2 < nit ? pt.hdr[2 * it + 5] : 0;
-      sync();
-#pragma unroll
-      for (int c = NC - 1; c >= 0; --c) {
-        if (8 * c >= mm || 8 * c + 7 < i0) continue;
-        gt_f64x2 w[8];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) w[u] = cs[8 * c + 7 - u];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) {
-          const int i = 8 * c + 7 - u;
-          if (i + 1 >= NP) continue;
-          const double hi = x[i + 1], lo = x[i];
-          x[i + 1] = fma(w[u].y, lo, w[u].x * hi);
-          x[i] = fma(w[u].x, lo, -(w[u].y * hi));
-        }
-      }
-      sync();
+      wave_sync();
+      rows_rotate<T>(x, cs, mm, i0);
+      wave_sync();
       mm = mm2;
       i0 = i02;
       mm2 = mm3;
@@ -1788,34 +1816,20 @@ __global__ void __launch_bounds__(GT_TH) geneig_tri_trace_kernel(int nv, const d
 // lane-per-column products, the reduction in global scratch and 53 counts per xi, 1000 points
 // of N_v = 128 took 3.38 ms.
 // Measured: 0.66 ms.
-template <int T>
-__global__ void __launch_bounds__(GT_TH, reg_waves<T>())
-    geneig_reg_trace_kernel(int nv, const double* __restrict__ k_z, double g_max, double tau, double rho,
-                            double* __restrict__ dos, int32_t* __restrict__ ranks, int rank_stride,
-                            double* __restrict__ scratch, int64_t stride, const double* __restrict__ s_floor) {
-  typedef double f64x4 __attribute__((ext_vector_type(4)));
-  __shared__ RegShared sh;
-  __shared__ double scale[GT_REG_NV];
-  __shared__ int kidx[GT_REG_NV];
-  __shared__ double red[GT_TH / 64];
-  __shared__ int misc[3];
-  const int n = nv;
-  const int i = blockIdx.x;
-  const int tid = threadIdx.x, tr = tid >> 4, tc = tid & 15;
-  const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  TriPoint pt(scratch + i * stride, n);
-  if (*pt.status != 0.0) return;  // the Jacobi kernel writes this point
-  const double* kz = k_z + i * (int64_t)n * n;
-  // 2. truncation: wave 0, 64 eigenvalues at a time
-  if (wave == 0) {
+// Step 2: the kept s_j (s_j >= tau max s, and >= floor), their indices and s_j^-1/2; returns r1.
+// Every lane of the workgroup calls it.
+__device__ __forceinline__ int reg_truncate(int n, const double* eig, double tau, double floor, int* kidx,
+                                            double* scale, int* misc) {
+  const int lane = threadIdx.x & 63;
+  if (threadIdx.x < 64) {  // wave 0, 64 eigenvalues at a time
     double smax = -INFINITY;
-    for (int j = lane; j < n; j += 64) smax = fmax(smax, pt.eig[j]);
+    for (int j = lane; j < n; j += 64) smax = fmax(smax, eig[j]);
     for (int o = 32; o > 0; o >>= 1) smax = fmax(smax, __shfl_xor(smax, o));
-    const double thr = s_floor ? fmax(tau * smax, s_floor[i]) : tau * smax;
+    const double thr = fmax(tau * smax, floor);
     int r1 = 0;
     for (int j0 = 0; j0 < n; j0 += 64) {
       const int j = j0 + lane;
-      const double sj = j < n ? pt.eig[j] : -INFINITY;
+      const double sj = j < n ? eig[j] : -INFINITY;
       const bool keep = j < n && smax > 0.0 && sj >= thr;
       const uint64_t m = __ballot(keep);
       if (keep) {
@@ -1828,28 +1842,29 @@ __global__ void __launch_bounds__(GT_TH, reg_waves<T>())
     if (lane == 0) misc[0] = r1;
   }
   __syncthreads();
-  const int r1 = __builtin_amdgcn_readfirstlane(misc[0]);
-  if (r1 == 0) {
-    if (tid == 0) {
-      dos[i] = 0.0;
-      if (ranks) {
-        ranks[i] = 0;
-        ranks[rank_stride + i] = 0;
-      }
-    }
-    return;
-  }
-  // 3. the products, KB steps of four k at a time: their loads are issued together
+  return __builtin_amdgcn_readfirstlane(misc[0]);
+}
+
+// Step 3: B = S~^-1/2 U~^T K_Z U~ S~^-1/2 (r1 x r1) into registers, lane (tr, tc) of the grid holding
+// the entries (tr + 16 a, tc + 16 b).  zt: eigenvector j in row j (stride ldz); q: n x 16 ceil(r1 /
+// 16) and bm: r1 rows of stride ldb, scratch (global or LDS).
+template <int T>
+__device__ __forceinline__ void reg_pencil(int n, int r1, const double* __restrict__ kz, const double* zt, int ldz,
+                                           double* q, double* bm, int ldb, const int* kidx, const double* scale,
+                                           double (&A)[T][T]) {
+  typedef double f64x4 __attribute__((ext_vector_type(4)));
+  const int tid = threadIdx.x, tr = tid >> 4, tc = tid & 15;
+  const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  // KB steps of four k at a time: their loads are issued together
   constexpr int KB = T >= 7 ? 2 : 4;
   const int nb = (r1 + 15) / 16, ldq = 16 * nb;
   const int lm = lane & 15, lk = lane >> 4;
-  double* q = pt.rec;  // T1, n x ldq
   int uo[T];           // eigenvector 16 a + lm's row of Z^T
   double us[T];
 #pragma unroll
   for (int a = 0; a < T; ++a) {
     const int m = 16 * a + lm;
-    uo[a] = kidx[m < r1 ? m : 0] * n;
+    uo[a] = kidx[m < r1 ? m : 0] * ldz;
     us[a] = m < r1 ? scale[m] : 0.0;
   }
 #pragma unroll
@@ -1860,7 +1875,7 @@ __global__ void __launch_bounds__(GT_TH, reg_waves<T>())
 #pragma unroll
     for (int a = 0; a < T; ++a) acc[a] = (f64x4){0.0, 0.0, 0.0, 0.0};
     const int j = 16 * b + lm;
-    const double* u = pt.zt + (int64_t)kidx[j < r1 ? j : 0] * n;
+    const double* u = zt + kidx[j < r1 ? j : 0] * ldz;
     const double sc = j < r1 ? scale[j] : 0.0;
 #pragma unroll 1
     for (int k0 = 0; k0 < n; k0 += 4 * KB) {
@@ -1909,7 +1924,7 @@ __global__ void __launch_bounds__(GT_TH, reg_waves<T>())
         bv[s] = q[kc * ldq + j];
 #pragma unroll
         for (int a = 0; a < T; ++a)
-          if (a <= b) av[s][a] = pt.zt[uo[a] + kc];
+          if (a <= b) av[s][a] = zt[uo[a] + kc];
       }
 #pragma unroll
       for (int s = 0; s < KB; ++s) {
@@ -1924,12 +1939,11 @@ __global__ void __launch_bounds__(GT_TH, reg_waves<T>())
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
         const int r = 16 * a + lk + 4 * e;
-        if (a <= b && r < r1 && j < r1) pt.a[r * n + j] = acc[a][e];
+        if (a <= b && r < r1 && j < r1) bm[r * ldb + j] = acc[a][e];
       }
   }
   __threadfence_block();
   __syncthreads();
-  double A[T][T];
 #pragma unroll
   for (int a = 0; a < T; ++a)
 #pragma unroll
@@ -1937,28 +1951,36 @@ __global__ void __launch_bounds__(GT_TH, reg_waves<T>())
       const int r = tr + 16 * a, c = tc + 16 * b;
       double v = 0.0;
       if (r < r1 && c < r1)
-        v = a < b   ? pt.a[(int64_t)r * n + c]
-            : a > b ? pt.a[(int64_t)c * n + r]
-                    : 0.5 * (pt.a[(int64_t)r * n + c] + pt.a[(int64_t)c * n + r]);
+        v = a < b   ? bm[r * ldb + c]
+            : a > b ? bm[c * ldb + r]
+                    : 0.5 * (bm[r * ldb + c] + bm[c * ldb + r]);
       A[a][b] = v;
     }
-  reg_reduce<T, false>(A, r1, nullptr, sh);
-  // 4. range filter and trace
+}
+
+// Step 4: the in-range eigenvalues of B (in registers, spent): their sum and count, and whether
+// all of them are in range.  Every lane returns the same.
+template <int T>
+__device__ __forceinline__ bool reg_in_range(double (&A)[T][T], int r1, double hi, RegShared& sh, double* red,
+                                             int* misc, bool all_only, double& sum, int& count) {
+  const int tid = threadIdx.x;
+  reg_reduce<T, false>(A, r1, nullptr, 0, sh);
   double* e2 = sh.x;
   for (int j = tid; j + 1 < r1; j += GT_TH) e2[j] = sh.e[j] * sh.e[j];
   __syncthreads();
-  double e2max = 0.0, glo = INFINITY, ghi = -INFINITY;
+  double e2max = 0.0;
   for (int j = 0; j + 1 < r1; ++j) e2max = fmax(e2max, e2[j]);
   const double pivmin = 0x1p-1022 * fmax(1.0, e2max);
-  const double hi = (1.0 + rho) * g_max;
   if (tid < 2) misc[1 + tid] = tri_count(r1, sh.d, e2, tid ? hi : 0.0, pivmin);
   __syncthreads();
+  const bool all = misc[1] == 0 && misc[2] == r1;
   double part = 0.0;
   int in = 0;
-  if (misc[1] == 0 && misc[2] == r1) {
+  if (all) {
     if (tid < r1) part = sh.d[tid];
     in = tid < r1;
-  } else {
+  } else if (!all_only) {
+    double glo = INFINITY, ghi = -INFINITY;
     for (int j = 0; j < r1; ++j) {
       const double rad = (j > 0 ? fabs(sh.e[j - 1]) : 0.0) + (j + 1 < r1 ? fabs(sh.e[j]) : 0.0);
       glo = fmin(glo, sh.d[j] - rad);
@@ -1972,10 +1994,190 @@ __global__ void __launch_bounds__(GT_TH, reg_waves<T>())
       }
     }
   }
-  const double tr_in = gt_sum(part, red);
-  const int r2 = __syncthreads_count(in);
+  sum = gt_sum(part, red);
+  count = __syncthreads_count(in);
+  return all;
+}
+
+template <int T>
+__global__ void __launch_bounds__(GT_TH, reg_waves<T>())
+    geneig_reg_trace_kernel(int nv, const double* __restrict__ k_z, double g_max, double tau, double rho,
+                            double* __restrict__ dos, int32_t* __restrict__ ranks, int rank_stride,
+                            double* __restrict__ scratch, int64_t stride, const double* __restrict__ s_floor) {
+  __shared__ RegShared sh;
+  __shared__ double scale[GT_REG_NV];
+  __shared__ int kidx[GT_REG_NV];
+  __shared__ double red[GT_TH / 64];
+  __shared__ int misc[3];
+  const int n = nv;
+  const int i = blockIdx.x;
+  TriPoint pt(scratch + i * stride, n);
+  if (*pt.status != 0.0) return;  // the Jacobi kernel writes this point
+  const int r1 = reg_truncate(n, pt.eig, tau, s_floor ? s_floor[i] : -INFINITY, kidx, scale, misc);
+  double sum = 0.0;
+  int r2 = 0;
+  if (r1 > 0) {
+    double A[T][T];
+    reg_pencil<T>(n, r1, k_z + i * (int64_t)n * n, pt.zt, n, pt.rec, pt.a, n, kidx, scale, A);
+    reg_in_range<T>(A, r1, (1.0 + rho) * g_max, sh, red, misc, false, sum, r2);
+  }
+  if (threadIdx.x == 0) {
+    dos[i] = sum;
+    if (ranks) {
+      ranks[i] = r1;
+      ranks[rank_stride + i] = r2;
+    }
+  }
+}
+
+// Every lane: all entries finite and the largest within 1e-100 .. 1e100.  Ends in a barrier.
+template <int T>
+__device__ __forceinline__ bool small_in_scale(const double (&A)[T][T]) {
+  bool below = true, above = false;
+#pragma unroll
+  for (int a = 0; a < T; ++a)
+#pragma unroll
+    for (int b = 0; b < T; ++b) {
+      below = below && fabs(A[a][b]) <= 1e100;  // false for NaN
+      above = above || fabs(A[a][b]) >= 1e-100;
+    }
+  const int ok = __syncthreads_and(below);
+  return __syncthreads_or(above) && ok;
+}
+
+// Algorithm 4 for N_v <= 48, one workgroup per point, everything in LDS and registers: the
+// reduction (reg_reduce, reflectors in LDS), then wave 0 runs the QL iterations while wave 1, one
+// row of U per lane, applies the reflectors and then each iteration's rotations one iteration
+// behind (one barrier an iteration, the rotations passed by plane through two buffers), then
+// the truncation, B and the trace as above.  nvh > 0: the hybrid term too, where every xi is in
+// range (then ||G Q~||_F = ||G||_F, G = K_C U~ S~^-1/2).  flag[i] becomes 1, and the Jacobi kernel
+// does the point, where QL runs past its limit, where K_W or B is not finite or its largest entry
+// is not within 1e-100 .. 1e100 (f^2 + g^2 and the Sturm counts' e^2 could leave FP64's range), or
+// where with nvh > 0 an xi is out of range; else 0.
+// What bounds it: the QL chain, about 1.07 N_v^2 rotations.
+// Measured: N_v = 40, 200 points 1400 to 366 us, N_v = 16, 100 points 98 us (with its launch), the
+// cyclic Jacobi kernel before, seven sweeps of 39 rounds over K_W and as many over B.
+template <int T>
+__global__ void __launch_bounds__(GT_TH)
+    geneig_small_kernel(int nv, const double* __restrict__ k_w, const double* __restrict__ k_z, double g_max,
+                        double tau, double rho, double* __restrict__ dos, int32_t* __restrict__ ranks,
+                        int rank_stride, double* __restrict__ flag, int64_t flag_stride,
+                        const double* __restrict__ s_floor, int nvh, const double* __restrict__ k_c,
+                        const double* __restrict__ trw) {
+  constexpr int N = 16 * T, LD = N + 1;
+  __shared__ RegShared sh;
+  __shared__ double refl[N * LD];  // reflectors, then T1
+  __shared__ double zt[N * LD];
+  __shared__ double bm[N * LD];
+  __shared__ gt_f64x2 ring[4 * 64];
+  __shared__ double eig[N], scale[N], red[GT_TH / 64];
+  __shared__ int kidx[N], misc[3], hdr[2][3];  // hdr: an iteration's mm and i0, and 0 running, 1 done, 2 stopped
+  const int n = nv;
+  const int i = blockIdx.x;
+  const int tid = threadIdx.x, tr = tid >> 4, tc = tid & 15;
+  const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  gt_f64x2* de = ring;             // (d_j, e_j)
+  gt_f64x2* own = ring + 64;
+  gt_f64x2* cs0 = ring + 128;      // (c, s) by plane, of even and of odd iterations
+  const double* kw = k_w + i * (int64_t)n * n;
+  const double* kz = k_z + i * (int64_t)n * n;
+  {
+    double A[T][T];
+#pragma unroll
+    for (int a = 0; a < T; ++a)
+#pragma unroll
+      for (int b = 0; b < T; ++b) {
+        const int r = tr + 16 * a, c = tc + 16 * b;
+        A[a][b] = r < n && c < n ? 0.5 * (kw[r * n + c] + kw[c * n + r]) : 0.0;
+      }
+    for (int j = tid; j < N * LD; j += GT_TH) refl[j] = 0.0;
+    if (!small_in_scale<T>(A)) {
+      if (tid == 0) flag[i * flag_stride] = 1.0;
+      return;
+    }
+    reg_reduce<T, true>(A, n, refl, LD, sh);
+  }
+  if (tid < 64) de[tid] = tid < n ? (gt_f64x2){sh.d[tid], tid < n - 1 ? sh.e[tid] : 0.0} : (gt_f64x2){0.0, 0.0};
+  __syncthreads();
+  int state = 0;
+  int l = 0, iters = 0;  // wave 0
+  double x[N];           // wave 1
+  if (wave == 1) {
+#pragma unroll
+    for (int j = 0; j < N; ++j) x[j] = j == lane ? 1.0 : 0.0;
+  }
+  for (int it = 0;; ++it) {  // wave 0 forms iteration it, wave 1 applies iteration it - 1
+    if (wave == 0) {
+      int mm = 0, st = 0, i0 = 0;
+      if (!ql_block<1>(de, n, lane, l, mm)) {
+        st = 1;
+      } else if (++iters > GT_MAX_QL * n) {
+        st = 2;
+      } else {
+        gt_f64x2* w = cs0 + 64 * (it & 1);
+        w[lane] = (gt_f64x2){1.0, 0.0};
+        wave_sync();
+        i0 = ql_iterate<1>(de, w, own, lane, l, mm);
+        if (lane < i0) w[lane] = (gt_f64x2){1.0, 0.0};  // an iteration cut short by a split
+      }
+      if (lane == 0) {
+        hdr[it & 1][0] = mm;
+        hdr[it & 1][1] = i0;
+        hdr[it & 1][2] = st;
+      }
+    } else if (wave == 1) {
+      if (it == 0) {
+        for (int k = 0; k + 2 < n; ++k) {
+          const double tk = sh.tau[k];
+          if (tk != 0.0) rows_reflect<T>(x, refl + k * LD, tk, k);
+        }
+      } else {
+        const int mm = __builtin_amdgcn_readfirstlane(hdr[(it - 1) & 1][0]);
+        const int i0 = __builtin_amdgcn_readfirstlane(hdr[(it - 1) & 1][1]);
+        if (i0 < mm) rows_rotate<T>(x, cs0 + 64 * ((it - 1) & 1), mm, i0);
+      }
+    }
+    __syncthreads();
+    // uniform, and wave 0 writes this slot again only two iterations on, past the next barrier
+    state = __builtin_amdgcn_readfirstlane(hdr[it & 1][2]);
+    if (state != 0) break;
+  }
+  const bool stopped = state == 2;
+  if (wave == 1 && lane < N) {
+#pragma unroll
+    for (int j = 0; j < N; ++j) zt[j * LD + lane] = x[j];
+  }
+  if (tid < n) eig[tid] = de[tid].x;
+  if (tid == 0) flag[i * flag_stride] = stopped ? 1.0 : 0.0;
+  __syncthreads();
+  if (stopped) return;
+  const int r1 = reg_truncate(n, eig, tau, s_floor ? s_floor[i] : -INFINITY, kidx, scale, misc);
+  double sum = 0.0;
+  int r2 = 0;
+  if (r1 > 0) {
+    double A[T][T];
+    reg_pencil<T>(n, r1, kz, zt, LD, refl, bm, LD, kidx, scale, A);
+    if (!small_in_scale<T>(A) ||
+        (!reg_in_range<T>(A, r1, (1.0 + rho) * g_max, sh, red, misc, nvh > 0, sum, r2) && nvh > 0)) {
+      if (tid == 0) flag[i * flag_stride] = 1.0;
+      return;
+    }
+  }
+  if (nvh > 0) {
+    const double* kc = k_c + (int64_t)i * nvh * n;
+    double part = 0.0;
+    for (int idx = tid; idx < nvh * r1; idx += GT_TH) {
+      const int a = idx / r1, b = idx - a * r1;
+      const double* u = zt + kidx[b] * LD;
+      double g = 0.0;
+      for (int c = 0; c < n; ++c) g += kc[a * n + c] * u[c];
+      g *= scale[b];
+      part += g * g;
+    }
+    sum += (trw[i] - gt_sum(part, red)) / nvh;
+  }
   if (tid == 0) {
-    dos[i] = tr_in;
+    dos[i] = sum;
     if (ranks) {
       ranks[i] = r1;
       ranks[rank_stride + i] = r2;
@@ -2429,6 +2631,17 @@ hipError_t launch_tri_trace(int np, int n, const double* kz, double g_max, doubl
   return hipGetLastError();
 }
 
+hipError_t launch_small(int np, int n, const double* kw, const double* kz, double g_max, double tau, double rho,
+                        double* dos, int32_t* ranks, int rank_stride, double* flag, int64_t flag_stride,
+                        const double* s_floor, int nvh, const double* kc, const double* trw, hipStream_t stream) {
+  const void* kernel = n <= 16   ? (const void*)geneig_small_kernel<1>
+                       : n <= 32 ? (const void*)geneig_small_kernel<2>
+                                 : (const void*)geneig_small_kernel<3>;
+  void* args[] = {&n, &kw, &kz, &g_max, &tau, &rho, &dos, &ranks, &rank_stride, &flag, &flag_stride, &s_floor,
+                  &nvh, &kc, &trw};
+  return hipLaunchKernel(kernel, dim3(np), dim3(GT_TH), args, 0, stream);
+}
+
 // U of np points: rows in registers up to N_v = 128, in LDS above
 hipError_t launch_vectors(int np, int n, double* scratch, int64_t stride, hipStream_t stream) {
   switch ((n + 15) / 16) {
@@ -2558,9 +2771,16 @@ hipError_t launch_geneig_trace(int nv, int ntb, const double* k_w, const double*
   if (nv < 1 || nv > GE_MAX_NV) return hipErrorInvalidValue;
   if (nvh < 0 || (nvh > 0 && (!k_c || !trw || !hscr))) return hipErrorInvalidValue;
   if (rank_stride <= 0) rank_stride = ntb;
-  if (!geneig_tri_path(nv))
+  if (!geneig_tri_path(nv)) {
+    // the first double of a point's scratch flags it for the Jacobi kernel, all of whose waves
+    // read the flag before the first barrier and none writes the scratch before it
+    const int64_t stride = geneig_scratch_doubles(nv);
+    hipError_t err = launch_small(ntb, nv, k_w, k_z, g_max, tau, rho, dos, ranks, rank_stride, scratch, stride, s_floor,
+                                  nvh, k_c, trw, stream);
+    if (err != hipSuccess) return err;
     return launch_jacobi_trace(nv, ntb, k_w, k_z, g_max, tau, rho, dos, ranks, scratch, nvh, k_c, trw, hscr, s_floor,
-                               rank_stride, stream, geneig_scratch_doubles(nv), nullptr);
+                               rank_stride, stream, stride, scratch);
+  }
   // the tridiagonal path, kGeTriChunk points at a time through the same scratch
   const int64_t stride = geneig_tri_point_doubles(nv);
   const int64_t nn = (int64_t)nv * nv;

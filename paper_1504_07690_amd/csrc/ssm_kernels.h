@@ -134,9 +134,9 @@ __host__ __device__ inline int64_t geneig_scratch_doubles(int nv) {
   const int64_t n = nv;
   return n * n + (2 - geneig_lds_matrices(nv)) * n * (n + 1);
 }
-// Above N_v = 48 the trace (with or without the hybrid term) goes through a tridiagonal matrix
-// (Householder reduction, QL for eig(K_W) with the eigenvectors built in LDS from a record
-// of its rotations, bisection for eig(B)), kGeTriChunk points per launch group through
+// The trace (with or without the hybrid term) goes through a tridiagonal matrix (Householder
+// reduction, QL for eig(K_W) with its eigenvectors, Sturm counts or bisection for eig(B)).  Up to
+// N_v = 48 that is one kernel in LDS; above, kGeTriChunk points per launch group through
 // geneig_tri_point_doubles of scratch each: 6 n^2 + 8 n + 8 (the reduced matrix, U^T, the
 // rotation record of 4 n^2, the tridiagonal matrix and status).
 constexpr int kGeTriChunk = 2048;
