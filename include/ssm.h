@@ -146,7 +146,7 @@ typedef struct ssm_stats {
   double ms_sweep;         /* all sweep GEMM launches */
   double ms_gram;          /* Gram kernels incl. partial-sum reduction */
   double ms_geneig;        /* Algorithm 4 kernel */
-  int64_t spmm_launches;   /* number of block-SpMM launches */
+  int64_t spmm_launches;   /* number of block-SpMM steps (few rows: many in one launch) */
   int64_t sweep_launches;  /* number of sweep GEMM launches */
   int32_t passes;          /* recurrence passes (sweep-point batches) */
   int32_t chunk;           /* K_c: Chebyshev blocks held at once */

@@ -62,6 +62,18 @@ __device__ __forceinline__ double vdot<f64x2>(const f64x2& u, const f64x2& v) {
 // reading the block the step before wrote), and 1024 slowed the FP64 and moment variants.
 constexpr int CS_THREADS = 256;
 
+// a acc + b x, rounded as every kernel of a step rounds it: the product with x, then one FMA
+template <typename T, typename V>
+__device__ __forceinline__ V step_value(T a, const V& acc, T b, const V& x) {
+  V t, u;
+  {
+#pragma clang fp contract(off)
+    t = b * x;
+  }
+  u = __builtin_elementwise_fma((V)a, acc, t);
+  return u;
+}
+
 // row visited at position rho of the tiled order
 __device__ __forceinline__ int64_t tiled_row(int64_t rho, const RowOrder& o) {
   const int tile_rows = o.tx * o.ty;
@@ -127,7 +139,7 @@ __global__ void __launch_bounds__(CS_THREADS) cheb_step_kernel(int64_t n, int nv
 #pragma unroll
       for (int j = 0; j < 8; ++j) g[j] = (j < cnt) ? x[(int64_t)cols[j] * nvv + q] : (V)(T)0;
 #pragma unroll
-      for (int j = 0; j < 8; ++j) acc += vals[j] * g[j];
+      for (int j = 0; j < 8; ++j) acc = __builtin_elementwise_fma((V)vals[j], g[j], acc);
     }
   } else {
   const int p0 = row_ptr[r];
@@ -150,12 +162,12 @@ __global__ void __launch_bounds__(CS_THREADS) cheb_step_kernel(int64_t n, int nv
         g[j] = (V)(T)0;
     }
 #pragma unroll
-    for (int j = 0; j < 8; ++j) acc += vals[j] * g[j];
+    for (int j = 0; j < 8; ++j) acc = __builtin_elementwise_fma((V)vals[j], g[j], acc);
   }
   }
   const V xo = x[gid];
-  V res = a * acc + b * xo;
-  if (xprev) res += c * xp;
+  V res = step_value<T, V>(a, acc, b, xo);
+  if (xprev) res = __builtin_elementwise_fma((V)c, xp, res);
   if (d) res += dd;
   if (valid) {
     if constexpr (KEEP)
@@ -421,6 +433,113 @@ hipError_t launch(int64_t n, int nv, const int32_t* row_ptr, const int32_t* col_
                                       d, out, dots, o, stream);
 }
 
+// Many steps of the recurrence in one launch, for blocks of few rows.  The columns of a block do
+// not touch each other in a step, so a workgroup takes one 16-byte slice of every row through all
+// steps by itself: the slice of Y_k in LDS (two buffers, one barrier a step), Y_k and Y_k-1 of its
+// own rows and up to RUN_NNZ CSR entries of each in the lanes' registers (a longer row's rest is
+// read again each step), every step's slice written to its ring slot.  Sums are taken in the
+// order of cheb_step_kernel: the blocks are bit for bit the same.  Workgroup b runs on XCD
+// b % 8, and takes a slice next to the XCD's others, whose 16-byte pieces share its L2's lines.
+// What bounds it: the LDS gathers of one CU, and the rows whose entries its registers hold: 2048.
+// Measured per step (100 steps of a 5-point lattice, N_v = 40, FP64; the launches before, of any
+// size at this end, 3.6): 576 rows 0.58 us, 1024 rows 0.69 us, 2025 rows 1.35 us.
+constexpr int RUN_TH = 1024;
+constexpr int RUN_NNZ = 8;
+
+template <typename T, typename V, int R>
+__global__ void __launch_bounds__(RUN_TH) cheb_run_kernel(int n, int nvv, const int32_t* __restrict__ row_ptr,
+                                                          const int32_t* __restrict__ col_idx,
+                                                          const T* __restrict__ val, T a1, T b1, T a, T b, T c, int k0,
+                                                          int k1, const V* x, const V* xprev, V* y, int ring) {
+  extern __shared__ char run_lds[];
+  V* buf = (V*)run_lds;  // 2 x (n + 1) slices, the last of each zero (what a row's missing entries gather)
+  const int per_xcd = (nvv + 7) / 8;
+  const int q = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
+  if (q >= nvv) return;  // uniform over the workgroup
+  const int tid = threadIdx.x;
+  V cur[R], prev[R];
+  uint32_t cols[R][RUN_NNZ / 2];  // two 16-bit columns a register
+  T vals[R][RUN_NNZ];
+  constexpr int G = R == 1 ? RUN_NNZ : 4;  // gathers in flight: what the registers leave room for
+  const uint32_t slice = (uint32_t)(tid * nvv + q) * sizeof(V);
+  uint32_t longer = 0;  // bit i: row i has more than RUN_NNZ entries
+#pragma unroll
+  for (int i = 0; i < R; ++i) {
+    const int r = tid + RUN_TH * i;
+    const bool in = r < n;
+    const int ps = in ? row_ptr[r] : 0, pe = in ? row_ptr[r + 1] : 0;
+    if (pe - ps > RUN_NNZ) longer |= 1u << i;
+    cur[i] = in ? x[(int64_t)r * nvv + q] : (V)(T)0;
+    prev[i] = in && xprev ? xprev[(int64_t)r * nvv + q] : (V)(T)0;
+    if (in) buf[r] = cur[i];
+#pragma unroll
+    for (int j = 0; j < RUN_NNZ; ++j) {
+      const bool ok = ps + j < pe;
+      const uint32_t col = ok ? (uint32_t)col_idx[ps + j] : (uint32_t)n;
+      cols[i][j / 2] = j & 1 ? cols[i][j / 2] | col << 16 : col;
+      vals[i][j] = ok ? val[ps + j] : (T)0;
+    }
+  }
+  if (tid < 2) buf[(n + 1) * tid + n] = (V)(T)0;
+  __syncthreads();
+  bool three = xprev != nullptr;
+  int slot = k0 % ring;
+#pragma unroll 1
+  for (int k = k0; k <= k1; ++k) {
+    const V* src = buf + ((k - k0) & 1 ? n + 1 : 0);
+    V* dst = buf + ((k - k0) & 1 ? 0 : n + 1);
+    char* out = (char*)(y + (int64_t)slot * n * nvv);
+    slot = slot + 1 == ring ? 0 : slot + 1;
+    const T sa = three ? a : a1, sb = three ? b : b1;
+#pragma unroll
+    for (int i = 0; i < R; ++i) {
+      const int r = tid + RUN_TH * i;
+      V acc = (V)(T)0;
+#pragma unroll
+      for (int h = 0; h < RUN_NNZ; h += G) {
+        V g[G];
+#pragma unroll
+        for (int j = 0; j < G; j += 2) {
+          uint32_t w = cols[i][(h + j) / 2];
+          asm volatile("" : "+v"(w));  // unpacked anew each step: the addresses do not stay in registers
+          g[j] = src[w & 0xFFFF];
+          g[j + 1] = src[w >> 16];
+        }
+#pragma unroll
+        for (int j = 0; j < G; ++j) acc = __builtin_elementwise_fma((V)vals[i][h + j], g[j], acc);
+      }
+      if (longer >> i & 1) {
+        const int pe = row_ptr[r + 1];
+        for (int p = row_ptr[r] + RUN_NNZ; p < pe; ++p) acc = __builtin_elementwise_fma((V)val[p], src[col_idx[p]], acc);
+      }
+      V res = step_value<T, V>(sa, acc, sb, cur[i]);
+      if (three) res = __builtin_elementwise_fma((V)c, prev[i], res);
+      prev[i] = cur[i];
+      cur[i] = res;
+      if (r < n) {
+        dst[r] = res;
+        *(V*)(out + (size_t)i * RUN_TH * nvv * sizeof(V) + slice) = res;
+      }
+    }
+    three = true;
+    __syncthreads();
+  }
+}
+
+template <typename T, typename V>
+hipError_t launch_run(int n, int nvv, const int32_t* row_ptr, const int32_t* col_idx, const T* val, double alpha,
+                      double beta, int k0, int k1, const void* x, const void* xprev, void* y, int ring,
+                      hipStream_t stream) {
+  const auto fn = n <= RUN_TH ? cheb_run_kernel<T, V, 1> : cheb_run_kernel<T, V, 2>;
+  const size_t lds = 2 * (size_t)(n + 1) * sizeof(V);
+  hipError_t err = hipFuncSetAttribute((const void*)fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  if (err != hipSuccess) return err;
+  hipLaunchKernelGGL(fn, dim3(8 * ((nvv + 7) / 8)), dim3(RUN_TH), lds, stream, n, nvv, row_ptr, col_idx, val, (T)alpha,
+                     (T)beta, (T)(2.0 * alpha), (T)(2.0 * beta), (T)-1.0, k0, k1, (const V*)x, (const V*)xprev, (V*)y,
+                     ring);
+  return hipGetLastError();
+}
+
 }  // namespace
 
 hipError_t launch_cheb_step_f64(int64_t n, int nv, const int32_t* row_ptr, const int32_t* col_idx,
@@ -435,6 +554,22 @@ hipError_t launch_cheb_step_f32(int64_t n, int nv, const int32_t* row_ptr, const
                                 const float* xprev, const float* d, float* out, hipStream_t stream,
                                 double* dots, const RowOrder& order) {
   return launch<float, f32x4, 4>(n, nv, row_ptr, col_idx, val, a, b, c, x, xprev, d, out, dots, order, stream);
+}
+
+// Rows of more entries would mostly be read again each step, and more than 256 slices would take
+// turns on the CUs: such calls go step by step, as do more rows (3600 rows: 3.6 to 4.9 us a step).
+bool cheb_run_fits(int64_t n, int64_t nnz, int nv, int is_f32) {
+  return n <= 2 * RUN_TH && nnz <= RUN_NNZ * n && nv / (is_f32 ? 4 : 2) <= 256;
+}
+
+hipError_t launch_cheb_run(int is_f32, int64_t n, int nv, const int32_t* row_ptr, const int32_t* col_idx,
+                           const void* val, double alpha, double beta, int k0, int k1, const void* x,
+                           const void* xprev, void* y, int ring, hipStream_t stream) {
+  if (is_f32)
+    return launch_run<float, f32x4>((int)n, nv / 4, row_ptr, col_idx, (const float*)val, alpha, beta, k0, k1, x, xprev,
+                                    y, ring, stream);
+  return launch_run<double, f64x2>((int)n, nv / 2, row_ptr, col_idx, (const double*)val, alpha, beta, k0, k1, x, xprev,
+                                   y, ring, stream);
 }
 
 hipError_t launch_box_check(int64_t n, const int32_t* row_ptr, const int32_t* col_idx, int nx, int ny, int nz,

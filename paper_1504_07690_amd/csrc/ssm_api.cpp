@@ -691,12 +691,23 @@ ssm_status forward_pass(ssm_ctx* c, int pass, bool first, Timeline* tl, int64_t&
     if (!resident || pass == 0) {
       Span rs{tl ? tl->mark() : 0, 0, 0};
       SSM_HIP(record(rs.b), "hipEventRecord");
+      // few rows and no inner products: the chunk's steps in one launch
+      const bool run = k_last > 0 && !(first && pl.dgc_group) && ssm::cheb_run_fits(n, c->a.nnz, nv, !f64);
+      if (run) {
+        const int kb = std::max(k_first, 1);
+        hipError_t err = ssm::launch_cheb_run(!f64, n, nv, c->a.row_ptr, c->a.col_idx, c->a.values, alpha, beta, kb,
+                                              k_last, kb == 1 ? c->w : (const void*)y_slot(kb - 1),
+                                              kb == 1 ? nullptr : (const void*)y_slot(kb - 2),
+                                              c->y, pl.chunk, st);
+        if (err != hipSuccess) return hip_fail(err, "Chebyshev steps");
+        spmm_launches += k_last - kb + 1;
+      }
       for (int k = k_first; k <= k_last; ++k) {
         char* out = y_slot(k);
-        hipError_t err;
+        hipError_t err = hipSuccess;
         if (k == 0) {
           err = hipMemcpyAsync(out, c->w, e * es, hipMemcpyDeviceToDevice, st);
-        } else {
+        } else if (!run) {
           const void* x = (k == 1) ? c->w : (const void*)y_slot(k - 1);
           const void* xp = (k == 1) ? nullptr : (const void*)y_slot(k - 2);
           const double a = (k == 1) ? alpha : 2.0 * alpha;
@@ -927,7 +938,14 @@ ssm_status ress_dos(ssm_ctx* c, double* dos_host, int32_t* ranks_host) {
     const int k_last = std::min(S, s_done + pl.chunk);
     Span rs{mark(), 0, 0};
     SSM_HIP(rec(rs.b), "hipEventRecord");
-    for (int kk = k + 1; kk <= k_last; ++kk) {
+    const bool run = k < k_last && ssm::cheb_run_fits(n, c->a.nnz, nvp, !f64);
+    if (run) {
+      err = ssm::launch_cheb_run(!f64, n, nvp, c->a.row_ptr, c->a.col_idx, c->a.values, alpha, beta, k + 1, k_last,
+                                 slot(k), k == 0 ? nullptr : slot(k - 1), c->y, R, st);
+      if (err != hipSuccess) return hip_fail(err, "Chebyshev steps");
+      spmm_launches += k_last - k;
+    }
+    for (int kk = k + 1; kk <= k_last && !run; ++kk) {
       const char* x = slot(kk - 1);
       const char* xp = kk == 1 ? nullptr : slot(kk - 2);
       const double sa = kk == 1 ? alpha : 2.0 * alpha, sb = kk == 1 ? beta : 2.0 * beta, sc = kk == 1 ? 0.0 : -1.0;
@@ -1518,6 +1536,11 @@ ssm_status ssm_chebyshev(const ssm_csr* a, double lo, double hi, int32_t precisi
   hipStream_t st = (hipStream_t)stream;
   const double alpha = 2.0 / (hi - lo), beta = -(hi + lo) / (hi - lo);
   SSM_HIP(hipMemcpyAsync(y, w, e * es, hipMemcpyDeviceToDevice, st), "copy W");
+  if (degree > 0 && ssm::cheb_run_fits(a->n, a->nnz, nv, !f64)) {
+    hipError_t err = ssm::launch_cheb_run(!f64, a->n, nv, a->row_ptr, a->col_idx, a->values, alpha, beta, 1, degree, w,
+                                          nullptr, y, degree + 1, st);
+    return err == hipSuccess ? SSM_OK : hip_fail(err, "Chebyshev steps");
+  }
   for (int k = 1; k <= degree; ++k) {
     char* out = (char*)y + (size_t)k * e * es;
     const char* x = (char*)y + (size_t)(k - 1) * e * es;

@@ -1,0 +1,74 @@
+"""The recurrence of few rows in one launch: the same bits as step by step.  The same matrix with
+more diagonal rows below it is too large for the one launch and goes step by step."""
+import numpy as np
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+DEV = "cuda:0"
+
+
+def _rows(n, kind, rng):
+    """CSR arrays of a symmetric-pattern matrix of at most 8 entries a row on average."""
+    rows = [set() for _ in range(n)]
+    if kind == "long":  # one full row up to 40 entries, the others short, some empty
+        for j in rng.choice(n, min(n, 40), replace=False):
+            rows[n // 2].add(int(j))
+    for i in range(n):
+        if kind == "long" and i % 5 == 0:
+            continue
+        rows[i].update(int(j) for j in rng.choice(n, min(n, 5 if kind == "long" else 8), replace=False))
+    return [sorted(r) for r in rows]
+
+
+def _csr(rows, total, dtype, rng):
+    from paper_1504_07690_amd import ssm as S
+    rows = rows + [[i] for i in range(len(rows), total)]
+    ptr = np.concatenate([[0], np.cumsum([len(r) for r in rows])])
+    idx = np.concatenate([np.array(r, dtype=np.int64) for r in rows])
+    val = rng.uniform(-0.12, 0.12, len(idx))
+    return S.DeviceCSR(total, ptr, idx, val, dtype=dtype)
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.float64])
+@pytest.mark.parametrize("n,nv,degree,kind", [(1, 4, 3, "even"), (2, 8, 1, "even"), (63, 12, 9, "long"),
+                                              (1023, 4, 6, "long"), (1024, 36, 17, "even"), (1025, 20, 8, "long"),
+                                              (2047, 100, 5, "even"), (2048, 256, 4, "long")])
+def test_run_equals_steps(n, nv, degree, kind, dtype):
+    from paper_1504_07690_amd import ssm as S
+    rows = _rows(n, kind, np.random.default_rng(n))
+    big = 2600
+    small = _csr(rows, n, dtype, np.random.default_rng(5))
+    large = _csr(rows, big, dtype, np.random.default_rng(5))
+    g = torch.Generator(device=DEV).manual_seed(n)
+    w = torch.randn(big, nv, dtype=dtype, device=DEV, generator=g)
+    ys = torch.full((degree + 1, n, nv), 7.0, dtype=dtype, device=DEV)
+    yl = torch.empty(degree + 1, big, nv, dtype=dtype, device=DEV)
+    precision = "fp32" if dtype == torch.float32 else "fp64"
+    S.chebyshev(small, -1.3, 1.1, precision, w[:n].contiguous(), ys)
+    S.chebyshev(large, -1.3, 1.1, precision, w, yl)
+    assert torch.equal(ys, yl[:, :n])
+
+
+@pytest.mark.parametrize("precision", ["fp32", "fp64"])
+def test_run_across_ring_chunks(precision):
+    """With a ring of all blocks and of 16 slots: with the inner products of Algorithm 2 the recurrence
+    goes step by step, and the DOS is the same."""
+    from paper_1504_07690_amd import ssm as S
+    dtype = torch.float32 if precision == "fp32" else torch.float64
+    rng = np.random.default_rng(3)
+    n, m = 300, 40
+    ring = [[(i - 1) % n, i, (i + 1) % n] for i in range(n)]
+    ptr = np.arange(0, 3 * n + 1, 3)
+    csr = S.DeviceCSR(n, ptr, np.array(ring).ravel(), np.tile([-1.0, 2.0, -1.0], n), dtype=dtype)
+    t = np.linspace(0.2, 3.8, 9)
+    w = torch.tensor(rng.standard_normal((n, 12)), dtype=dtype, device=DEV)
+    for plan in (None, (9, 16)):
+        out = []
+        for dgc in (False, True):
+            ctx = S.SSM(csr, lo=-0.1, hi=4.1, sigma=0.25, nv=12, degree=m, t=t, precision=precision, w=w,
+                        plan=plan, dgc=dgc)
+            out.append(ctx.dos()[0].copy())
+            assert ctx.stats()["spmm_launches"] == m * ctx.stats()["passes"]
+        assert np.array_equal(out[0], out[1])
