@@ -6,6 +6,8 @@
 //                                                    with the coefficient table transposed)
 //   Lambda_k = Ybar_k + 2 A~ Lambda_{k+1} - Lambda_{k+2}   (the recurrence kernel)
 //   abar_e += alpha c_k Lambda_k[r_e] . Y_{k-1}[c_e],  c_1 = 1, c_k = 2 (k >= 2)
+#include <algorithm>
+
 #include "ssm_kernels.h"
 
 namespace ssm {
@@ -185,116 +187,182 @@ __global__ void __launch_bounds__(256) zbar_big_kernel(int64_t n, int nv, const 
 //   abar[p] += coef * Lambda_k[r] . y[c_p] for the stored entries p of row r,
 //         y = Y_{k-1}, in FP64.
 //
-// A row of N_v values is held by L = N_v/4 lanes, 4 values each (16 bytes in FP32,
-// 32 in FP64); a wave holds R = 64/L whole rows, so the L partial dot products of an
-// entry are summed inside the wave with lane permutes.  Rows go to XCDs in contiguous
-// ranges, as in the forward recurrence, and a lattice's rows are visited in the same tiled
-// order (TILED); when a row fills a whole wave (WAVE_ROW: N_v = 256 in FP32) its CSR
-// entries come through the scalar cache.
+// A row of N_v values is held by L = N_v/4 lanes, 4 values each (16 bytes in FP32, 32 in FP64); a
+// wave holds R = min(64/L, 16) whole rows side by side, so that a gather's lanes read whole
+// cache lines (eight lanes a row in passes read parts of more lines, and stalled on lines in flight).
+// Each CSR entry of the wave's rows is loaded once, by one lane, and reaches the row's lanes
+// through LDS: eight entries a row at a time.  The lanes' partial dot products of those go
+// through LDS too: H lanes sum one (row, entry) over the row's L lanes.  (Summed by permutes,
+// each entry's six steps of two permutes bounded the kernel.)
+// Rows go to XCDs in contiguous ranges, as in the forward recurrence, and a lattice's rows are
+// visited in the same tiled order.
+// What bounds it: up to the gradient's part, the blocks that it moves (14.7 us of the 21 at N = 32768,
+// N_v = 80 in FP32, 52 MB a step with Y's 10); then the exact products, 36 conversions and 32 FP64
+// operations a lane, and their sums through LDS.
+// Measured per step, FP32 (FP64), permutes and per-lane entries before: N = 32768 lattice, N_v = 80
+// 28.9 to 21.1 us (47 to 36); N = 22500, N_v = 40 12.8 to 8.0; N = 262144, N_v = 80 173 to 142;
+// a random graph of 20000 rows and 17 entries a row, N_v = 80 43.6 to 36.8.
 // ---------------------------------------------------------------------------
-__device__ __forceinline__ int64_t lattice_row(int64_t rho, const RowOrder& o) {
-  const int tile_rows = o.tx * o.ty;
-  const int64_t col_rows = (int64_t)tile_rows * o.nz;
-  const int tile = (int)(rho / col_rows);
-  const int64_t rem = rho - (int64_t)tile * col_rows;
-  const int z = (int)(rem / tile_rows);
-  const int in = (int)(rem - (int64_t)z * tile_rows);
-  const int yy = in / o.tx, xx = in - yy * o.tx;
-  const int tiles_x = o.nx / o.tx;
-  const int ty_i = tile / tiles_x, tx_i = tile - ty_i * tiles_x;
-  return (int64_t)(tx_i * o.tx + xx) + (int64_t)o.nx * ((int64_t)(ty_i * o.ty + yy) + (int64_t)o.ny * z);
-}
+constexpr int RV_ROWS = 16;
+constexpr int RV_LD = 65;  // lanes of one entry's partial sums, padded: the sums' reads spread over the banks
 
-__device__ __forceinline__ double row_sum(double s, int lane, int q, int L) {
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) {
-    const double t = __shfl(s, (lane + off) & 63);
-    if (q < off && q + off < L) s += t;
-  }
-  return s;  // the row's total, in its lane q == 0
-}
+template <typename T>
+struct ReverseShared {
+  double part[8 * RV_LD];
+  T vals[8 * RV_ROWS];
+  uint32_t cols[8 * RV_ROWS];
+};
 
-template <typename T, typename V, bool TILED, bool WAVE_ROW>
-__global__ void __launch_bounds__(256) reverse_step_kernel(int64_t n, int L, int R, int64_t nblocks, int64_t per_xcd,
-                                                           const int32_t* __restrict__ row_ptr,
-                                                           const int32_t* __restrict__ col_idx,
-                                                           const T* __restrict__ val, T a, T b, T c,
-                                                           const V* __restrict__ x, const V* __restrict__ xprev,
-                                                           const V* __restrict__ d, V* __restrict__ out,
-                                                           const V* __restrict__ y, double coef,
-                                                           double* __restrict__ abar, RowOrder order) {
+__device__ __forceinline__ void reverse_sync() { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); }
+
+// BUF: blocks below 2 GiB, gathered through buffer resources: a 32-bit offset an entry instead of
+// a 64-bit address, and the padding's offset is past the block, which reads as zero unasked.
+template <typename T, typename V, bool BUF>
+__global__ void __launch_bounds__(256, !BUF ? 1 : sizeof(T) == 4 ? 4 : 3)
+    reverse_step_kernel(int64_t n, int L, int R, int H, int64_t nblocks, int64_t per_xcd,
+                        const int32_t* __restrict__ row_ptr, const int32_t* __restrict__ col_idx,
+                        const T* __restrict__ val, T a, T b, T c, const V* __restrict__ x,
+                        const V* __restrict__ xprev, const V* __restrict__ d, V* __restrict__ out,
+                        const V* __restrict__ y, double coef, double* __restrict__ abar, int keep,
+                        TileOrder order) {
+  __shared__ ReverseShared<T> shared[4];
   const int64_t lblock = (int64_t)(blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
   if (lblock >= nblocks) return;  // uniform over the workgroup
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  ReverseShared<T>& sh = shared[wave];
   const int lane = threadIdx.x & 63;
   const int g = lane / L;
   const int q = lane - g * L;
-  const int64_t rho = (lblock * 4 + (threadIdx.x >> 6)) * R + g;
+  const int64_t rho = (lblock * 4 + wave) * R + g;
   const bool active = g < R && rho < n;
-  int64_t rs = active ? (TILED ? lattice_row(rho, order) : rho) : 0;  // idle lanes read row 0 and write nothing
-  if constexpr (WAVE_ROW) rs = __builtin_amdgcn_readfirstlane((int)rs);  // one row per wave
+  const int64_t rs = !active ? 0 : order.nx ? (int64_t)order.row((uint32_t)rho) : rho;  // idle lanes read row 0
   const int p0 = row_ptr[rs];
   const int len = active ? row_ptr[rs + 1] - p0 : 0;
+  const bool longer = __any(len > 8);  // uniform over the wave, like every loop below
+  const uint32_t bytes = BUF ? (uint32_t)(n * L * sizeof(V)) : 0;
+  const int slots = 8 * R;
+
+  // entries j .. j + 7 of the wave's rows: to LDS, then each row's eight to its lanes
+  uint32_t cols[8];  // BUF: the rows' byte offsets
+  T vals[8];
+  auto load_entries = [&](int j) {
+    reverse_sync();
+    for (int s0 = 0; s0 < slots; s0 += 64) {
+      const int s = s0 + lane, src = (s >> 3) * L;
+      const int pg = __shfl(p0, src), lg = __shfl(len, src), e = j + (s & 7);
+      if (s < slots) {
+        const bool ok = e < lg;
+        const uint32_t col = ok ? (uint32_t)col_idx[pg + e] : 0u;
+        sh.cols[s] = !BUF ? col : ok ? col * (uint32_t)(L * sizeof(V)) : 0x80000000u;
+        sh.vals[s] = ok ? val[pg + e] : (T)0;
+      }
+    }
+    reverse_sync();
+    const int s = 8 * (g < R ? g : 0);
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      cols[u] = BUF && !active ? 0x80000000u : sh.cols[s + u];
+      vals[u] = sh.vals[s + u];
+    }
+  };
+  // their rows' pieces in a block; padded slots issue no gather
+  auto gather = [&](const V* block, int j, V (&v)[8]) {
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      if constexpr (BUF) {
+        const auto r = __builtin_amdgcn_make_buffer_rsrc((void*)block, (short)0, bytes, 0x00020000);
+        typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+        u32x4 w[sizeof(V) / 16];
+#pragma unroll
+        for (int h = 0; h < (int)sizeof(V) / 16; ++h)
+          w[h] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(
+                                               r, (int)(cols[u] + (uint32_t)sizeof(V) * q + 16 * h), 0, 0));
+        __builtin_memcpy(&v[u], w, sizeof(V));
+      } else {
+        v[u] = (V)(T)0;
+        if (j + u < len) v[u] = block[(int64_t)cols[u] * L + q];
+      }
+    }
+  };
+
+  // the sums that this lane's group of H forms: (row, entry j + (o & 7)) o = lane / H, ...
+  const int hl = lane & (H - 1), per_round = 64 / H;
+  double g0[2] = {};  // what they are added to, for j = 0, loaded ahead of the gathers
+#pragma unroll
+  for (int r = 0; r < 2; ++r) {
+    const int o = lane / H + r * per_round, src = (o >> 3) * L & 63;
+    const int pg = __shfl(p0, src), lg = __shfl(len, src);
+    if (o < slots && hl == 0 && (o & 7) < lg) g0[r] = abar[pg + (o & 7)];
+  }
+
+  load_entries(0);
   const int64_t own = rs * L + q;
-  V res;
+  V res = (V)(T)0, xp = (V)(T)0, xo = (V)(T)0;
+  if (active) {
+    // Lambda_{k+2} and Ybar_k are read for the last time: streamed with non-temporal hints
+    res = __builtin_nontemporal_load(&d[own]);
+    if (xprev) xp = __builtin_nontemporal_load(&xprev[own]);
+    if (x) xo = x[own];
+  }
   if (x) {
     V acc = (V)(T)0;
-    for (int p = 0; p < len; p += 8) {
-      int cols[8];
-      T vals[8];
+    V v[8];
+    gather(x, 0, v);
 #pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        const bool ok = p + j < len;
-        cols[j] = ok ? col_idx[p0 + p + j] : (int)rs;
-        vals[j] = ok ? val[p0 + p + j] : (T)0;
+    for (int u = 0; u < 8; ++u) acc += vals[u] * v[u];
+    if (longer) {
+#pragma unroll 1
+      for (int j = 8; __any(j < len); j += 8) {
+        load_entries(j);
+        gather(x, j, v);
+#pragma unroll
+        for (int u = 0; u < 8; ++u) acc += vals[u] * v[u];
       }
-      V gv[8];
-#pragma unroll
-      for (int j = 0; j < 8; ++j) {  // padded slots issue no gather
-        if (p + j < len)
-          gv[j] = x[(int64_t)cols[j] * L + q];
-        else
-          gv[j] = (V)(T)0;
-      }
-#pragma unroll
-      for (int j = 0; j < 8; ++j) acc += vals[j] * gv[j];
+      load_entries(0);
     }
-    res = a * acc + b * x[own];
-    // Lambda_{k+2} and Ybar_k are read for the last time and Lambda_k is next read by the
-    // following step's gathers: streamed with non-temporal hints, as in the forward
-    // recurrence (175 -> 166 ms for the 1000 steps at N = 262144, N_v = 80)
-    if (xprev) res += c * __builtin_nontemporal_load(&xprev[own]);
-    res += __builtin_nontemporal_load(&d[own]);
-  } else {
-    res = __builtin_nontemporal_load(&d[own]);
+    V t = a * acc + b * xo;
+    if (xprev) t += c * xp;
+    res = t + res;
   }
-  if (active) __builtin_nontemporal_store(res, &out[own]);
-  // every lane of the wave runs the permutes: the loop bound is the wave's longest row
-  for (int j = 0; __any(j < len); j += 4) {
-    int cols[4];
+  if (active) {
+    if (keep)
+      out[own] = res;
+    else
+      __builtin_nontemporal_store(res, &out[own]);
+  }
+#pragma unroll 1
+  for (int j = 0; __any(j < len); j += 8) {
+    if (j > 0) load_entries(j);
+    V v[8];
+    gather(y, j, v);
 #pragma unroll
-    for (int u = 0; u < 4; ++u) cols[u] = (j + u < len) ? col_idx[p0 + j + u] : (int)rs;
-    V yv[4];
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      if (j + u < len)
-        yv[u] = y[(int64_t)cols[u] * L + q];
-      else
-        yv[u] = (V)(T)0;
+    for (int u = 0; u < 8; ++u) {
+      double t = (double)res.x * (double)v[u].x;
+      t += (double)res.y * (double)v[u].y;
+      t += (double)res.z * (double)v[u].z;
+      t += (double)res.w * (double)v[u].w;
+      sh.part[u * RV_LD + lane] = t;
     }
-    double sum[4];
+    reverse_sync();
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      double t = (double)res.x * (double)yv[u].x;
-      t += (double)res.y * (double)yv[u].y;
-      t += (double)res.z * (double)yv[u].z;
-      t += (double)res.w * (double)yv[u].w;
-      sum[u] = row_sum(t, lane, q, L);
+    for (int r = 0; r < 2; ++r) {
+      const int o = lane / H + r * per_round;
+      if (r * per_round >= slots) break;  // uniform
+      const int src = (o >> 3) * L & 63;
+      const int pg = __shfl(p0, src), lg = __shfl(len, src), e = j + (o & 7);
+      const bool ok = o < slots && e < lg;
+      double t = 0.0;
+      if (ok) {
+        const double* part = sh.part + (o & 7) * RV_LD + src;
+        for (int i = hl; i < L; i += H) t += part[i];
+      }
+      for (int m = H >> 1; m > 0; m >>= 1) t += __shfl_xor(t, m);
+      if (ok && hl == 0) {
+        double* to = &abar[pg + e];
+        *to = (j == 0 ? g0[r] : *to) + coef * t;
+      }
     }
-    if (q == 0 && active) {
-#pragma unroll
-      for (int u = 0; u < 4; ++u)
-        if (j + u < len) abar[p0 + j + u] += coef * sum[u];
-    }
+    reverse_sync();
   }
 }
 
@@ -393,29 +461,30 @@ hipError_t launch_zbar(int is_f32, int64_t n, int nv, int ntb, const void* w, vo
 }
 
 template <typename T, typename V>
-hipError_t launch_reverse_t(int64_t n, int nv, const int32_t* row_ptr, const int32_t* col_idx, const T* val, T a,
-                            T b, T c, const void* x, const void* xprev, const void* d, void* out, const void* y,
-                            double coef, double* abar, const RowOrder& o, hipStream_t stream) {
+hipError_t launch_reverse_t(int64_t n, int nv, const int32_t* row_ptr, const int32_t* col_idx, const T* val, T a, T b,
+                            T c, const T* x, const T* xprev, const T* d, T* out, const T* y, double coef,
+                            double* abar, const RowOrder& o, hipStream_t stream) {
   const int L = nv / 4;
   if (L < 1 || L > 64 || nv % 4) return hipErrorInvalidValue;
-  const int R = 64 / L;
+  const int R = std::min(64 / L, RV_ROWS);
+  int H = 1;  // lanes that sum one (row, entry): 8 R groups of H, in one round up to 8 rows
+  while (16 * R * H <= 64) H *= 2;
   const int64_t rows_per_block = 4 * (int64_t)R;
   const int64_t nblocks = (n + rows_per_block - 1) / rows_per_block;
   const int64_t per_xcd = (nblocks + 7) / 8;
   if (per_xcd * 8 > 0x7FFFFFFF) return hipErrorInvalidValue;
-  const bool tiled = o.nx > 0;
-  if (tiled && !(o.tx > 0 && o.ty > 0 && o.nx % o.tx == 0 && o.ny % o.ty == 0 && (int64_t)o.nx * o.ny * o.nz == n))
+  if (o.nx > 0 &&
+      !(o.tx > 0 && o.ty > 0 && o.nx % o.tx == 0 && o.ny % o.ty == 0 && (int64_t)o.nx * o.ny * o.nz == n))
     return hipErrorInvalidValue;
-  const dim3 grid((unsigned)(per_xcd * 8)), block(256);
-#define SSM_REVERSE_LAUNCH(TL, WR)                                                                                \
-  hipLaunchKernelGGL((reverse_step_kernel<T, V, TL, WR>), grid, block, 0, stream, n, L, R, nblocks, per_xcd, row_ptr, \
-                     col_idx, val, a, b, c, (const V*)x, (const V*)xprev, (const V*)d, (V*)out, (const V*)y, coef,     \
-                     abar, o)
-  if (tiled && L == 64) SSM_REVERSE_LAUNCH(true, true);
-  else if (tiled) SSM_REVERSE_LAUNCH(true, false);
-  else if (L == 64) SSM_REVERSE_LAUNCH(false, true);
-  else SSM_REVERSE_LAUNCH(false, false);
-#undef SSM_REVERSE_LAUNCH
+  // Lambda_k is next gathered by the following step, from the last-level cache if a step's five
+  // blocks leave it there: stored normally up to 64 MiB (33 MB: 56.3 us a step against 59.4 stored
+  // non-temporally; 84 MB: 144 against 142)
+  const int keep = n * L * (int64_t)sizeof(V) <= ((int64_t)64 << 20);
+  const auto fn = n * L * (int64_t)sizeof(V) < ((int64_t)1 << 31) ? reverse_step_kernel<T, V, true>
+                                                                  : reverse_step_kernel<T, V, false>;
+  hipLaunchKernelGGL(fn, dim3((unsigned)(per_xcd * 8)), dim3(256), 0, stream, n, L, R, H, nblocks, per_xcd, row_ptr,
+                     col_idx, val, a, b, c, (const V*)x, (const V*)xprev, (const V*)d, (V*)out, (const V*)y, coef, abar,
+                     keep, o.nx > 0 ? TileOrder(o) : TileOrder());
   return hipGetLastError();
 }
 
