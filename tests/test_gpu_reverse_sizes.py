@@ -92,3 +92,41 @@ def test_reverse_order_of_rows(nv):
         ctx.dos()
         out.append(ctx.backward(weight))
     assert torch.equal(out[0], out[1])
+
+
+@pytest.mark.parametrize("part", [False, True])
+@pytest.mark.parametrize("nv", [56, 128, 136])
+def test_backward_with_eigenvalues_out_of_range(nv, part):
+    """Algorithm 4's backward above N_v = 48 against the Jacobi kernel's: W's 44 columns padded with zero
+    columns, whose eigenvalues are cut off, give the same gradient.  Once with every eigenvalue of the
+    pencil in range, once with K_Z scaled so that the range's upper end is in their widest gap."""
+    from paper_1504_07690_amd import ssm as S
+    rng = np.random.default_rng(nv)
+    n, base = 400, 44
+    ptr, idx, val, _ = _matrix(n, rng)
+    w = torch.tensor(rng.standard_normal((n, base)), device=DEV)
+    weight = np.array([1.0, -0.7, 0.4])
+    grads, conds, scale = [], [], None
+    for cols in (base, nv):
+        ctx = S.SSM(S.DeviceCSR(n, ptr, idx, val, dtype=torch.float64), lo=-4.0, hi=4.0, sigma=1.2, nv=cols, degree=M,
+                    t=np.array([-1.0, 0.1, 1.2]), precision="fp64",
+                    w=torch.cat([w, torch.zeros(n, cols - base, dtype=w.dtype, device=DEV)], 1).contiguous())
+        _, r1, r2 = ctx.dos()
+        assert (r1 == base).all() and (r2 == base).all()
+        v = ctx.views()
+        if scale is None:
+            kw, kz = v["k_w"].cpu().numpy(), v["k_z"].cpu().numpy()
+            s, u = np.linalg.eigh(0.5 * (kw + kw.transpose(0, 2, 1)))
+            conds = s[:, -1] / s[:, 0]
+            half = u / np.sqrt(s)[:, None, :]
+            xi = np.linalg.eigvalsh(half.transpose(0, 2, 1) @ kz @ half)
+            mid = xi[:, base // 4: 3 * base // 4]
+            gap = np.diff(mid, axis=1).argmax(1)
+            end = 0.5 * (mid[np.arange(NT), gap] + mid[np.arange(NT), gap + 1])
+            g_max = 1.0 / (n * np.sqrt(2 * np.pi) * 1.2)
+            scale = torch.tensor(1.001 * g_max / end if part else np.ones(NT), device=DEV)
+        v["k_z"].mul_(scale[:, None, None])
+        grads.append(ctx.backward(weight).cpu().numpy())
+    # rounding of K_W over its smallest eigenvalue, to the power in F's differences; scaled K_Z
+    tol = 500 * 2.0 ** -52 * conds.max() ** 1.5 * max(1.0, float(scale.max()))
+    assert np.linalg.norm(grads[1] - grads[0]) <= tol * np.linalg.norm(grads[0])
