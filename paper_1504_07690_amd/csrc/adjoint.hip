@@ -23,12 +23,21 @@ typedef double f64x4 __attribute__((ext_vector_type(4)));
 // v_mfma_f64_16x16x4_f64, T = N_v/16 output blocks per wave.  A wave reads only
 // the rows it writes, and writes them after its last read of them.
 // ---------------------------------------------------------------------------
-constexpr int ZB_ROWS_PER_BLOCK = 4096;
+// What bounds it: the FP64 MFMAs: 1.15 ms at the rate of a large product for 100 points of N = 32768,
+// N_v = 80 in FP32, which took 1.81 ms with one wave a SIMD and 4096 rows a workgroup and take 1.6:
+// two waves a SIMD, one's stores and conversions behind the other's MFMAs, where the registers hold
+// it, and rows dealt so that no CU waits for a last round (zbar_rows).
+template <int T, typename In>
+constexpr int zbar_threads() {
+  return T <= (sizeof(In) == 4 ? 5 : 4) ? 512 : 256;
+}
 
 template <int T, typename In>
-__global__ void __launch_bounds__(256) zbar_kernel(int64_t n, int nv, const In* __restrict__ w, In* __restrict__ z,
-                                                   const double* __restrict__ kw_bar,
-                                                   const double* __restrict__ kz_bar) {
+__global__ void __launch_bounds__((zbar_threads<T, In>())) zbar_kernel(int64_t n, int nv, int64_t rows_per_block,
+                                                                       const In* __restrict__ w, In* __restrict__ z,
+                                                                       const double* __restrict__ kw_bar,
+                                                                       const double* __restrict__ kz_bar) {
+  constexpr int TH = zbar_threads<T, In>();
   // [Kbar_W; 2 Kbar_Z] as two NP x NP halves (rows and columns past N_v zero), so that
   // the contraction index q < 2 NP needs no bounds test
   extern __shared__ double kb[];
@@ -40,11 +49,11 @@ __global__ void __launch_bounds__(256) zbar_kernel(int64_t n, int nv, const In* 
   const double* kzb = kz_bar + i * nn;
   // stack fill: eight loads in flight per thread before their LDS stores
   constexpr int total = 2 * NP * NP;
-  for (int base = threadIdx.x; base < total; base += 8 * 256) {
+  for (int base = threadIdx.x; base < total; base += 8 * TH) {
     double v[8];
 #pragma unroll
     for (int u = 0; u < 8; ++u) {
-      const int idx = base + 256 * u;
+      const int idx = base + TH * u;
       const int r = idx / NP, c = idx % NP;
       const int hr = r < NP ? r : r - NP;  // row inside its half
       double x = 0.0;
@@ -53,14 +62,14 @@ __global__ void __launch_bounds__(256) zbar_kernel(int64_t n, int nv, const In* 
     }
 #pragma unroll
     for (int u = 0; u < 8; ++u)
-      if (base + 256 * u < total) kb[base + 256 * u] = v[u];
+      if (base + TH * u < total) kb[base + TH * u] = v[u];
   }
   __syncthreads();
   In* zi = z + (int64_t)i * n * nv;
   const int lane = threadIdx.x & 63;
   const int wave = threadIdx.x >> 6;
-  const int64_t r_begin = (int64_t)blockIdx.x * ZB_ROWS_PER_BLOCK;
-  const int64_t r_end = (r_begin + ZB_ROWS_PER_BLOCK < n) ? r_begin + ZB_ROWS_PER_BLOCK : n;
+  const int64_t r_begin = (int64_t)blockIdx.x * rows_per_block;
+  const int64_t r_end = (r_begin + rows_per_block < n) ? r_begin + rows_per_block : n;
   // the 16 x 2 NP slab of [W | Z] for rows r0 .. r0+15: A[m = lane%16][k = 4 s + lane/16];
   // indices are clamped into the arrays (rows past the range, columns past N_v), and the
   // values they bring meet zero stack rows or feed rows that are not stored
@@ -80,9 +89,9 @@ __global__ void __launch_bounds__(256) zbar_kernel(int64_t n, int nv, const In* 
   In cur[KQ], nxt[KQ];
   int64_t r0 = r_begin + 16 * wave;
   if (r0 < r_end) load_slab(r0, cur);
-  for (; r0 < r_end; r0 += 64) {
+  for (; r0 < r_end; r0 += TH / 4) {
     // the next slab's loads are in flight behind this slab's MFMAs
-    if (r0 + 64 < r_end) load_slab(r0 + 64, nxt);
+    if (r0 + TH / 4 < r_end) load_slab(r0 + TH / 4, nxt);
     f64x4 acc[T];
 #pragma unroll
     for (int t = 0; t < T; ++t) acc[t] = (f64x4){0.0, 0.0, 0.0, 0.0};
@@ -124,7 +133,8 @@ __global__ void __launch_bounds__(256) zbar_kernel(int64_t n, int nv, const In* 
 // 2 Kbar_Z] through the cache (one point's stack is shared by all its row blocks),
 // and the 16 x 2 N_v slab is loaded eight k-steps at a time.
 template <int T, typename In>
-__global__ void __launch_bounds__(256) zbar_big_kernel(int64_t n, int nv, const In* __restrict__ w,
+__global__ void __launch_bounds__(256) zbar_big_kernel(int64_t n, int nv, int64_t rows_per_block,
+                                                       const In* __restrict__ w,
                                                        In* __restrict__ z, const double* __restrict__ kw_bar,
                                                        const double* __restrict__ kz_bar) {
   constexpr int NP = 16 * T;
@@ -136,8 +146,8 @@ __global__ void __launch_bounds__(256) zbar_big_kernel(int64_t n, int nv, const 
   In* zi = z + (int64_t)i * n * nv;
   const int lane = threadIdx.x & 63;
   const int wave = threadIdx.x >> 6;
-  const int64_t r_begin = (int64_t)blockIdx.x * ZB_ROWS_PER_BLOCK;
-  const int64_t r_end = (r_begin + ZB_ROWS_PER_BLOCK < n) ? r_begin + ZB_ROWS_PER_BLOCK : n;
+  const int64_t r_begin = (int64_t)blockIdx.x * rows_per_block;
+  const int64_t r_end = (r_begin + rows_per_block < n) ? r_begin + rows_per_block : n;
   for (int64_t r0 = r_begin + 16 * wave; r0 < r_end; r0 += 64) {
     const int64_t row = r0 + (lane & 15);
     const bool rok = row < r_end;
@@ -379,39 +389,55 @@ __global__ void __launch_bounds__(256) transpose_coefficients_kernel(const doubl
   if (ct32) ct32[gid] = (float)v;
 }
 
+// Rows per workgroup of `step` rows a turn, at most 4096: of the multiples of step the one whose
+// workgroups, one a CU at a time, end first, counting what each spends before its rows (the
+// stack's fill, the last rows' stores) as `before` rows.
+int64_t zbar_rows(int64_t n, int ntb, int step, int before) {
+  int64_t best = step, least = INT64_MAX;
+  for (int64_t r = step; r <= 4096; r += step) {
+    const int64_t groups = (n + r - 1) / r * ntb;
+    const int64_t cost = (groups + 255) / 256 * (r + before);
+    if (cost < least) {
+      least = cost;
+      best = r;
+    }
+  }
+  return best;
+}
+
 template <int T>
 hipError_t launch_zbar_big(int is_f32, int64_t n, int nv, int ntb, const void* w, void* z, const double* kwb,
                            const double* kzb, hipStream_t stream) {
-  dim3 grid((unsigned)((n + ZB_ROWS_PER_BLOCK - 1) / ZB_ROWS_PER_BLOCK), ntb);
+  constexpr int64_t rows = 256;  // no stack to fill: as many workgroups as hide each other's loads
+  dim3 grid((unsigned)((n + rows - 1) / rows), ntb);
   if (is_f32)
-    hipLaunchKernelGGL((zbar_big_kernel<T, float>), grid, dim3(256), 0, stream, n, nv, (const float*)w, (float*)z, kwb,
-                       kzb);
+    hipLaunchKernelGGL((zbar_big_kernel<T, float>), grid, dim3(256), 0, stream, n, nv, rows, (const float*)w,
+                       (float*)z, kwb, kzb);
   else
-    hipLaunchKernelGGL((zbar_big_kernel<T, double>), grid, dim3(256), 0, stream, n, nv, (const double*)w, (double*)z,
-                       kwb, kzb);
+    hipLaunchKernelGGL((zbar_big_kernel<T, double>), grid, dim3(256), 0, stream, n, nv, rows, (const double*)w,
+                       (double*)z, kwb, kzb);
+  return hipGetLastError();
+}
+
+template <int T, typename In>
+hipError_t launch_zbar_in(int64_t n, int nv, int ntb, const In* w, In* z, const double* kwb, const double* kzb,
+                          hipStream_t stream) {
+  constexpr int TH = zbar_threads<T, In>();
+  const size_t lds = (size_t)2 * (16 * T) * (16 * T) * sizeof(double);
+  const int64_t rows = zbar_rows(n, ntb, TH / 4, 64);
+  hipError_t err = hipFuncSetAttribute((const void*)zbar_kernel<T, In>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                       (int)lds);
+  if (err != hipSuccess) return err;
+  hipLaunchKernelGGL((zbar_kernel<T, In>), dim3((unsigned)((n + rows - 1) / rows), ntb), dim3(TH), lds, stream, n, nv,
+                     rows, w, z, kwb, kzb);
   return hipGetLastError();
 }
 
 template <int T>
 hipError_t launch_zbar_t(int is_f32, int64_t n, int nv, int ntb, const void* w, void* z, const double* kwb,
                          const double* kzb, hipStream_t stream) {
-  const size_t lds = (size_t)2 * (16 * T) * (16 * T) * sizeof(double);
-  dim3 grid((unsigned)((n + ZB_ROWS_PER_BLOCK - 1) / ZB_ROWS_PER_BLOCK), ntb);
-  hipError_t err;
-  if (is_f32) {
-    err = hipFuncSetAttribute((const void*)zbar_kernel<T, float>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                              (int)lds);
-    if (err != hipSuccess) return err;
-    hipLaunchKernelGGL((zbar_kernel<T, float>), grid, dim3(256), lds, stream, n, nv, (const float*)w, (float*)z, kwb,
-                       kzb);
-  } else {
-    err = hipFuncSetAttribute((const void*)zbar_kernel<T, double>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                              (int)lds);
-    if (err != hipSuccess) return err;
-    hipLaunchKernelGGL((zbar_kernel<T, double>), grid, dim3(256), lds, stream, n, nv, (const double*)w, (double*)z,
-                       kwb, kzb);
-  }
-  return hipGetLastError();
+  return is_f32 ? launch_zbar_in<T, float>(n, nv, ntb, (const float*)w, (float*)z, kwb, kzb, stream)
+                : launch_zbar_in<T, double>(n, nv, ntb, (const double*)w, (double*)z, kwb, kzb, stream);
 }
 
 // Split tables of the transposed sweep: rows k, columns the sweep points i,
