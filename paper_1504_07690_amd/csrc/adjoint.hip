@@ -210,8 +210,8 @@ __global__ void __launch_bounds__(256) zbar_big_kernel(int64_t n, int nv, int64_
 // N_v = 80 in FP32, 52 MB a step with Y's 10); then the exact products, 36 conversions and 32 FP64
 // operations a lane, and their sums through LDS.
 // Measured per step, FP32 (FP64), permutes and per-lane entries before: N = 32768 lattice, N_v = 80
-// 28.9 to 21.1 us (47 to 36); N = 22500, N_v = 40 12.8 to 8.0; N = 262144, N_v = 80 173 to 142;
-// a random graph of 20000 rows and 17 entries a row, N_v = 80 43.6 to 36.8.
+// 28.9 to 21.0 us (47 to 33); N = 22500, N_v = 40 12.8 to 7.7; N = 262144, N_v = 80 173 to 139;
+// a random graph of 20000 rows and 17 entries a row, N_v = 80 43.6 to 36.4.
 // ---------------------------------------------------------------------------
 constexpr int RV_ROWS = 16;
 constexpr int RV_LD = 65;  // lanes of one entry's partial sums, padded: the sums' reads spread over the banks
@@ -280,6 +280,10 @@ __global__ void __launch_bounds__(256, !BUF ? 1 : sizeof(T) == 4 ? 4 : 3)
 #pragma unroll
     for (int u = 0; u < 8; ++u) {
       if constexpr (BUF) {
+        if (u >= 5 && !__any(j + u < len)) {  // no row of the wave has a sixth, seventh, eighth entry
+          v[u] = (V)(T)0;
+          continue;
+        }
         const auto r = __builtin_amdgcn_make_buffer_rsrc((void*)block, (short)0, bytes, 0x00020000);
         typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
         u32x4 w[sizeof(V) / 16];

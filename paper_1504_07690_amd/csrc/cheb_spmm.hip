@@ -74,6 +74,26 @@ __device__ __forceinline__ V step_value(T a, const V& acc, T b, const V& x) {
   return u;
 }
 
+// A DOTS workgroup's sums of <out, x> and <x, x>
+template <typename V>
+__device__ __forceinline__ void step_dots(bool valid, const V& res, const V& xo, int64_t lblock, double* dots) {
+  __shared__ double red[2][CS_THREADS];
+  red[0][threadIdx.x] = valid ? vdot<V>(res, xo) : 0.0;
+  red[1][threadIdx.x] = valid ? vdot<V>(xo, xo) : 0.0;
+  __syncthreads();
+  for (int st = CS_THREADS / 2; st > 0; st >>= 1) {
+    if ((int)threadIdx.x < st) {
+      red[0][threadIdx.x] += red[0][threadIdx.x + st];
+      red[1][threadIdx.x] += red[1][threadIdx.x + st];
+    }
+    __syncthreads();
+  }
+  if (threadIdx.x == 0) {
+    dots[2 * lblock] = red[0][0];
+    dots[2 * lblock + 1] = red[1][0];
+  }
+}
+
 // row visited at position rho of the tiled order
 __device__ __forceinline__ int64_t tiled_row(int64_t rho, const RowOrder& o) {
   const int tile_rows = o.tx * o.ty;
@@ -175,23 +195,76 @@ __global__ void __launch_bounds__(CS_THREADS) cheb_step_kernel(int64_t n, int nv
     else
       __builtin_nontemporal_store(res, &out[gid]);
   }
-  if constexpr (DOTS) {
-    __shared__ double red[2][CS_THREADS];
-    red[0][threadIdx.x] = valid ? vdot<V>(res, xo) : 0.0;
-    red[1][threadIdx.x] = valid ? vdot<V>(xo, xo) : 0.0;
-    __syncthreads();
-    for (int st = CS_THREADS / 2; st > 0; st >>= 1) {
-      if ((int)threadIdx.x < st) {
-        red[0][threadIdx.x] += red[0][threadIdx.x + st];
-        red[1][threadIdx.x] += red[1][threadIdx.x + st];
-      }
-      __syncthreads();
+  if constexpr (DOTS) step_dots<V>(valid, res, xo, lblock, dots);
+}
+
+// The step of blocks up to 128 MiB whose rows are not whole waves.  The same lanes as above, with the
+// vector units' work cut to what the sums need (above, 310 instructions a wave, most of them 64-bit
+// divisions, addresses and masks, take 45 us of a 56 us step of N = 262144, N_v = 80 in FP32).  Rows
+// come from products by reciprocals; a row's next eight entries come in four 16-byte loads (FP32),
+// which may run on into the next row's; every gather is a buffer load at a 32-bit offset, past
+// the block's end for the slots that the row does not have, which reads as zero without a request.
+// What bounds it: the three blocks moved, at a large copy's rate from 80 MB on.
+// Measured per step: 5-point lattice, N_v = 40, FP32, N = 22500 5.44 to 4.61 us, N_v = 64, FP64,
+// N = 160000 49.2 to 45.1; 7-point, N_v = 80, FP32, N = 110592 24.1 to 22.5, N = 262144 56.9 to 55.1;
+// a random graph of 100000 rows and 17 entries a row, N_v = 96, FP32 99.7 to 98.4.
+template <typename T, typename V, bool DOTS>
+__global__ void __launch_bounds__(CS_THREADS)
+    cheb_slice_kernel(uint32_t total, uint32_t nvv, FastDiv per_row, uint32_t nblocks, uint32_t per_xcd,
+                      const int32_t* __restrict__ row_ptr, const int32_t* __restrict__ col_idx,
+                      const T* __restrict__ val, uint32_t nnz, T a, T b, T c, const V* __restrict__ x,
+                      const V* __restrict__ xprev, const V* __restrict__ d, V* __restrict__ out,
+                      double* __restrict__ dots, TileOrder order) {
+  typedef int32_t i32x4 __attribute__((ext_vector_type(4)));
+  const uint32_t lblock = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
+  if (lblock >= nblocks) return;  // uniform over the workgroup
+  const uint32_t gid0 = lblock * CS_THREADS + threadIdx.x;
+  const bool valid = gid0 < total;
+  if (!DOTS && !valid) return;
+  const uint32_t vid = valid ? gid0 : 0;  // idle lanes of a DOTS block recompute slice 0 and store nothing
+  const uint32_t rho = per_row(vid);
+  const uint32_t q = vid - rho * nvv;
+  const uint32_t r = order.nx ? order.row(rho) : rho;
+  const uint32_t own = (r * nvv + q) * 16;  // bytes
+  const auto rx = __builtin_amdgcn_make_buffer_rsrc((void*)x, (short)0, total * 16, 0x00020000);
+  const auto rc = __builtin_amdgcn_make_buffer_rsrc((void*)col_idx, (short)0, nnz * 4, 0x00020000);
+  const auto rv = __builtin_amdgcn_make_buffer_rsrc((void*)val, (short)0, nnz * (uint32_t)sizeof(T), 0x00020000);
+  V xp = (V)(T)0, dd = (V)(T)0;  // streamed operands first: they do not depend on the row's CSR
+  if (xprev) xp = __builtin_nontemporal_load((const V*)((const char*)xprev + own));
+  if (d) dd = __builtin_nontemporal_load((const V*)((const char*)d + own));
+  const V xo = *(const V*)((const char*)x + own);
+  const int p1 = row_ptr[r + 1];
+  V acc = (V)(T)0;
+  for (int p = row_ptr[r]; p < p1; p += 8) {
+    i32x4 cols[2];
+    T vals[8];
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+      cols[j] = __builtin_bit_cast(i32x4, __builtin_amdgcn_raw_buffer_load_b128(rc, 4 * p + 16 * j, 0, 0));
+#pragma unroll
+    for (int j = 0; j < (int)sizeof(T) / 2; ++j) {
+      const auto w = __builtin_amdgcn_raw_buffer_load_b128(rv, (int)((uint32_t)p * sizeof(T)) + 16 * j, 0, 0);
+      __builtin_memcpy((char*)vals + 16 * j, &w, 16);
     }
-    if (threadIdx.x == 0) {
-      dots[2 * lblock] = red[0][0];
-      dots[2 * lblock + 1] = red[1][0];
+    V g[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      const bool ok = j == 0 || p + j < p1;
+      const uint32_t off = ok ? (uint32_t)cols[j >> 2][j & 3] * (nvv * 16) + q * 16 : 0x80000000u;
+      vals[j] = ok ? vals[j] : (T)0;
+      if (j < 5 || __any(ok))  // no row of the wave has a sixth, seventh, eighth entry: no gather
+        g[j] = __builtin_bit_cast(V, __builtin_amdgcn_raw_buffer_load_b128(rx, (int)off, 0, 0));
+      else
+        g[j] = (V)(T)0;
     }
+#pragma unroll
+    for (int j = 0; j < 8; ++j) acc = __builtin_elementwise_fma((V)vals[j], g[j], acc);
   }
+  V res = step_value<T, V>(a, acc, b, xo);
+  if (xprev) res = __builtin_elementwise_fma((V)c, xp, res);
+  if (d) res += dd;
+  if (valid) *(V*)((char*)out + own) = res;
+  if constexpr (DOTS) step_dots<V>(valid, res, xo, lblock, dots);
 }
 
 // Inner products of a group of recurrence steps from their workgroup partials: workgroup
@@ -404,8 +477,8 @@ hipError_t launch_v(dim3 grid, bool keep, int64_t n, int nvv, int64_t nblocks, i
 }
 
 template <typename T, typename V, int VEC>
-hipError_t launch(int64_t n, int nv, const int32_t* row_ptr, const int32_t* col_idx, const T* val, T a, T b,
-                  T c, const T* x, const T* xprev, const T* d, T* out, double* dots, const RowOrder& o,
+hipError_t launch(int64_t n, int nv, const int32_t* row_ptr, const int32_t* col_idx, const T* val, int64_t nnz, T a,
+                  T b, T c, const T* x, const T* xprev, const T* d, T* out, double* dots, const RowOrder& o,
                   hipStream_t stream) {
   const int nvv = nv / VEC;
   const int64_t threads = n * nvv;
@@ -420,6 +493,19 @@ hipError_t launch(int64_t n, int nv, const int32_t* row_ptr, const int32_t* col_
       return hipErrorInvalidValue;
     if (o.box && !dots && nvv % 64 == 0 && o.tx % kBoxRows == 0 && o.nx >= 3 && o.ny >= 3 && o.nz >= 3)
       return launch_box<T, V>(keep, n, nvv, (const T*)o.box, a, b, c, x, xprev, d, out, o, stream);
+  }
+  // Blocks up to 128 MiB, where the vector units are what the slice kernel relieves; above, memory
+  // bounds the step, and it was 1.5% slower (N = 262144, N_v = 80, FP64: 148.8 us against 146.6).
+  // Its offsets are 32 bits: CSR arrays below 4 GiB.  Rows of whole waves read their entries
+  // through the scalar cache instead.
+  if (nvv % 64 != 0 && keep && nnz * (int64_t)sizeof(T) < ((int64_t)1 << 32)) {
+    const auto fn = dots ? cheb_slice_kernel<T, V, true> : cheb_slice_kernel<T, V, false>;
+    hipLaunchKernelGGL(fn, grid, dim3(CS_THREADS), 0, stream, (uint32_t)threads, (uint32_t)nvv, FastDiv((uint32_t)nvv),
+                       (uint32_t)nblocks, (uint32_t)per_xcd, row_ptr, col_idx, val, (uint32_t)nnz, a, b, c, (const V*)x,
+                       (const V*)xprev, (const V*)d, (V*)out, dots, o.nx > 0 ? TileOrder(o) : TileOrder());
+    return hipGetLastError();
+  }
+  if (o.nx > 0) {
     if (nvv % 64 == 0)
       return launch_v<T, V, true, true>(grid, keep, n, nvv, nblocks, per_xcd, row_ptr, col_idx, val, a, b, c, x, xprev,
                                         d, out, dots, o, stream);
@@ -543,17 +629,17 @@ hipError_t launch_run(int n, int nvv, const int32_t* row_ptr, const int32_t* col
 }  // namespace
 
 hipError_t launch_cheb_step_f64(int64_t n, int nv, const int32_t* row_ptr, const int32_t* col_idx,
-                                const double* val, double a, double b, double c, const double* x,
+                                const double* val, int64_t nnz, double a, double b, double c, const double* x,
                                 const double* xprev, const double* d, double* out, hipStream_t stream,
                                 double* dots, const RowOrder& order) {
-  return launch<double, f64x2, 2>(n, nv, row_ptr, col_idx, val, a, b, c, x, xprev, d, out, dots, order, stream);
+  return launch<double, f64x2, 2>(n, nv, row_ptr, col_idx, val, nnz, a, b, c, x, xprev, d, out, dots, order, stream);
 }
 
 hipError_t launch_cheb_step_f32(int64_t n, int nv, const int32_t* row_ptr, const int32_t* col_idx,
-                                const float* val, float a, float b, float c, const float* x,
+                                const float* val, int64_t nnz, float a, float b, float c, const float* x,
                                 const float* xprev, const float* d, float* out, hipStream_t stream,
                                 double* dots, const RowOrder& order) {
-  return launch<float, f32x4, 4>(n, nv, row_ptr, col_idx, val, a, b, c, x, xprev, d, out, dots, order, stream);
+  return launch<float, f32x4, 4>(n, nv, row_ptr, col_idx, val, nnz, a, b, c, x, xprev, d, out, dots, order, stream);
 }
 
 // Rows of more entries would mostly be read again each step, and more than 256 slices would take

@@ -717,12 +717,12 @@ ssm_status forward_pass(ssm_ctx* c, int pass, bool first, Timeline* tl, int64_t&
           const bool moments = first && pl.dgc_group && s_step < dgc_steps(m);
           double* dots = moments ? c->dpart + (size_t)(s_step % pl.dgc_group) * 2 * dgc_nblocks : nullptr;
           if (f64)
-            err = ssm::launch_cheb_step_f64(n, nv, c->a.row_ptr, c->a.col_idx, (const double*)c->a.values, a, b, cc,
-                                            (const double*)x, (const double*)xp, nullptr, (double*)out, st, dots,
+            err = ssm::launch_cheb_step_f64(n, nv, c->a.row_ptr, c->a.col_idx, (const double*)c->a.values, c->a.nnz, a, b,
+                                            cc, (const double*)x, (const double*)xp, nullptr, (double*)out, st, dots,
                                             c->order);
           else
-            err = ssm::launch_cheb_step_f32(n, nv, c->a.row_ptr, c->a.col_idx, (const float*)c->a.values, (float)a,
-                                            (float)b, (float)cc, (const float*)x, (const float*)xp, nullptr,
+            err = ssm::launch_cheb_step_f32(n, nv, c->a.row_ptr, c->a.col_idx, (const float*)c->a.values, c->a.nnz,
+                                            (float)a, (float)b, (float)cc, (const float*)x, (const float*)xp, nullptr,
                                             (float*)out, st, dots, c->order);
           ++spmm_launches;
           if (err == hipSuccess && moments &&
@@ -950,12 +950,12 @@ ssm_status ress_dos(ssm_ctx* c, double* dos_host, int32_t* ranks_host) {
       const char* xp = kk == 1 ? nullptr : slot(kk - 2);
       const double sa = kk == 1 ? alpha : 2.0 * alpha, sb = kk == 1 ? beta : 2.0 * beta, sc = kk == 1 ? 0.0 : -1.0;
       if (f64)
-        err = ssm::launch_cheb_step_f64(n, nvp, c->a.row_ptr, c->a.col_idx, (const double*)c->a.values, sa, sb, sc,
-                                        (const double*)x, (const double*)xp, nullptr, (double*)slot(kk), st, nullptr,
+        err = ssm::launch_cheb_step_f64(n, nvp, c->a.row_ptr, c->a.col_idx, (const double*)c->a.values, c->a.nnz, sa, sb,
+                                        sc, (const double*)x, (const double*)xp, nullptr, (double*)slot(kk), st, nullptr,
                                         c->order);
       else
-        err = ssm::launch_cheb_step_f32(n, nvp, c->a.row_ptr, c->a.col_idx, (const float*)c->a.values, (float)sa,
-                                        (float)sb, (float)sc, (const float*)x, (const float*)xp, nullptr,
+        err = ssm::launch_cheb_step_f32(n, nvp, c->a.row_ptr, c->a.col_idx, (const float*)c->a.values, c->a.nnz,
+                                        (float)sa, (float)sb, (float)sc, (const float*)x, (const float*)xp, nullptr,
                                         (float*)slot(kk), st, nullptr, c->order);
       if (err != hipSuccess) return hip_fail(err, "Chebyshev step");
       ++spmm_launches;
@@ -1169,10 +1169,10 @@ ssm_status ssm_backward(ssm_ctx* c, const double* dos_bar_host, double* grad_dev
   auto cheb = [&](const void* x, const void* xp, void* out) {
     const double a = xp ? 2 * alpha : alpha, b = xp ? 2 * beta : beta, cc = xp ? -1.0 : 0.0;
     if (f64)
-      return ssm::launch_cheb_step_f64(n, nv, c->a.row_ptr, c->a.col_idx, (const double*)c->a.values, a, b, cc,
-                                       (const double*)x, (const double*)xp, nullptr, (double*)out, st, nullptr,
+      return ssm::launch_cheb_step_f64(n, nv, c->a.row_ptr, c->a.col_idx, (const double*)c->a.values, c->a.nnz, a, b,
+                                       cc, (const double*)x, (const double*)xp, nullptr, (double*)out, st, nullptr,
                                        c->order);
-    return ssm::launch_cheb_step_f32(n, nv, c->a.row_ptr, c->a.col_idx, (const float*)c->a.values, (float)a,
+    return ssm::launch_cheb_step_f32(n, nv, c->a.row_ptr, c->a.col_idx, (const float*)c->a.values, c->a.nnz, (float)a,
                                      (float)b, (float)cc, (const float*)x, (const float*)xp, nullptr, (float*)out, st,
                                      nullptr, c->order);
   };
@@ -1546,9 +1546,9 @@ ssm_status ssm_chebyshev(const ssm_csr* a, double lo, double hi, int32_t precisi
     const char* x = (char*)y + (size_t)(k - 1) * e * es;
     const char* xp = k >= 2 ? (char*)y + (size_t)(k - 2) * e * es : nullptr;
     const double aa = k == 1 ? alpha : 2 * alpha, bb = k == 1 ? beta : 2 * beta, cc = k == 1 ? 0.0 : -1.0;
-    hipError_t err = f64 ? ssm::launch_cheb_step_f64(a->n, nv, a->row_ptr, a->col_idx, (const double*)a->values, aa, bb,
-                                                     cc, (const double*)x, (const double*)xp, nullptr, (double*)out, st)
-                         : ssm::launch_cheb_step_f32(a->n, nv, a->row_ptr, a->col_idx, (const float*)a->values,
+    hipError_t err = f64 ? ssm::launch_cheb_step_f64(a->n, nv, a->row_ptr, a->col_idx, (const double*)a->values, a->nnz,
+                                                     aa, bb, cc, (const double*)x, (const double*)xp, nullptr, (double*)out, st)
+                         : ssm::launch_cheb_step_f32(a->n, nv, a->row_ptr, a->col_idx, (const float*)a->values, a->nnz,
                                                      (float)aa, (float)bb, (float)cc, (const float*)x,
                                                      (const float*)xp, nullptr, (float*)out, st);
     if (err != hipSuccess) return hip_fail(err, "Chebyshev step");

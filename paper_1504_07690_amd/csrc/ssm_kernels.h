@@ -76,11 +76,11 @@ constexpr int kBoxRows = 8;
 //   out = a * (A x) + b * x + c * xprev + d   (xprev, d may be null)
 // The rows are computed in `order` (the result does not depend on it).
 hipError_t launch_cheb_step_f64(int64_t n, int nv, const int32_t* row_ptr, const int32_t* col_idx,
-                                const double* val, double a, double b, double c, const double* x,
+                                const double* val, int64_t nnz, double a, double b, double c, const double* x,
                                 const double* xprev, const double* d, double* out, hipStream_t stream,
                                 double* dots = nullptr, const RowOrder& order = RowOrder{});
 hipError_t launch_cheb_step_f32(int64_t n, int nv, const int32_t* row_ptr, const int32_t* col_idx,
-                                const float* val, float a, float b, float c, const float* x,
+                                const float* val, int64_t nnz, float a, float b, float c, const float* x,
                                 const float* xprev, const float* d, float* out, hipStream_t stream,
                                 double* dots = nullptr, const RowOrder& order = RowOrder{});
 // Blocks Y_k0 .. Y_k1 (1 <= k0 <= k1) in one launch, Y_k to slot k % ring of y, from x = Y_k0-1 and

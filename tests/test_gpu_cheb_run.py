@@ -51,6 +51,26 @@ def test_run_equals_steps(n, nv, degree, kind, dtype):
     assert torch.equal(ys, yl[:, :n])
 
 
+@pytest.mark.parametrize("dtype,nv", [(torch.float32, 252), (torch.float64, 132), (torch.float32, 20)])
+def test_step_kernels_agree(dtype, nv):
+    """A block above 128 MiB and one below it take different step kernels: the same bits in the rows
+    that they share.  The last row of the smaller matrix ends at the end of its arrays."""
+    from paper_1504_07690_amd import ssm as S
+    n = 2501
+    rows = _rows(n, "long", np.random.default_rng(nv))
+    big = (129 << 20) // (nv * torch.empty((), dtype=dtype).element_size())
+    small = _csr(rows, n, dtype, np.random.default_rng(5))
+    large = _csr(rows, big, dtype, np.random.default_rng(5))
+    g = torch.Generator(device=DEV).manual_seed(n)
+    w = torch.randn(big, nv, dtype=dtype, device=DEV, generator=g)
+    ys = torch.full((5, n, nv), 7.0, dtype=dtype, device=DEV)
+    yl = torch.empty(5, big, nv, dtype=dtype, device=DEV)
+    precision = "fp32" if dtype == torch.float32 else "fp64"
+    S.chebyshev(small, -1.3, 1.1, precision, w[:n].contiguous(), ys)
+    S.chebyshev(large, -1.3, 1.1, precision, w, yl)
+    assert torch.equal(ys, yl[:, :n])
+
+
 @pytest.mark.parametrize("precision", ["fp32", "fp64"])
 def test_run_across_ring_chunks(precision):
     """With a ring of all blocks and of 16 slots: with the inner products of Algorithm 2 the recurrence
