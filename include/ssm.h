@@ -395,10 +395,9 @@ ssm_status ssm_sweep_split(int64_t e, int32_t kc, int32_t ntb, const void* chi, 
  * (W^T Z_i + Z_i^T W)/2 up to rounding with one block product less.
  * k_z[i] = Z_i^T Z_i  (nv x nv doubles each), Z_i = z + i*n*nv.
  * Products and sums in FP64 (FP32 inputs widened exactly).
- * w, z: double for SSM_FP64, float otherwise.  The rows are split in nseg
- * segments, each walked by four waves whose partial sums go to `scratch`
- * (4*nseg*ntb*2*nv*nv doubles)
- * and are then added in a fixed order (deterministic). */
+ * w, z: double for SSM_FP64, float otherwise.  Partial sums over rows go to
+ * `scratch` (4*nseg*ntb*2*nv*nv doubles: at most 4*nseg of them a point) and are
+ * then added in a fixed order (deterministic). */
 ssm_status ssm_gram(int32_t precision, int64_t n, int32_t nv, int32_t ntb, const void* w, const void* z,
                     double* k_w, double* k_z, int32_t nseg, double* scratch, void* stream);
 

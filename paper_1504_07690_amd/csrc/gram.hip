@@ -20,7 +20,7 @@
 // a time (two MFMA steps of four rows), writes its partial blocks to scratch at each item's end,
 // and a second kernel adds the partials of an item in order and completes the symmetric
 // matrices (deterministic).  Where the caller's scratch (4 nseg partials per point) or the number
-// of items is too small for that, every item is cut into 4 nseg parts.
+// of items is too small for that, or the parts are short, every item is cut into 4 nseg parts.
 //
 // What bounds it: the FP64 matrix cores.  Operands come straight from memory, two steps ahead of
 // the MFMAs that consume them: lane l reads column 16a + l%16 of row r + l/16 for each column
@@ -47,8 +47,16 @@ constexpr int GR_ROWS = 8;    // rows per unit of work
 struct GramShare {
   int64_t units;  // per item
   int64_t items, q, rem;
+  int64_t seg;
   int waves, parts;
 
+  // first row of piece k, or the row past its last (end = 1)
+  __host__ __device__ int64_t part_begin(int k, int64_t n, int end = 0) const {
+    const int64_t s0 = k / GR_WAVES * seg, s1 = s0 + seg < n ? s0 + seg : n;
+    const int64_t q = ((s1 - s0 + GR_WAVES - 1) / GR_WAVES + 3) / 4 * 4;
+    const int64_t r = s0 + (k % GR_WAVES + end) * q;
+    return r < s1 ? r : s1;
+  }
   __host__ __device__ int64_t start(int64_t w) const { return w * q + (w < rem ? w : rem); }
   // the wave that holds unit u of the line
   __host__ __device__ int64_t owner(int64_t u) const {
@@ -234,28 +242,28 @@ __device__ __forceinline__ void gram_share(const GramShare& sh, int64_t wv, int6
                                            int64_t z_stride, double* __restrict__ part, F locate) {
   using G = GramShape<TA, TB, UPPER>;
   const int64_t nn = (int64_t)nv * nv;
-  int64_t it, u, left;  // item, first unit in it, units left to do
+  int64_t it, r0, left;  // item, first row in it, rows left to do
+  const int64_t item = sh.units * GR_ROWS;  // rows of an item, the last unit filled up
   if (sh.parts) {
     it = wv / sh.parts;
-    const int64_t k = wv - it * sh.parts;
-    u = k * sh.units / sh.parts;
-    left = (k + 1) * sh.units / sh.parts - u;
+    const int k = (int)(wv - it * sh.parts);
+    r0 = sh.part_begin(k, n);
+    left = sh.part_begin(k, n, 1) - r0;
   } else {
     const int64_t s0 = sh.start(wv);
     it = s0 / sh.units;
-    u = s0 - it * sh.units;
-    left = sh.start(wv + 1) - s0;
+    r0 = (s0 - it * sh.units) * GR_ROWS;
+    left = (sh.start(wv + 1) - s0) * GR_ROWS;
   }
 #pragma unroll 1
-  while (left > 0) {
-    const int64_t take = left < sh.units - u ? left : sh.units - u;
+  do {
+    const int64_t take = left < item - r0 ? left : item - r0;
     const int zt = (int)(it / ntb);
     const int i = (int)(it - (int64_t)zt * ntb);
     const int64_t slot = sh.parts ? wv - it * sh.parts : wv - sh.owner(it * sh.units);
     int ca, cb;
     locate(zt, ca, cb);
-    const int64_t r0 = u * GR_ROWS;
-    const int64_t r1 = r0 + take * GR_ROWS < n ? r0 + take * GR_ROWS : n;
+    const int64_t r1 = r0 + take < n ? r0 + take : n;
     f64x4 acc_zz[G::NP], acc_wz[G::NP];
 #pragma unroll
     for (int p = 0; p < G::NP; ++p) {
@@ -267,8 +275,8 @@ __device__ __forceinline__ void gram_share(const GramShare& sh, int64_t wv, int6
     gram_store<TA, TB, UPPER>(part + (slot * ntb + i) * 2 * nn, nv, ca, cb, acc_zz, acc_wz);
     left -= take;
     ++it;
-    u = 0;
-  }
+    r0 = 0;
+  } while (left > 0);
 }
 
 // T >= 1: one tile of T x T blocks (upper); T = 0: 4 x 4-block tiles
@@ -345,12 +353,14 @@ bool share_evenly(GramShare& sh, int64_t waves, int slots, int64_t max_rows) {
   return (sh.units + sh.q - 1) / sh.q + 1 <= slots && std::min(sh.q + 1, sh.units) * GR_ROWS <= max_rows;
 }
 
-// every item in as many parts as the scratch has slots
-bool share_parts(GramShare& sh, int slots, int64_t max_rows) {
-  sh.parts = (int)std::min<int64_t>(slots, sh.units);
-  if (sh.items * sh.parts > 0x3FFFFFFF) return false;
-  sh.waves = (int)(sh.items * sh.parts);
-  return ((sh.units + sh.parts - 1) / sh.parts) * GR_ROWS <= max_rows;
+// every item in its scratch's slots: segments of `seg` rows of GR_WAVES parts
+bool share_parts(GramShare& sh, int64_t n, int64_t seg, int64_t max_rows) {
+  const int64_t parts = (n + seg - 1) / seg * GR_WAVES;
+  if (sh.items * parts > 0x3FFFFFFF) return false;
+  sh.seg = seg;
+  sh.parts = (int)parts;
+  sh.waves = (int)(sh.items * parts);
+  return seg / GR_WAVES <= max_rows;
 }
 
 template <int T>
@@ -364,11 +374,17 @@ hipError_t launch_t(int is_f32, GramPlan& pl, int nv, int nseg, const void* w, i
   // matrix work of a row: 20 MFMAs a step on a diagonal tile, 32 off it
   const int64_t dw = pl.diag.items * 20, ow = pl.off.items * 32;
   const int64_t wd = ow ? std::max<int64_t>(1, resident * dw / (dw + ow)) : resident;
-  const bool fits = (pl.diag.items + pl.off.items) * slots > resident && share_evenly(pl.diag, wd, slots, max_rows) &&
+  // Rows of a segment, of which a part is a quarter.  Parts below 1024 rows stay parts: a wave's
+  // even share is a longer chain of sums, whose rounding shows where the chains are short (a RESS-DGC
+  // ring of 1000 rows: 2.5e-15 of the largest moment against 5e-16 in parts of 252; none at 262144).
+  int64_t seg = (pl.n + nseg - 1) / nseg;
+  seg = (seg + 4 * GR_WAVES - 1) / (4 * GR_WAVES) * (4 * GR_WAVES);
+  const bool fits = seg / GR_WAVES >= 1024 && (pl.diag.items + pl.off.items) * slots > resident &&
+                    share_evenly(pl.diag, wd, slots, max_rows) &&
                     (!ow || share_evenly(pl.off, resident - wd, slots, max_rows));
   if (!fits) {
     pl = whole;
-    if (!share_parts(pl.diag, slots, max_rows) || (ow && !share_parts(pl.off, slots, max_rows)))
+    if (!share_parts(pl.diag, pl.n, seg, max_rows) || (ow && !share_parts(pl.off, pl.n, seg, max_rows)))
       return hipErrorInvalidValue;
   }
   const int64_t waves = (int64_t)pl.diag.waves + pl.off.waves;
