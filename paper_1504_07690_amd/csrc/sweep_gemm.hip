@@ -14,6 +14,7 @@
 // a run of consecutive (point-tile, element-tile) pairs with the point tile
 // fastest, so all point tiles that read one Y slice share that XCD's L2.
 #include "ssm_kernels.h"
+#include "sweep_tiles.h"
 
 #include <type_traits>
 
@@ -254,10 +255,9 @@ __global__ void __launch_bounds__(256, (sweep_waves<T, MB>()))
   tile_coords(mt, nt_tiles, m_tile, n_tile);
   if (n_tile < 0) return;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int nb = (ntb + Op::MT - 1) / Op::MT;
-  const int b0 = (int)((int64_t)m_tile * nb / mt);
-  const int count = (int)((int64_t)(m_tile + 1) * nb / mt) - b0;  // MB or MB - 1
-  const int64_t i0 = (int64_t)b0 * Op::MT;
+  const SweepTiling tiles{(ntb + Op::MT - 1) / Op::MT, mt};
+  const int count = tiles.count(m_tile);  // MB or MB - 1: the launch has MB = tiles.mb()
+  const int64_t i0 = (int64_t)tiles.first(m_tile) * Op::MT;
   const int64_t q0 = ((int64_t)n_tile * 4 + wave) * (Op::NB * Op::VEC * Op::MT);
   if (q0 >= e) return;  // uniform over the wave; the kernel has no barrier
   if (MB == 1 || count == MB)
@@ -751,42 +751,22 @@ hipError_t launch_tiles(K kernel, int bm, int bn, int64_t e, int kc, int ntb, co
 
 namespace {
 
-// Tiles of points: the count mt that makes the busiest SIMD's share smallest.  A launch has
-// strips x mt waves of ceil(nb / mt) blocks' matrix work (nb blocks of MT points in all) on
-// 1024 SIMDs.  While a SIMD gets only a few waves, whole waves count; with many, the mean
-// does.  + 0.5 stands for the loads of a wave that do not grow with its blocks.
-template <int MAXB>
-int sweep_tiles(int64_t strips, int nb) {
-  int best = nb;
-  double cost = 0.0;
-  for (int mt = (nb + MAXB - 1) / MAXB; mt <= nb; ++mt) {
-    const int mb = (nb + mt - 1) / mt;
-    const int64_t per_simd = (strips * mt + 1023) / 1024;
-    const double c = per_simd <= 6 ? (double)per_simd * (mb + 0.5) : (double)strips * (nb + 0.5 * mt) / 1024.0;
-    if (cost == 0.0 || c < cost) {
-      cost = c;
-      best = mt;
-    }
-  }
-  return best;
-}
-
 template <typename T, int MB, int MAXB, bool WIDE>
-hipError_t launch_sweep_mb(int mb, int mt, int64_t e, int kc, int ntb, const T* c, int64_t ldc, int64_t acols,
-                           const T* y, T* z, int accumulate, hipStream_t stream) {
+hipError_t launch_sweep_mb(const SweepTiling& tiles, int64_t e, int kc, int ntb, const T* c, int64_t ldc,
+                           int64_t acols, const T* y, T* z, int accumulate, hipStream_t stream) {
   using Op = SweepOp<T>;
-  if (mb == MB) {
+  if (tiles.mb() == MB) {
     const int64_t bn = 4 * Op::NB * Op::VEC * Op::MT;
     const int64_t ntiles = (e + bn - 1) / bn;
-    const int64_t blocks = (int64_t)mt * ((ntiles + 7) / 8 * 8);
+    const int64_t blocks = (int64_t)tiles.mt * ((ntiles + 7) / 8 * 8);
     if (blocks > 0x7FFFFFFF) return hipErrorInvalidValue;
     hipLaunchKernelGGL((sweep_kernel<T, MB, WIDE>), dim3((unsigned)blocks), dim3(256), 0, stream, e, kc, ntb, c, ldc,
-                       acols, y, z, accumulate, mt, (int)ntiles);
+                       acols, y, z, accumulate, tiles.mt, (int)ntiles);
     return hipGetLastError();
   }
   if constexpr (MB < MAXB)
-    return launch_sweep_mb<T, MB + 1, MAXB, WIDE>(mb, mt, e, kc, ntb, c, ldc, acols, y, z, accumulate, stream);
-  return hipErrorInvalidValue;
+    return launch_sweep_mb<T, MB + 1, MAXB, WIDE>(tiles, e, kc, ntb, c, ldc, acols, y, z, accumulate, stream);
+  return hipErrorInvalidValue;  // no kernel of so many blocks
 }
 
 template <typename T, int MAXB>
@@ -799,13 +779,9 @@ hipError_t launch_sweep_any(int64_t e, int kc, int ntb, const T* c, int64_t ldc,
   const int nb = (ntb + Op::MT - 1) / Op::MT;
   const int64_t es = sizeof(T), limit = (int64_t)1 << 31;
   const bool wide = Op::KS * e * es >= limit || Op::KS * ldc * es >= limit;
-  if (wide) {  // the widest tile only
-    const int mt = (nb + MAXB - 1) / MAXB;
-    return launch_sweep_mb<T, MAXB, MAXB, true>(MAXB, mt, e, kc, ntb, c, ldc, acols, y, z, accumulate, stream);
-  }
-  const int mt = sweep_tiles<MAXB>((e + strip - 1) / strip, nb);
-  return launch_sweep_mb<T, 1, MAXB, false>((nb + mt - 1) / mt, mt, e, kc, ntb, c, ldc, acols, y, z, accumulate,
-                                            stream);
+  const SweepTiling tiles = sweep_tiling((e + strip - 1) / strip, nb, MAXB, wide);
+  if (wide) return launch_sweep_mb<T, 1, MAXB, true>(tiles, e, kc, ntb, c, ldc, acols, y, z, accumulate, stream);
+  return launch_sweep_mb<T, 1, MAXB, false>(tiles, e, kc, ntb, c, ldc, acols, y, z, accumulate, stream);
 }
 
 }  // namespace

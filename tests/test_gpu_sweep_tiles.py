@@ -44,3 +44,28 @@ def test_sweep_tile_edges(precision, accumulate, kc, ntb, ldc, e):
 @pytest.mark.parametrize("precision,e", [("fp64", (1 << 26) + 2), ("fp32", (1 << 28) + 4)])
 def test_sweep_wide_rows(precision, e):
     _check(precision, 3, 2, 4, e, False)
+
+
+# the same with several tiles of points, added onto Z: every block of points in one tile only
+@pytest.mark.parametrize("ntb", [65, 70, 80, 100])
+def test_sweep_wide_rows_accumulate(ntb):
+    from paper_1504_07690_amd import ssm as S
+    kc, e, piece = 3, (1 << 26) + 2, 1 << 23
+    g = torch.Generator(device=DEV).manual_seed(ntb)
+    c = torch.randn(kc, (ntb + 3) // 4 * 4, dtype=torch.float64, device=DEV, generator=g)
+    y = torch.randn(kc, e, dtype=torch.float64, device=DEV, generator=g)
+
+    def start(q):  # of Z's columns q .. q + piece - 1
+        col = torch.arange(q, min(q + piece, e), device=DEV, dtype=torch.float64)
+        return (1.0 + col % 1024) / 512 - torch.arange(ntb, device=DEV, dtype=torch.float64)[:, None] / 64
+
+    z = torch.empty(ntb, e, dtype=torch.float64, device=DEV)
+    for q in range(0, e, piece):
+        z[:, q: q + piece] = start(q)
+    S.sweep("fp64", c, y, z, accumulate=True)
+    cq = c[:, :ntb]
+    for q in range(0, e, piece):
+        yq, base = y[:, q: q + piece], start(q)
+        # a sum of kc rounded products in any order, and one more addition
+        bound = (kc + 2) * 2.0 ** -52 * (cq.abs().T @ yq.abs() + base.abs())
+        assert bool(((z[:, q: q + piece] - (cq.T @ yq + base)).abs() <= bound).all())
