@@ -13,14 +13,17 @@
 // of one point in registers.  Above, the block grid is cut into tiles of 4 x 4 blocks (ti <= tj)
 // and a wave keeps one tile's (the upper ten of a diagonal tile: with all sixteen a quarter of
 // the matrix work at N_v = 128 went into blocks that are never read).  The pairs (tile, point)
-// are items of n rows each.  The items of a kind (diagonal or not), laid end to end, are cut into
-// equal parts, one per wave, for as many waves as are resident on the 1024 SIMDs (the two kinds
-// sharing them by their matrix work), so that no last round is half empty: 125 points in 9
-// segments of 4 waves were 4.4 rounds of 1024 waves, 12% idle.  A wave walks its part eight rows at
-// a time (two MFMA steps of four rows), writes its partial blocks to scratch at each item's end,
-// and a second kernel adds the partials of an item in order and completes the symmetric
-// matrices (deterministic).  Where the caller's scratch (4 nseg partials per point) or the number
-// of items is too small for that, or the parts are short, every item is cut into 4 nseg parts.
+// are items of n rows each.  Every item is cut into 4 nseg parts, what the caller's scratch holds,
+// one per wave.  Where whole rounds of the waves resident on the 1024 SIMDs would leave the last one
+// rather empty (125 points in 9 segments of 4 waves are 4.4 rounds of 1024, 12% idle), the items, laid
+// end to end, are cut into equal shares instead, one per resident wave.  A wave walks its rows eight
+// at a time (two MFMA steps of four rows) and writes its partial blocks to scratch; a second kernel
+// adds the partials of an item in order and completes the symmetric matrices (deterministic).
+//
+// Rounding.  The error of a chain of MFMAs over sums of one sign grows with its length, not with the
+// root of it (rms of the diagonal of W^T Z at N = 262144, N_v = 80: parts of 7282 rows 1.9e-15, shares of
+// 32000 rows as one chain 9.2e-15).  So a share is summed in runs no longer than a part, each a chain
+// of its own, which are added in the wave's partial: then 1.8e-15.
 //
 // What bounds it: the FP64 matrix cores.  Operands come straight from memory, two steps ahead of
 // the MFMAs that consume them: lane l reads column 16a + l%16 of row r + l/16 for each column
@@ -43,11 +46,12 @@ constexpr int GR_ROWS = 8;    // rows per unit of work
 
 // The items of one kind (nz tiles x ntb points, item it = z ntb + i) and the waves that share
 // them.  parts > 0: every item in `parts` equal pieces, one per wave; else wave w takes q units
-// (GR_ROWS rows), and one more if w < rem, of the items' units laid end to end.
+// (GR_ROWS rows), and one more if w < rem, of the items' units laid end to end, in runs.
 struct GramShare {
   int64_t units;  // per item
   int64_t items, q, rem;
   int64_t seg;
+  int64_t run;  // rows of one chain of sums at most (a multiple of GR_ROWS)
   int waves, parts;
 
   // first row of piece k, or the row past its last (end = 1)
@@ -210,33 +214,68 @@ __device__ __forceinline__ void gram_rows(const In* __restrict__ z, const In* __
   }
 }
 
-template <int TA, int TB, bool UPPER>
-__device__ __forceinline__ void gram_store(double* __restrict__ pz, int nv, int ca, int cb,
+// The blocks into a partial, or (ADD and add) onto what the same lanes stored there before.  Entries past
+// N_v go to an offset past the resource's range: the hardware reads 0 there and drops the store.
+template <int TA, int TB, bool UPPER, bool ADD>
+__device__ __forceinline__ void gram_store(double* __restrict__ pz, int nv, int ca, int cb, bool add,
                                            const f64x4 (&acc_zz)[GramShape<TA, TB, UPPER>::NP],
                                            const f64x4 (&acc_wz)[GramShape<TA, TB, UPPER>::NP]) {
+  typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
   const int lane = threadIdx.x & 63;
-  double* pw = pz + (int64_t)nv * nv;
   int cols = nv;  // opaque: the bounds tests are made here, not kept in registers over the row loop
   asm volatile("" : "+s"(cols));
+  const __amdgpu_buffer_rsrc_t rp = __builtin_amdgcn_make_buffer_rsrc((void*)pz, (short)0, 16 * cols * cols, kBufferWord3);
+  const int to_w = 8 * cols * cols;
+  // the lane's entry r of block p; FP64 result layout: D[l/16 + 4r][l%16]
+  auto offset = [&](int p, int r) {
+    int a = 0, b = p;
+    if constexpr (UPPER) {
+      while (b >= TA - a) b -= TA - a++;
+      b += a;
+    } else {
+      a = p / TB;
+      b = p % TB;
+    }
+    const int row = 16 * (ca + a) + (lane >> 4) + 4 * r, col = 16 * (cb + b) + (lane & 15);
+    return row < cols && col < cols ? 8 * (row * cols + col) : (int)0x80000000;
+  };
+  // a group of blocks at a time: the loads of its old values are in flight together
+  constexpr int NP = GramShape<TA, TB, UPPER>::NP, G = !ADD ? 1 : NP == 15 ? 5 : NP >= 6 ? 2 : 1;
 #pragma unroll
-  for (int a = 0; a < TA; ++a)
+  for (int p0 = 0; p0 < NP; p0 += G) {
+    double z[G][4] = {}, w[G][4] = {};
+    if (ADD && add) {  // uniform
 #pragma unroll
-    for (int b = UPPER ? a : 0; b < TB; ++b) {
-      const int p = GramShape<TA, TB, UPPER>::index(a, b);
-      const int col = 16 * (cb + b) + (lane & 15);
+      for (int g = 0; g < G; ++g)
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int row = 16 * (ca + a) + (lane >> 4) + 4 * r;  // FP64 result layout: D[l/16 + 4r][l%16]
-        if (row < cols && col < cols) {
-          pz[(int64_t)row * cols + col] = acc_zz[p][r];
-          pw[(int64_t)row * cols + col] = acc_wz[p][r];
+        for (int r = 0; r < 4; ++r)
+          if (p0 + g < NP) {
+            const int off = offset(p0 + g, r);
+            z[g][r] = __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(rp, off, 0, 0));
+            w[g][r] = __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(rp, off, to_w, 0));
+          }
+    }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int g = 0; g < G; ++g)
+      if (p0 + g < NP) {
+        f64x4 az = acc_zz[p0 + g], aw = acc_wz[p0 + g];
+        // five blocks a side fill the accumulation registers, and stay there until their turn
+        if constexpr (ADD && NP == 15) asm volatile("" : "+a"(az), "+a"(aw));
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const int off = offset(p0 + g, r);
+          const double vz = ADD ? z[g][r] + az[r] : az[r], vw = ADD ? w[g][r] + aw[r] : aw[r];
+          __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, vz), rp, off, 0, 0);
+          __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, vw), rp, off, to_w, 0);
         }
       }
-    }
+    __builtin_amdgcn_sched_barrier(0);  // group by group: their offsets and old values need not be live together
+  }
 }
 
 // A wave's part of the items of one kind.  locate(zt, ca, cb) gives the first columns of tile zt.
-template <int TA, int TB, bool UPPER, typename In, typename F>
+template <int TA, int TB, bool UPPER, bool EVEN, typename In, typename F>
 __device__ __forceinline__ void gram_share(const GramShare& sh, int64_t wv, int64_t n, int ntb, int nv,
                                            const In* __restrict__ w, int64_t w_stride, const In* __restrict__ z,
                                            int64_t z_stride, double* __restrict__ part, F locate) {
@@ -244,7 +283,7 @@ __device__ __forceinline__ void gram_share(const GramShare& sh, int64_t wv, int6
   const int64_t nn = (int64_t)nv * nv;
   int64_t it, r0, left;  // item, first row in it, rows left to do
   const int64_t item = sh.units * GR_ROWS;  // rows of an item, the last unit filled up
-  if (sh.parts) {
+  if (!EVEN || sh.parts) {
     it = wv / sh.parts;
     const int k = (int)(wv - it * sh.parts);
     r0 = sh.part_begin(k, n);
@@ -255,12 +294,14 @@ __device__ __forceinline__ void gram_share(const GramShare& sh, int64_t wv, int6
     r0 = (s0 - it * sh.units) * GR_ROWS;
     left = (sh.start(wv + 1) - s0) * GR_ROWS;
   }
+  bool add = false;  // an item's later runs are added onto its first
 #pragma unroll 1
-  do {
-    const int64_t take = left < item - r0 ? left : item - r0;
+  do {  // a run: a chain of sums of its own
+    int64_t take = left < item - r0 ? left : item - r0;
+    if (EVEN && take > sh.run) take = sh.run;
     const int zt = (int)(it / ntb);
     const int i = (int)(it - (int64_t)zt * ntb);
-    const int64_t slot = sh.parts ? wv - it * sh.parts : wv - sh.owner(it * sh.units);
+    const int64_t slot = !EVEN || sh.parts ? wv - it * sh.parts : wv - sh.owner(it * sh.units);
     int ca, cb;
     locate(zt, ca, cb);
     const int64_t r1 = r0 + take < n ? r0 + take : n;
@@ -272,14 +313,26 @@ __device__ __forceinline__ void gram_share(const GramShare& sh, int64_t wv, int6
     }
     gram_rows<TA, TB, UPPER, In>(z + (int64_t)i * z_stride, w + (int64_t)i * w_stride, r0, (int)(r1 - r0), nv, ca, cb,
                                  acc_zz, acc_wz);
-    gram_store<TA, TB, UPPER>(part + (slot * ntb + i) * 2 * nn, nv, ca, cb, acc_zz, acc_wz);
+    gram_store<TA, TB, UPPER, EVEN>(part + (slot * ntb + i) * 2 * nn, nv, ca, cb, add, acc_zz, acc_wz);
     left -= take;
-    ++it;
-    r0 = 0;
-  } while (left > 0);
+    r0 += take;
+    add = r0 < item;
+    if (!add) {
+      ++it;
+      r0 = 0;
+    }
+  } while (EVEN && left > 0);
 }
 
 // T >= 1: one tile of T x T blocks (upper); T = 0: 4 x 4-block tiles
+// Even shares where the blocks leave registers for the partials they are added onto: at six blocks a side
+// the row loop spilled (N = 100000, N_v = 96, 64 points in FP64: 5.0 ms, in parts 3.0).  Tiles are so many
+// items that parts are not far from whole rounds (N = 200000, N_v = 256, 40 points: 23.5 ms, in parts 18.6).
+template <int T>
+constexpr bool gram_even() {
+  return T >= 1 && T <= 5;
+}
+
 template <int T>
 constexpr int gram_occupancy() {  // waves per SIMD (16 T (T + 1) accumulator registers, or 256)
   return T == 0 || T >= 5 ? 1 : T == 4 ? 2 : T == 3 ? 3 : T == 2 ? 5 : 8;
@@ -292,18 +345,18 @@ __global__ void __launch_bounds__(64 * GR_WAVES, (gram_occupancy<T>()))
   const int64_t wv = (int64_t)blockIdx.x * GR_WAVES + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   constexpr int D = T ? T : GT_B;
   if (wv < pl.diag.waves) {  // uniform over the wave; the kernel has no barrier
-    gram_share<D, D, true, In>(pl.diag, wv, pl.n, pl.ntb, nv, w, w_stride, z, z_stride, part,
-                               [](int zt, int& ca, int& cb) { ca = cb = GT_B * zt; });
+    gram_share<D, D, true, gram_even<T>(), In>(pl.diag, wv, pl.n, pl.ntb, nv, w, w_stride, z, z_stride, part,
+                                               [](int zt, int& ca, int& cb) { ca = cb = GT_B * zt; });
   } else if (T == 0 && wv < pl.diag.waves + pl.off.waves) {
     const int side = pl.ntile;
     if constexpr (T == 0)
-      gram_share<GT_B, GT_B, false, In>(pl.off, wv - pl.diag.waves, pl.n, pl.ntb, nv, w, w_stride, z, z_stride, part,
-                                        [side](int zt, int& ca, int& cb) {
-                                          int ti = 0;  // tiles (ti, tj), ti < tj, row by row
-                                          while (zt >= side - 1 - ti) zt -= side - 1 - ti++;
-                                          ca = GT_B * ti;
-                                          cb = GT_B * (ti + 1 + zt);
-                                        });
+      gram_share<GT_B, GT_B, false, false, In>(pl.off, wv - pl.diag.waves, pl.n, pl.ntb, nv, w, w_stride, z, z_stride,
+                                               part, [side](int zt, int& ca, int& cb) {
+                                                 int ti = 0;  // tiles (ti, tj), ti < tj, row by row
+                                                 while (zt >= side - 1 - ti) zt -= side - 1 - ti++;
+                                                 ca = GT_B * ti;
+                                                 cb = GT_B * (ti + 1 + zt);
+                                               });
   }
 }
 
@@ -340,17 +393,17 @@ __global__ void __launch_bounds__(256) gram_reduce_kernel(GramPlan pl, int nv, c
   k_w[gid] = both ? 0.5 * (sw1 + sw2) : sw1;
 }
 
-// `waves` equal shares of the items, if there is work for them (64 rows each), an item's
-// partials (at most its units over a wave's, and one) fit `slots`, and a wave's rows of an item
-// fit `max_rows`
-bool share_evenly(GramShare& sh, int64_t waves, int slots, int64_t max_rows) {
+// `waves` equal shares of the items in runs of at most `part` rows, if an item's partials (at most its
+// units over a wave's, and one) fit `slots` and a run's rows fit `max_rows`
+bool share_evenly(GramShare& sh, int64_t waves, int slots, int64_t part, int64_t max_rows) {
   const int64_t total = sh.items * sh.units;
-  if (waves < 1 || total < 8 * waves) return false;
+  if (total < waves) return false;
   sh.parts = 0;
   sh.waves = (int)waves;
   sh.q = total / waves;
   sh.rem = total % waves;
-  return (sh.units + sh.q - 1) / sh.q + 1 <= slots && std::min(sh.q + 1, sh.units) * GR_ROWS <= max_rows;
+  sh.run = part / GR_ROWS * GR_ROWS;
+  return (sh.units + sh.q - 1) / sh.q + 1 <= slots && sh.run <= max_rows;
 }
 
 // every item in its scratch's slots: segments of `seg` rows of GR_WAVES parts
@@ -360,7 +413,8 @@ bool share_parts(GramShare& sh, int64_t n, int64_t seg, int64_t max_rows) {
   sh.seg = seg;
   sh.parts = (int)parts;
   sh.waves = (int)(sh.items * parts);
-  return seg / GR_WAVES <= max_rows;
+  sh.run = seg / GR_WAVES;
+  return sh.run <= max_rows;
 }
 
 template <int T>
@@ -370,22 +424,19 @@ hipError_t launch_t(int is_f32, GramPlan& pl, int nv, int nseg, const void* w, i
   // a wave's rows, with the prefetch's overrun, must be addressable by 32-bit byte offsets
   const int64_t max_rows = (((int64_t)1 << 31) - 1) / ((int64_t)nv * (is_f32 ? 4 : 8)) - 16;
   const int64_t resident = 1024 * (int64_t)gram_occupancy<T>();
-  const GramPlan whole = pl;
-  // matrix work of a row: 20 MFMAs a step on a diagonal tile, 32 off it
-  const int64_t dw = pl.diag.items * 20, ow = pl.off.items * 32;
-  const int64_t wd = ow ? std::max<int64_t>(1, resident * dw / (dw + ow)) : resident;
-  // Rows of a segment, of which a part is a quarter.  Parts below 1024 rows stay parts: a wave's
-  // even share is a longer chain of sums, whose rounding shows where the chains are short (a RESS-DGC
-  // ring of 1000 rows: 2.5e-15 of the largest moment against 5e-16 in parts of 252; none at 262144).
+  // rows of a segment, of which a part is a quarter
   int64_t seg = (pl.n + nseg - 1) / nseg;
   seg = (seg + 4 * GR_WAVES - 1) / (4 * GR_WAVES) * (4 * GR_WAVES);
-  const bool fits = seg / GR_WAVES >= 1024 && (pl.diag.items + pl.off.items) * slots > resident &&
-                    share_evenly(pl.diag, wd, slots, max_rows) &&
-                    (!ow || share_evenly(pl.off, resident - wd, slots, max_rows));
-  if (!fits) {
-    pl = whole;
-    if (!share_parts(pl.diag, pl.n, seg, max_rows) || (ow && !share_parts(pl.off, pl.n, seg, max_rows)))
-      return hipErrorInvalidValue;
+  GramShare& d = pl.diag;
+  if (!share_parts(d, pl.n, seg, max_rows) || (pl.off.items && !share_parts(pl.off, pl.n, seg, max_rows)))
+    return hipErrorInvalidValue;
+  // Even shares instead where the parts' last round of resident waves would leave 5% and more of the
+  // waves' time idle, and parts are long beside the stores and loads of a run's end (1024 rows, a
+  // quarter of a millisecond at N_v = 80).  N = 262144, N_v = 80, 125 points: 8.94 ms in parts, 7.97 in even shares.
+  const int64_t idle = (d.waves + resident - 1) / resident * resident - d.waves;
+  if (gram_even<T>() && seg / GR_WAVES >= 1024 && d.waves > resident && 20 * idle >= d.waves) {
+    GramShare even = d;
+    if (share_evenly(even, resident, slots, seg / GR_WAVES, max_rows)) d = even;
   }
   const int64_t waves = (int64_t)pl.diag.waves + pl.off.waves;
   const dim3 grid((unsigned)((waves + GR_WAVES - 1) / GR_WAVES)), block(64 * GR_WAVES);
