@@ -1,6 +1,5 @@
-"""The Gram kernel's rounding where resident waves share rows evenly: against exact integer sums, no larger
-than with every item in the scratch's parts (a point at a time), whose chains of sums are short.  The
-matrix cores' sums of like sign drift in proportion to a chain's length."""
+"""The Gram kernel's rounding where resident waves share rows evenly: against compensated sums, no larger than
+with every item in the scratch's parts (a point at a time), whose chains of sums are short."""
 import numpy as np
 import pytest
 import torch
@@ -10,6 +9,24 @@ pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
 
 
+def _gram(a):
+    """a^T a as hi + lo: sums of 16 rows, added pairwise with their rounding errors kept (two-sum)."""
+    n, nv = a.shape
+    m = n // 16 * 16
+    b = a[:m].view(-1, 16, nv)
+    s = torch.bmm(b.transpose(1, 2).contiguous(), b.contiguous())
+    s = torch.cat([s, (a[m:].T.contiguous() @ a[m:])[None]])
+    lo = torch.zeros_like(s)
+    while s.shape[0] > 1:
+        if s.shape[0] % 2:
+            s, lo = torch.cat([s, torch.zeros_like(s[:1])]), torch.cat([lo, torch.zeros_like(lo[:1])])
+        x, y = s[0::2], s[1::2]
+        s = x + y
+        bb = s - x
+        lo = lo[0::2] + lo[1::2] + ((x - (s - bb)) + (y - bb))
+    return s[0], lo[0]
+
+
 @pytest.mark.parametrize("precision", ["fp32", "fp64"])
 @pytest.mark.parametrize("n,nv,ntb,nseg", [(40013, 80, 125, 9), (40013, 44, 125, 9), (45001, 64, 70, 9),
                                            (40013, 96, 60, 9), (40013, 128, 40, 9)])
@@ -17,25 +34,19 @@ def test_gram_shares_round_like_parts(precision, n, nv, ntb, nseg):
     from paper_1504_07690_amd import ssm as S
     dt = torch.float64 if precision == "fp64" else torch.float32
     g = torch.Generator(device=DEV).manual_seed(n + nv)
-    # integers of 23 bits: products below 2^46, sums below 2^62, exact in int64
-    w = torch.randint(1 << 22, 1 << 23, (n, nv), device=DEV, generator=g).to(dt)
+    w = torch.randn(n, nv, dtype=dt, device=DEV, generator=g)
     z = torch.empty(ntb, n, nv, dtype=dt, device=DEV)
     for i in range(ntb):
-        z[i] = torch.randint(1 << 22, 1 << 23, (n, nv), device=DEV, generator=g).to(dt)
+        z[i] = torch.randn(n, nv, dtype=dt, device=DEV, generator=g)
     kw = torch.empty(ntb, nv, nv, dtype=torch.float64, device=DEV)
     kz = torch.empty_like(kw)
     S.gram(precision, w, z, kw, kz, nseg=nseg)
-    k1, k2 = torch.empty(1, nv, nv, dtype=torch.float64, device=DEV), torch.empty(1, nv, nv, dtype=torch.float64,
-                                                                                  device=DEV)
-    err = {}
-    cols = min(nv, 16)  # the first block row of Z^T Z, in which every entry is stored as formed but the first block
+    one_w, one_z = torch.empty_like(kw[:1]), torch.empty_like(kz[:1])
+    shares, parts = [], []
     for i in (0, ntb // 2, ntb - 1):
-        S.gram(precision, w, z[i: i + 1], k1, k2, nseg=nseg)
-        zi = z[i].cpu().numpy().astype(np.int64)
-        exact = zi[:, :cols].T @ zi
-        for name, k in (("shares", kz[i]), ("parts", k2[0])):
-            d = k.cpu().numpy()[:cols].astype(np.int64) - exact
-            err.setdefault(name, []).append((d.astype(np.float64) / exact) ** 2)
-    rms = {name: float(np.sqrt(np.mean(e))) for name, e in err.items()}
+        S.gram(precision, w, z[i: i + 1], one_w, one_z, nseg=nseg)
+        hi, lo = _gram(z[i].double())
+        for k, err in ((kz[i], shares), (one_z[0], parts)):
+            err.append(((((k - hi) - lo).diagonal() / hi.diagonal()) ** 2).mean().item())
     # chains no longer than the parts': the same error up to what the rounding of three points scatters
-    assert rms["shares"] <= 1.5 * rms["parts"], rms
+    assert np.sqrt(np.mean(shares)) <= 1.5 * np.sqrt(np.mean(parts)), (shares, parts)
