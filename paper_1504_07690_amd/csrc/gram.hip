@@ -20,10 +20,10 @@
 // at a time (two MFMA steps of four rows) and writes its partial blocks to scratch; a second kernel
 // adds the partials of an item in order and completes the symmetric matrices (deterministic).
 //
-// Rounding.  The error of a chain of MFMAs over sums of one sign grows with its length, not with the
-// root of it (rms of the diagonal of W^T Z at N = 262144, N_v = 80: parts of 7282 rows 1.9e-15, shares of
-// 32000 rows as one chain 9.2e-15).  So a share is summed in runs no longer than a part, each a chain
-// of its own, which are added in the wave's partial: then 1.8e-15.
+// Rounding.  A matrix that is the sum of many chains of MFMAs is off in proportion to the chains' length:
+// each by its length's root, with as many fewer to average (rms of the diagonal of W^T Z at N = 262144,
+// N_v = 80: parts of 7282 rows 1.9e-15, shares of 32000 rows as one chain 9.2e-15).  So a share is summed
+// in runs no longer than a part, each a chain of its own, which are added in the wave's partial: 1.8e-15.
 //
 // What bounds it: the FP64 matrix cores.  Operands come straight from memory, two steps ahead of
 // the MFMAs that consume them: lane l reads column 16a + l%16 of row r + l/16 for each column
@@ -360,37 +360,74 @@ __global__ void __launch_bounds__(64 * GR_WAVES, (gram_occupancy<T>()))
   }
 }
 
-// K(i)[r][c] = sum over an item's partials of the stored upper block entry; the lower blocks
-// mirror the upper ones; the diagonal blocks are averaged with their transpose.
+// K(i) from its items' partials, added in order: a workgroup per 16 x 16 block (a <= b) of a point, an
+// entry per lane, which stores a diagonal block's average with its transpose, or the block and, through
+// LDS, its mirror.
+// What bounds it: reading the partials, GR_LOAD of each kind in flight a lane (N = 4096, N_v = 80, 200
+// points, 24 partials each: 0.3 GB).  A lane per entry of the whole matrices, which branched on the
+// block's kind before its loads, read most entries twice, those of the lower blocks N_v apart.
+// Measured, FP32 blocks: that case 520 to 76 us (before the branch 298), N = 1000, N_v = 80, 200 points
+// 220 to 26 (136), N = 200000, N_v = 256, 12 points 3600 to 318 (3600), N = 20000, N_v = 4, 16 points
+// 82 to 20.
+constexpr int GR_LOAD = 8;
+
 __global__ void __launch_bounds__(256) gram_reduce_kernel(GramPlan pl, int nv, const double* __restrict__ part,
                                                           double* __restrict__ k_w, double* __restrict__ k_z) {
+  __shared__ double tz[16][17], tw[16][17];
+  const int side = (nv + 15) / 16, pairs = side * (side + 1) / 2;
+  const int i = (int)(blockIdx.x / (unsigned)pairs);
+  int b = (int)blockIdx.x - i * pairs, a = 0;
+  while (b >= side - a) b -= side - a++;
+  b += a;
   const int64_t nn = (int64_t)nv * nv;
-  const int64_t gid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (gid >= (int64_t)pl.ntb * nn) return;
-  const int i = (int)(gid / nn);
-  const int rc = (int)(gid - (int64_t)i * nn);
-  const int r = rc / nv, c = rc % nv;
-  const int lo = (r < c ? r : c) >> 4, hi = (r < c ? c : r) >> 4;
-  const bool both = lo == hi;  // a diagonal block: (r, c) and (c, r) are stored
-  const int64_t o1 = lo == r >> 4 ? (int64_t)r * nv + c : (int64_t)c * nv + r;
-  const int64_t o2 = (int64_t)c * nv + r;
-  const int ti = pl.ntile ? lo / GT_B : 0, tj = pl.ntile ? hi / GT_B : 0;
+  const int ti = pl.ntile ? a / GT_B : 0, tj = pl.ntile ? b / GT_B : 0;
   const int zt = ti * (pl.ntile - 1) - ti * (ti - 1) / 2 + (tj - ti - 1);
   const int ns = ti == tj ? pl.diag.slots((int64_t)ti * pl.ntb + i) : pl.off.slots((int64_t)zt * pl.ntb + i);
-  double sz1 = 0.0, sw1 = 0.0, sz2 = 0.0, sw2 = 0.0;
-#pragma unroll 2
-  for (int s = 0; s < ns; ++s) {
-    const double* pz = part + ((int64_t)s * pl.ntb + i) * 2 * nn;
-    const double* pw = pz + nn;
-    sz1 += pz[o1];
-    sw1 += pw[o1];
-    if (both) {
-      sz2 += pz[o2];
-      sw2 += pw[o2];
+  const int y = threadIdx.x >> 4, x = threadIdx.x & 15;
+  const int r = 16 * a + y, c = 16 * b + x;
+  const bool in = r < nv && c < nv;
+  double sz = 0.0, sw = 0.0;
+  if (in) {
+    const double* p = part + (int64_t)i * 2 * nn + r * nv + c;
+    const int64_t step = (int64_t)pl.ntb * 2 * nn;
+    for (int s = 0; s < ns; s += GR_LOAD) {
+      double vz[GR_LOAD], vw[GR_LOAD];
+#pragma unroll
+      for (int u = 0; u < GR_LOAD; ++u) {
+        const double* q = p + (s + u < ns ? s + u : ns - 1) * step;
+        vz[u] = q[0];
+        vw[u] = q[nn];
+      }
+#pragma unroll
+      for (int u = 0; u < GR_LOAD; ++u) {
+        if (s + u < ns) {
+          sz += vz[u];
+          sw += vw[u];
+        }
+      }
     }
   }
-  k_z[gid] = both ? 0.5 * (sz1 + sz2) : sz1;
-  k_w[gid] = both ? 0.5 * (sw1 + sw2) : sw1;
+  tz[y][x] = sz;
+  tw[y][x] = sw;
+  __syncthreads();
+  double* oz = k_z + i * nn;
+  double* ow = k_w + i * nn;
+  if (a == b) {
+    if (in) {
+      oz[r * nv + c] = 0.5 * (sz + tz[x][y]);
+      ow[r * nv + c] = 0.5 * (sw + tw[x][y]);
+    }
+    return;
+  }
+  if (in) {
+    oz[r * nv + c] = sz;
+    ow[r * nv + c] = sw;
+  }
+  const int rm = 16 * b + y, cm = 16 * a + x;
+  if (rm < nv && cm < nv) {
+    oz[rm * nv + cm] = tz[x][y];
+    ow[rm * nv + cm] = tw[x][y];
+  }
 }
 
 // `waves` equal shares of the items in runs of at most `part` rows, if an item's partials (at most its
@@ -472,7 +509,7 @@ hipError_t launch_strided(int is_f32, int64_t n, int nv, int ntb, const void* w,
     default: err = launch_t<0>(is_f32, pl, nv, nseg, w, ws, z, zs, scratch, stream);
   }
   if (err != hipSuccess) return err;
-  const int64_t blocks = ((int64_t)ntb * nv * nv + 255) / 256;
+  const int64_t blocks = (int64_t)ntb * (t * (t + 1) / 2);
   if (blocks > 0x7FFFFFFF) return hipErrorInvalidValue;
   hipLaunchKernelGGL(gram_reduce_kernel, dim3((unsigned)blocks), dim3(256), 0, stream, pl, nv, scratch, k_w, k_z);
   return hipGetLastError();
