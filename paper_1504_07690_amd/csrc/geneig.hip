@@ -1846,9 +1846,8 @@ __global__ void __launch_bounds__(GT_TH) geneig_tri_trace_kernel(int nv, const d
 
 
 // d, for N_v <= 128.  The two products run on v_mfma_f64_16x16x4_f64, operands from memory:
-// T1 = K_Z^T U~ S~^-1/2 (K_Z^T for K_Z: B becomes B^T, which the symmetrisation takes to the same
-// matrix), then the blocks a <= b of B = (U~ S~^-1/2)^T T1; wave w takes the block columns b = w,
-// w + 4.  B is reduced in registers.  Where two Sturm counts find every xi inside [0, (1 + rho)
+// T1 = K_Z U~ S~^-1/2, then the blocks a <= b of B = (U~ S~^-1/2)^T T1; wave w takes the block columns
+// b = w, w + 4.  B is reduced in registers.  Where two Sturm counts find every xi inside [0, (1 + rho)
 // g_max], the usual case, the trace is that of the tridiagonal matrix; else every xi is bisected.
 // What bounds it: the reduction's chain (reg_reduce).  With eight eigenvectors at a time against
 // lane-per-column products, the reduction in global scratch and 53 counts per xi, 1000 points
@@ -1885,7 +1884,8 @@ __device__ __forceinline__ int reg_truncate(int n, const double* eig, double tau
 
 // Step 3: B = S~^-1/2 U~^T K_Z U~ S~^-1/2 (r1 x r1) into registers, lane (tr, tc) of the grid holding
 // the entries (tr + 16 a, tc + 16 b).  zt: eigenvector j in row j (stride ldz); q: n x 16 ceil(r1 /
-// 16) and bm: r1 rows of stride ldb, scratch (global or LDS).
+// 16) and bm: n rows of stride ldb, scratch (global or LDS).  Only B's blocks a <= b are formed, so
+// K_Z's symmetric part, which gives B's, goes through bm first.
 template <int T>
 __device__ __forceinline__ void reg_pencil(int n, int r1, const double* __restrict__ kz, const double* zt, int ldz,
                                            double* q, double* bm, int ldb, const int* kidx, const double* scale,
@@ -1897,6 +1897,15 @@ __device__ __forceinline__ void reg_pencil(int n, int r1, const double* __restri
   constexpr int KB = T >= 7 ? 2 : 4;
   const int nb = (r1 + 15) / 16, ldq = 16 * nb;
   const int lm = lane & 15, lk = lane >> 4;
+#pragma unroll
+  for (int a = 0; a < T; ++a)
+#pragma unroll
+    for (int b = 0; b < T; ++b) {
+      const int r = tr + 16 * a, c = tc + 16 * b;
+      if (r < n && c < n) bm[r * ldb + c] = 0.5 * (kz[r * n + c] + kz[c * n + r]);
+    }
+  __threadfence_block();
+  __syncthreads();
   int uo[T];           // eigenvector 16 a + lm's row of Z^T
   double us[T];
 #pragma unroll
@@ -1925,7 +1934,7 @@ __device__ __forceinline__ void reg_pencil(int n, int r1, const double* __restri
 #pragma unroll
         for (int a = 0; a < T; ++a) {
           const int r = 16 * a + lm;
-          av[s][a] = kz[kc * n + (r < n ? r : n - 1)];
+          av[s][a] = bm[kc * ldb + (r < n ? r : n - 1)];
         }
       }
 #pragma unroll

@@ -1,0 +1,37 @@
+"""Algorithm 4 where the given matrices are not symmetric: step 1 takes K_W's symmetric part, and step 3 the
+symmetric part of B, so that an antisymmetric part in either changes nothing."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import ssm_oracle as O
+
+pytestmark = pytest.mark.gpu
+
+DEV = "cuda:0"
+
+
+@pytest.mark.parametrize("nv", [2, 16, 17, 33, 40, 48, 49, 64, 81, 100, 128, 129, 200])
+def test_geneig_antisymmetric_parts_drop_out(nv):
+    from paper_1504_07690_amd import ssm as S
+    rng = np.random.default_rng(300 + nv)
+    npts, n = 3, 1000
+    kw, kz = np.empty((npts, nv, nv)), np.empty((npts, nv, nv))
+    for i in range(npts):
+        w = rng.standard_normal((n, nv))
+        z = w * rng.uniform(0.05, 0.95, n)[:, None]
+        skew = np.triu(rng.uniform(-0.2, 0.2, (nv, nv)) * n, 1)
+        skew -= skew.T
+        kw[i], kz[i] = w.T @ z, z.T @ z + skew
+        kw[i] = 0.5 * (kw[i] + kw[i].T) + (skew[::-1, ::-1] if i else 0.0)
+    dos = torch.full((npts,), 7.0, dtype=torch.float64, device=DEV)
+    ranks = torch.full((2 * npts,), -1, dtype=torch.int32, device=DEV)
+    # the second bound leaves some xi out of range, so that they are found one by one
+    for g_max in (1.0, 0.6):
+        S.geneig_trace(torch.tensor(kw, device=DEV), torch.tensor(kz, device=DEV), g_max, 1e-7, 1e-3, dos, ranks)
+        ref = [O.geneig_trace(kw[i], kz[i], g_max) for i in range(npts)]
+        # well conditioned K_W: 500 units of rounding in each of nv eigenvalues <= 1, by the parts' norms
+        scale = max(np.linalg.cond(0.5 * (k + k.T)) for k in kw) * (1 + 0.4 * nv ** 0.5)
+        assert ranks[:npts].tolist() == [r[1] for r in ref]
+        assert ranks[npts:].tolist() == [r[2] for r in ref]
+        assert np.abs(dos.cpu().numpy() - [r[0] for r in ref]).max() <= 500 * 2.0 ** -52 * nv * scale
