@@ -2005,28 +2005,34 @@ __device__ __forceinline__ void reg_pencil(int n, int r1, const double* __restri
     }
 }
 
-// Step 4: the in-range eigenvalues of B (in registers, spent): their sum and count, and whether
-// all of them are in range.  Every lane returns the same.
-template <int T>
-__device__ __forceinline__ bool reg_in_range(double (&A)[T][T], int r1, double hi, RegShared& sh, double* red,
-                                             int* misc, bool all_only, double& sum, int& count) {
+// Of the tridiagonal matrix (sh.d, sh.e) of order r1: whether two Sturm counts find every eigenvalue in
+// [0, hi].  Leaves e^2 in sh.x, and its maximum.  Every lane calls it and returns the same.
+__device__ __forceinline__ bool reg_all_in_range(int r1, double hi, RegShared& sh, int* misc, double& e2max) {
   const int tid = threadIdx.x;
-  reg_reduce<T, false>(A, r1, nullptr, 0, sh);
   double* e2 = sh.x;
   for (int j = tid; j + 1 < r1; j += GT_TH) e2[j] = sh.e[j] * sh.e[j];
   __syncthreads();
-  double e2max = 0.0;
+  e2max = 0.0;
   for (int j = 0; j + 1 < r1; ++j) e2max = fmax(e2max, e2[j]);
   const double pivmin = 0x1p-1022 * fmax(1.0, e2max);
   if (tid < 2) misc[1 + tid] = tri_count(r1, sh.d, e2, tid ? hi : 0.0, pivmin);
   __syncthreads();
-  const bool all = misc[1] == 0 && misc[2] == r1;
+  return misc[1] == 0 && misc[2] == r1;
+}
+
+// Step 4: the in-range eigenvalues of B (in registers, spent): their sum and count, the same in every lane.
+template <int T>
+__device__ __forceinline__ void reg_in_range(double (&A)[T][T], int r1, double hi, RegShared& sh, double* red,
+                                             int* misc, double& sum, int& count) {
+  const int tid = threadIdx.x;
+  reg_reduce<T, false>(A, r1, nullptr, 0, sh);
+  double e2max;
   double part = 0.0;
   int in = 0;
-  if (all) {
+  if (reg_all_in_range(r1, hi, sh, misc, e2max)) {
     if (tid < r1) part = sh.d[tid];
     in = tid < r1;
-  } else if (!all_only) {
+  } else {
     double glo = INFINITY, ghi = -INFINITY;
     for (int j = 0; j < r1; ++j) {
       const double rad = (j > 0 ? fabs(sh.e[j - 1]) : 0.0) + (j + 1 < r1 ? fabs(sh.e[j]) : 0.0);
@@ -2034,7 +2040,7 @@ __device__ __forceinline__ bool reg_in_range(double (&A)[T][T], int r1, double h
       ghi = fmax(ghi, sh.d[j] + rad);
     }
     if (tid < r1) {
-      const double xi = tri_bisect(tid, r1, sh.d, e2, glo, ghi, e2max);
+      const double xi = tri_bisect(tid, r1, sh.d, sh.x, glo, ghi, e2max);
       if (xi >= 0.0 && xi <= hi) {
         part = xi;
         in = 1;
@@ -2043,7 +2049,6 @@ __device__ __forceinline__ bool reg_in_range(double (&A)[T][T], int r1, double h
   }
   sum = gt_sum(part, red);
   count = __syncthreads_count(in);
-  return all;
 }
 
 template <int T>
@@ -2066,7 +2071,7 @@ __global__ void __launch_bounds__(GT_TH, reg_waves<T>())
   if (r1 > 0) {
     double A[T][T];
     reg_pencil<T>(n, r1, k_z + i * (int64_t)n * n, pt.zt, n, pt.rec, pt.a, n, kidx, scale, A);
-    reg_in_range<T>(A, r1, (1.0 + rho) * g_max, sh, red, misc, false, sum, r2);
+    reg_in_range<T>(A, r1, (1.0 + rho) * g_max, sh, red, misc, sum, r2);
   }
   if (threadIdx.x == 0) {
     dos[i] = sum;
@@ -2096,15 +2101,18 @@ __device__ __forceinline__ bool small_in_scale(const double (&A)[T][T]) {
 // reduction (reg_reduce, reflectors in LDS), then wave 0 runs the QL iterations while wave 1, one
 // row of U per lane, applies the reflectors and then each iteration's rotations one iteration
 // behind (one barrier an iteration, the rotations passed by plane through two buffers), then
-// the truncation, B and the trace as above.  nvh > 0: the hybrid term too, where every xi is in
-// range (then ||G Q~||_F = ||G||_F, G = K_C U~ S~^-1/2).  flag[i] becomes 1, and the Jacobi kernel
-// does the point, where QL runs past its limit, where K_W or B is not finite or its largest entry
-// is not within 1e-100 .. 1e100 (f^2 + g^2 and the Sturm counts' e^2 could leave FP64's range), or
-// where with nvh > 0 an xi is out of range; else 0.
+// the truncation, B and the trace as above.  nvh > 0: the hybrid term too: ||G Q~||_F = ||G||_F, G =
+// K_C U~ S~^-1/2, where every xi is in range; else B's reduction goes on through the same QL and
+// rows, and G Q~ is summed over the in-range eigenvectors.  flag[i] becomes 1, and the Jacobi kernel
+// does the point, where QL runs past its limit, or where K_W or B is not finite or its largest
+// entry is not within 1e-100 .. 1e100 (f^2 + g^2 and the Sturm counts' e^2 could leave FP64's range);
+// else 0.
 // What bounds it: the QL chain, about 1.07 N_v^2 rotations.
 // Measured: N_v = 40, 200 points 1400 to 366 us, N_v = 16, 100 points 98 us (with its launch), the
-// cyclic Jacobi kernel before, seven sweeps of 39 rounds over K_W and as many over B.
-template <int T>
+// cyclic Jacobi kernel before, seven sweeps of 39 rounds over K_W and as many over B.  RESS-DGC of
+// N_v = 40 + 40, 200 points of a random graph, most with an xi out of range: 1.53 ms in that kernel,
+// 1.86 while such points went on to it, 0.63 now.
+template <int T, bool HYB>
 __global__ void __launch_bounds__(GT_TH)
     geneig_small_kernel(int nv, const double* __restrict__ k_w, const double* __restrict__ k_z, double g_max,
                         double tau, double rho, double* __restrict__ dos, int32_t* __restrict__ ranks,
@@ -2144,81 +2152,120 @@ __global__ void __launch_bounds__(GT_TH)
     }
     reg_reduce<T, true>(A, n, refl, LD, sh);
   }
-  if (tid < 64) de[tid] = tid < n ? (gt_f64x2){sh.d[tid], tid < n - 1 ? sh.e[tid] : 0.0} : (gt_f64x2){0.0, 0.0};
-  __syncthreads();
-  int state = 0;
-  int l = 0, iters = 0;  // wave 0
-  double x[N];           // wave 1
-  if (wave == 1) {
-#pragma unroll
-    for (int j = 0; j < N; ++j) x[j] = j == lane ? 1.0 : 0.0;
-  }
-  for (int it = 0;; ++it) {  // wave 0 forms iteration it, wave 1 applies iteration it - 1
-    if (wave == 0) {
-      int mm = 0, st = 0, i0 = 0;
-      if (!ql_block<1>(de, n, lane, l, mm)) {
-        st = 1;
-      } else if (++iters > GT_MAX_QL * n) {
-        st = 2;
-      } else {
-        gt_f64x2* w = cs0 + 64 * (it & 1);
-        w[lane] = (gt_f64x2){1.0, 0.0};
-        wave_sync();
-        i0 = ql_iterate<1>(de, w, own, lane, l, mm);
-        if (lane < i0) w[lane] = (gt_f64x2){1.0, 0.0};  // an iteration cut short by a split
-      }
-      if (lane == 0) {
-        hdr[it & 1][0] = mm;
-        hdr[it & 1][1] = i0;
-        hdr[it & 1][2] = st;
-      }
-    } else if (wave == 1) {
-      if (it == 0) {
-        for (int k = 0; k + 2 < n; ++k) {
-          const double tk = sh.tau[k];
-          if (tk != 0.0) rows_reflect<T>(x, refl + k * LD, tk, k);
-        }
-      } else {
-        const int mm = __builtin_amdgcn_readfirstlane(hdr[(it - 1) & 1][0]);
-        const int i0 = __builtin_amdgcn_readfirstlane(hdr[(it - 1) & 1][1]);
-        if (i0 < mm) rows_rotate<T>(x, cs0 + 64 * ((it - 1) & 1), mm, i0);
-      }
-    }
-    __syncthreads();
-    // uniform, and wave 0 writes this slot again only two iterations on, past the next barrier
-    state = __builtin_amdgcn_readfirstlane(hdr[it & 1][2]);
-    if (state != 0) break;
-  }
-  const bool stopped = state == 2;
-  if (wave == 1 && lane < N) {
-#pragma unroll
-    for (int j = 0; j < N; ++j) zt[j * LD + lane] = x[j];
-  }
-  if (tid < n) eig[tid] = de[tid].x;
-  if (tid == 0) flag[i * flag_stride] = stopped ? 1.0 : 0.0;
-  __syncthreads();
-  if (stopped) return;
-  const int r1 = reg_truncate(n, eig, tau, s_floor ? s_floor[i] : -INFINITY, kidx, scale, misc);
+  const double hi = (1.0 + rho) * g_max;
+  int m = n;          // order of T: K_W's, then (pass 1) B's
+  double* vec = zt;   // its eigenvectors, in rows
+  int r1 = 0, r2 = 0;
   double sum = 0.0;
-  int r2 = 0;
-  if (r1 > 0) {
-    double A[T][T];
-    reg_pencil<T>(n, r1, kz, zt, LD, refl, bm, LD, kidx, scale, A);
-    if (!small_in_scale<T>(A) ||
-        (!reg_in_range<T>(A, r1, (1.0 + rho) * g_max, sh, red, misc, nvh > 0, sum, r2) && nvh > 0)) {
+  bool all = true;    // every xi in range
+#pragma unroll 1
+  for (int pass = 0;; ++pass) {
+    if (tid < 64) de[tid] = tid < m ? (gt_f64x2){sh.d[tid], tid < m - 1 ? sh.e[tid] : 0.0} : (gt_f64x2){0.0, 0.0};
+    __syncthreads();
+    int state = 0;
+    int l = 0, iters = 0;  // wave 0
+    double x[N];           // wave 1
+    if (wave == 1) {
+#pragma unroll
+      for (int j = 0; j < N; ++j) x[j] = j == lane ? 1.0 : 0.0;
+    }
+    for (int it = 0;; ++it) {  // wave 0 forms iteration it, wave 1 applies iteration it - 1
+      if (wave == 0) {
+        int mm = 0, st = 0, i0 = 0;
+        if (!ql_block<1>(de, m, lane, l, mm)) {
+          st = 1;
+        } else if (++iters > GT_MAX_QL * m) {
+          st = 2;
+        } else {
+          gt_f64x2* w = cs0 + 64 * (it & 1);
+          w[lane] = (gt_f64x2){1.0, 0.0};
+          wave_sync();
+          i0 = ql_iterate<1>(de, w, own, lane, l, mm);
+          if (lane < i0) w[lane] = (gt_f64x2){1.0, 0.0};  // an iteration cut short by a split
+        }
+        if (lane == 0) {
+          hdr[it & 1][0] = mm;
+          hdr[it & 1][1] = i0;
+          hdr[it & 1][2] = st;
+        }
+      } else if (wave == 1) {
+        if (it == 0) {
+          for (int k = 0; k + 2 < m; ++k) {
+            const double tk = sh.tau[k];
+            if (tk != 0.0) rows_reflect<T>(x, refl + k * LD, tk, k);
+          }
+        } else {
+          const int mm = __builtin_amdgcn_readfirstlane(hdr[(it - 1) & 1][0]);
+          const int i0 = __builtin_amdgcn_readfirstlane(hdr[(it - 1) & 1][1]);
+          if (i0 < mm) rows_rotate<T>(x, cs0 + 64 * ((it - 1) & 1), mm, i0);
+        }
+      }
+      __syncthreads();
+      // uniform, and wave 0 writes this slot again only two iterations on, past the next barrier
+      state = __builtin_amdgcn_readfirstlane(hdr[it & 1][2]);
+      if (state != 0) break;
+    }
+    if (wave == 1 && lane < N) {
+#pragma unroll
+      for (int j = 0; j < N; ++j) vec[j * LD + lane] = x[j];
+    }
+    if (tid < m) eig[tid] = de[tid].x;
+    if (state == 2) {  // QL stopped
       if (tid == 0) flag[i * flag_stride] = 1.0;
       return;
     }
+    __syncthreads();
+    if (HYB && pass == 1) break;
+    r1 = reg_truncate(n, eig, tau, s_floor ? s_floor[i] : -INFINITY, kidx, scale, misc);
+    if (r1 == 0) break;
+    double A[T][T];
+    reg_pencil<T>(n, r1, kz, zt, LD, refl, bm, LD, kidx, scale, A);
+    if (HYB)  // B's reflectors are wanted: entries up to k and past r1 are zero
+      for (int j = tid; j < N * LD; j += GT_TH) refl[j] = 0.0;
+    if (!small_in_scale<T>(A)) {
+      if (tid == 0) flag[i * flag_stride] = 1.0;
+      return;
+    }
+    if constexpr (HYB) {
+      reg_reduce<T, true>(A, r1, refl, LD, sh);
+      double e2max;
+      all = reg_all_in_range(r1, hi, sh, misc, e2max);
+      if (all) {
+        sum = gt_sum(tid < r1 ? sh.d[tid] : 0.0, red);
+        r2 = r1;
+        break;
+      }
+      m = r1;
+      vec = bm;
+    } else {
+      reg_in_range<T>(A, r1, hi, sh, red, misc, sum, r2);
+      break;
+    }
   }
-  if (nvh > 0) {
+  if (tid == 0) flag[i * flag_stride] = 0.0;
+  if constexpr (HYB) {
     const double* kc = k_c + (int64_t)i * nvh * n;
+    if (!all) {  // C~ = U~ S~^-1/2 Q~ into the reflectors' place, a row each, zero for an xi out of range
+      const double xi = tid < r1 ? eig[tid] : -1.0;
+      const bool in = xi >= 0.0 && xi <= hi;
+      sum = gt_sum(in ? xi : 0.0, red);
+      r2 = __syncthreads_count(in);
+      for (int idx = tid; idx < n * r1; idx += GT_TH) {
+        const int j = idx / n, c = idx - j * n;
+        double v = 0.0;
+        if (eig[j] >= 0.0 && eig[j] <= hi)
+          for (int b = 0; b < r1; ++b) v = fma(scale[b] * zt[kidx[b] * LD + c], bm[j * LD + b], v);
+        refl[j * LD + c] = v;
+      }
+      __syncthreads();
+    }
     double part = 0.0;
     for (int idx = tid; idx < nvh * r1; idx += GT_TH) {
       const int a = idx / r1, b = idx - a * r1;
-      const double* u = zt + kidx[b] * LD;
+      const double* u = all ? zt + kidx[b] * LD : refl + b * LD;
       double g = 0.0;
       for (int c = 0; c < n; ++c) g += kc[a * n + c] * u[c];
-      g *= scale[b];
+      if (all) g *= scale[b];
       part += g * g;
     }
     sum += (trw[i] - gt_sum(part, red)) / nvh;
@@ -2722,9 +2769,12 @@ hipError_t launch_tri_trace(int np, int n, const double* kz, double g_max, doubl
 hipError_t launch_small(int np, int n, const double* kw, const double* kz, double g_max, double tau, double rho,
                         double* dos, int32_t* ranks, int rank_stride, double* flag, int64_t flag_stride,
                         const double* s_floor, int nvh, const double* kc, const double* trw, hipStream_t stream) {
-  const void* kernel = n <= 16   ? (const void*)geneig_small_kernel<1>
-                       : n <= 32 ? (const void*)geneig_small_kernel<2>
-                                 : (const void*)geneig_small_kernel<3>;
+  const void* kernels[2][3] = {
+      {(const void*)geneig_small_kernel<1, false>, (const void*)geneig_small_kernel<2, false>,
+       (const void*)geneig_small_kernel<3, false>},
+      {(const void*)geneig_small_kernel<1, true>, (const void*)geneig_small_kernel<2, true>,
+       (const void*)geneig_small_kernel<3, true>}};
+  const void* kernel = kernels[nvh > 0][(n - 1) / 16];
   void* args[] = {&n, &kw, &kz, &g_max, &tau, &rho, &dos, &ranks, &rank_stride, &flag, &flag_stride, &s_floor,
                   &nvh, &kc, &trw};
   return hipLaunchKernel(kernel, dim3(np), dim3(GT_TH), args, 0, stream);
