@@ -523,26 +523,43 @@ hipError_t launch(int64_t n, int nv, const int32_t* row_ptr, const int32_t* col_
 // not touch each other in a step, so a workgroup takes one 16-byte slice of every row through all
 // steps by itself: the slice of Y_k in LDS (two buffers, one barrier a step), Y_k and Y_k-1 of its
 // own rows and up to RUN_NNZ CSR entries of each in the lanes' registers (a longer row's rest is
-// read again each step), every step's slice written to its ring slot.  Sums are taken in the
-// order of cheb_step_kernel: the blocks are bit for bit the same.  Workgroup b runs on XCD
-// b % 8, and takes a slice next to the XCD's others, whose 16-byte pieces share its L2's lines.
+// read again each step, four entries at a time), every step's slice written to its ring slot.  Sums
+// are taken in the order of cheb_step_kernel: the blocks are bit for bit the same.  Workgroup b runs
+// on XCD b % 8, and takes a slice next to the XCD's others, whose 16-byte pieces share its L2's lines.
 // What bounds it: the LDS gathers of one CU, and the rows whose entries its registers hold: 2048.
 // Measured per step (100 steps of a 5-point lattice, N_v = 40, FP64; the launches before, of any
 // size at this end, 3.6): 576 rows 0.58 us, 1024 rows 0.69 us, 2025 rows 1.35 us.
 constexpr int RUN_TH = 1024;
 constexpr int RUN_NNZ = 8;
 
+// sizeof(W) bytes at a byte offset, zero past the resource's range
+template <typename W>
+__device__ __forceinline__ W run_load(__amdgpu_buffer_rsrc_t r, int off) {
+  W w;
+#pragma unroll
+  for (int h = 0; h < (int)sizeof(W) / 16; ++h) {
+    const auto q = __builtin_amdgcn_raw_buffer_load_b128(r, off + 16 * h, 0, 0);
+    __builtin_memcpy((char*)&w + 16 * h, &q, 16);
+  }
+  return w;
+}
+
 template <typename T, typename V, int R>
 __global__ void __launch_bounds__(RUN_TH) cheb_run_kernel(int n, int nvv, const int32_t* __restrict__ row_ptr,
                                                           const int32_t* __restrict__ col_idx,
-                                                          const T* __restrict__ val, T a1, T b1, T a, T b, T c, int k0,
-                                                          int k1, const V* x, const V* xprev, V* y, int ring) {
+                                                          const T* __restrict__ val, int nnz, T a1, T b1, T a, T b, T c,
+                                                          int k0, int k1, const V* x, const V* xprev, V* y, int ring) {
+  typedef int32_t i32x4 __attribute__((ext_vector_type(4)));
+  typedef T v4 __attribute__((ext_vector_type(4)));
   extern __shared__ char run_lds[];
+  const auto rc = __builtin_amdgcn_make_buffer_rsrc((void*)col_idx, (short)0, 4 * nnz, 0x00020000);
+  const auto rv = __builtin_amdgcn_make_buffer_rsrc((void*)val, (short)0, (int)sizeof(T) * nnz, 0x00020000);
   V* buf = (V*)run_lds;  // 2 x (n + 1) slices, the last of each zero (what a row's missing entries gather)
   const int per_xcd = (nvv + 7) / 8;
   const int q = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
   if (q >= nvv) return;  // uniform over the workgroup
   const int tid = threadIdx.x;
+  const int wave0 = __builtin_amdgcn_readfirstlane(tid & ~63);  // the wave's first row
   V cur[R], prev[R];
   uint32_t cols[R][RUN_NNZ / 2];  // two 16-bit columns a register
   T vals[R][RUN_NNZ];
@@ -574,7 +591,8 @@ __global__ void __launch_bounds__(RUN_TH) cheb_run_kernel(int n, int nvv, const 
   for (int k = k0; k <= k1; ++k) {
     const V* src = buf + ((k - k0) & 1 ? n + 1 : 0);
     V* dst = buf + ((k - k0) & 1 ? 0 : n + 1);
-    char* out = (char*)(y + (int64_t)slot * n * nvv);
+    V* yb = y + (int64_t)slot * n * nvv;
+    const auto ro = __builtin_amdgcn_make_buffer_rsrc((void*)yb, (short)0, n * nvv * (int)sizeof(V), 0x00020000);
     slot = slot + 1 == ring ? 0 : slot + 1;
     const T sa = three ? a : a1, sb = three ? b : b1;
 #pragma unroll
@@ -596,15 +614,34 @@ __global__ void __launch_bounds__(RUN_TH) cheb_run_kernel(int n, int nvv, const 
       }
       if (longer >> i & 1) {
         const int pe = row_ptr[r + 1];
-        for (int p = row_ptr[r] + RUN_NNZ; p < pe; ++p) acc = __builtin_elementwise_fma((V)val[p], src[col_idx[p]], acc);
+#pragma unroll 1
+        for (int p = row_ptr[r] + RUN_NNZ; p < pe; p += 4) {
+          const i32x4 c4 = run_load<i32x4>(rc, 4 * p);
+          const v4 w4 = run_load<v4>(rv, (int)sizeof(T) * p);
+          constexpr int H = R == 2 && sizeof(T) == 8 ? 2 : 4;  // gathers in flight: what the registers leave room for
+#pragma unroll
+          for (int h = 0; h < 4; h += H) {
+            V g[H];
+#pragma unroll
+            for (int j = 0; j < H; ++j) g[j] = src[p + h + j < pe ? c4[h + j] : n];
+#pragma unroll
+            for (int j = 0; j < H; ++j)
+              acc = __builtin_elementwise_fma((V)(p + h + j < pe ? w4[h + j] : (T)0), g[j], acc);
+          }
+        }
       }
       V res = step_value<T, V>(sa, acc, sb, cur[i]);
       if (three) res = __builtin_elementwise_fma((V)c, prev[i], res);
       prev[i] = cur[i];
       cur[i] = res;
-      if (r < n) {
-        dst[r] = res;
-        *(V*)(out + (size_t)i * RUN_TH * nvv * sizeof(V) + slice) = res;
+      if (r < n) dst[r] = res;
+      if constexpr (R == 1) {
+        if (r < n) *(V*)((char*)yb + slice) = res;
+      } else if (wave0 + RUN_TH * i < n) {
+        // 32-bit offsets, which take fewer registers (with one row a lane this was 6% slower a step);
+        // a wave's rows past the block's end are out of the resource's range
+        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(i32x4, res), ro,
+                                               (int)(slice + (uint32_t)i * RUN_TH * (uint32_t)nvv * sizeof(V)), 0, 0);
       }
     }
     three = true;
@@ -613,16 +650,16 @@ __global__ void __launch_bounds__(RUN_TH) cheb_run_kernel(int n, int nvv, const 
 }
 
 template <typename T, typename V>
-hipError_t launch_run(int n, int nvv, const int32_t* row_ptr, const int32_t* col_idx, const T* val, double alpha,
-                      double beta, int k0, int k1, const void* x, const void* xprev, void* y, int ring,
+hipError_t launch_run(int n, int nvv, const int32_t* row_ptr, const int32_t* col_idx, const T* val, int nnz,
+                      double alpha, double beta, int k0, int k1, const void* x, const void* xprev, void* y, int ring,
                       hipStream_t stream) {
   const auto fn = n <= RUN_TH ? cheb_run_kernel<T, V, 1> : cheb_run_kernel<T, V, 2>;
   const size_t lds = 2 * (size_t)(n + 1) * sizeof(V);
   hipError_t err = hipFuncSetAttribute((const void*)fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   if (err != hipSuccess) return err;
-  hipLaunchKernelGGL(fn, dim3(8 * ((nvv + 7) / 8)), dim3(RUN_TH), lds, stream, n, nvv, row_ptr, col_idx, val, (T)alpha,
-                     (T)beta, (T)(2.0 * alpha), (T)(2.0 * beta), (T)-1.0, k0, k1, (const V*)x, (const V*)xprev, (V*)y,
-                     ring);
+  hipLaunchKernelGGL(fn, dim3(8 * ((nvv + 7) / 8)), dim3(RUN_TH), lds, stream, n, nvv, row_ptr, col_idx, val, nnz,
+                     (T)alpha, (T)beta, (T)(2.0 * alpha), (T)(2.0 * beta), (T)-1.0, k0, k1, (const V*)x, (const V*)xprev,
+                     (V*)y, ring);
   return hipGetLastError();
 }
 
@@ -642,20 +679,22 @@ hipError_t launch_cheb_step_f32(int64_t n, int nv, const int32_t* row_ptr, const
   return launch<float, f32x4, 4>(n, nv, row_ptr, col_idx, val, nnz, a, b, c, x, xprev, d, out, dots, order, stream);
 }
 
-// Rows of more entries would mostly be read again each step, and more than 256 slices would take
-// turns on the CUs: such calls go step by step, as do more rows (3600 rows: 3.6 to 4.9 us a step).
+// Matrices of more entries a row on average would mostly be read again each step, and more than 256
+// slices would take turns on the CUs: such calls go step by step, as do more rows (3600 rows: 3.6 to
+// 4.9 us a step).  A single long row is walked by one lane, here as there: an arrow matrix of 2048
+// rows, one of them full, N_v = 128, FP64 takes 110 us a step, step by step 135 (200 entry by entry).
 bool cheb_run_fits(int64_t n, int64_t nnz, int nv, int is_f32) {
   return n <= 2 * RUN_TH && nnz <= RUN_NNZ * n && nv / (is_f32 ? 4 : 2) <= 256;
 }
 
 hipError_t launch_cheb_run(int is_f32, int64_t n, int nv, const int32_t* row_ptr, const int32_t* col_idx,
-                           const void* val, double alpha, double beta, int k0, int k1, const void* x,
+                           const void* val, int64_t nnz, double alpha, double beta, int k0, int k1, const void* x,
                            const void* xprev, void* y, int ring, hipStream_t stream) {
   if (is_f32)
-    return launch_run<float, f32x4>((int)n, nv / 4, row_ptr, col_idx, (const float*)val, alpha, beta, k0, k1, x, xprev,
-                                    y, ring, stream);
-  return launch_run<double, f64x2>((int)n, nv / 2, row_ptr, col_idx, (const double*)val, alpha, beta, k0, k1, x, xprev,
-                                   y, ring, stream);
+    return launch_run<float, f32x4>((int)n, nv / 4, row_ptr, col_idx, (const float*)val, (int)nnz, alpha, beta, k0, k1,
+                                    x, xprev, y, ring, stream);
+  return launch_run<double, f64x2>((int)n, nv / 2, row_ptr, col_idx, (const double*)val, (int)nnz, alpha, beta, k0, k1,
+                                   x, xprev, y, ring, stream);
 }
 
 hipError_t launch_box_check(int64_t n, const int32_t* row_ptr, const int32_t* col_idx, int nx, int ny, int nz,

@@ -695,8 +695,8 @@ ssm_status forward_pass(ssm_ctx* c, int pass, bool first, Timeline* tl, int64_t&
       const bool run = k_last > 0 && !(first && pl.dgc_group) && ssm::cheb_run_fits(n, c->a.nnz, nv, !f64);
       if (run) {
         const int kb = std::max(k_first, 1);
-        hipError_t err = ssm::launch_cheb_run(!f64, n, nv, c->a.row_ptr, c->a.col_idx, c->a.values, alpha, beta, kb,
-                                              k_last, kb == 1 ? c->w : (const void*)y_slot(kb - 1),
+        hipError_t err = ssm::launch_cheb_run(!f64, n, nv, c->a.row_ptr, c->a.col_idx, c->a.values, c->a.nnz, alpha,
+                                              beta, kb, k_last, kb == 1 ? c->w : (const void*)y_slot(kb - 1),
                                               kb == 1 ? nullptr : (const void*)y_slot(kb - 2),
                                               c->y, pl.chunk, st);
         if (err != hipSuccess) return hip_fail(err, "Chebyshev steps");
@@ -940,8 +940,8 @@ ssm_status ress_dos(ssm_ctx* c, double* dos_host, int32_t* ranks_host) {
     SSM_HIP(rec(rs.b), "hipEventRecord");
     const bool run = k < k_last && ssm::cheb_run_fits(n, c->a.nnz, nvp, !f64);
     if (run) {
-      err = ssm::launch_cheb_run(!f64, n, nvp, c->a.row_ptr, c->a.col_idx, c->a.values, alpha, beta, k + 1, k_last,
-                                 slot(k), k == 0 ? nullptr : slot(k - 1), c->y, R, st);
+      err = ssm::launch_cheb_run(!f64, n, nvp, c->a.row_ptr, c->a.col_idx, c->a.values, c->a.nnz, alpha, beta, k + 1,
+                                 k_last, slot(k), k == 0 ? nullptr : slot(k - 1), c->y, R, st);
       if (err != hipSuccess) return hip_fail(err, "Chebyshev steps");
       spmm_launches += k_last - k;
     }
@@ -1537,8 +1537,8 @@ ssm_status ssm_chebyshev(const ssm_csr* a, double lo, double hi, int32_t precisi
   const double alpha = 2.0 / (hi - lo), beta = -(hi + lo) / (hi - lo);
   SSM_HIP(hipMemcpyAsync(y, w, e * es, hipMemcpyDeviceToDevice, st), "copy W");
   if (degree > 0 && ssm::cheb_run_fits(a->n, a->nnz, nv, !f64)) {
-    hipError_t err = ssm::launch_cheb_run(!f64, a->n, nv, a->row_ptr, a->col_idx, a->values, alpha, beta, 1, degree, w,
-                                          nullptr, y, degree + 1, st);
+    hipError_t err = ssm::launch_cheb_run(!f64, a->n, nv, a->row_ptr, a->col_idx, a->values, a->nnz, alpha, beta, 1, degree,
+                                          w, nullptr, y, degree + 1, st);
     return err == hipSuccess ? SSM_OK : hip_fail(err, "Chebyshev steps");
   }
   for (int k = 1; k <= degree; ++k) {

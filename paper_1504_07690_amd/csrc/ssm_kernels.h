@@ -88,7 +88,7 @@ hipError_t launch_cheb_step_f32(int64_t n, int nv, const int32_t* row_ptr, const
 // slots that the run overwrites.  Only where cheb_run_fits.
 bool cheb_run_fits(int64_t n, int64_t nnz, int nv, int is_f32);
 hipError_t launch_cheb_run(int is_f32, int64_t n, int nv, const int32_t* row_ptr, const int32_t* col_idx,
-                           const void* val, double alpha, double beta, int k0, int k1, const void* x,
+                           const void* val, int64_t nnz, double alpha, double beta, int k0, int k1, const void* x,
                            const void* xprev, void* y, int ring, hipStream_t stream);
 // Chebyshev moments for Algorithm 2.  With dots (2 cheb_step_blocks doubles) a step also
 // writes workgroup partials of <out, x> and <x, x>.  launch_moments reduces `count`

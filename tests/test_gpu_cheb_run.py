@@ -92,3 +92,24 @@ def test_run_across_ring_chunks(precision):
             out.append(ctx.dos()[0].copy())
             assert ctx.stats()["spmm_launches"] == m * ctx.stats()["passes"]
         assert np.array_equal(out[0], out[1])
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.float64])
+@pytest.mark.parametrize("n,long", [(1021, [(0, 1021), (700, 9), (701, 10), (702, 11), (1020, 12)]),
+                                    (2048, [(0, 2048), (1500, 13), (2047, 2047)])])
+def test_run_full_rows(n, long, dtype):
+    """A few full rows among short ones, the last row of the arrays among them: the same bits."""
+    from paper_1504_07690_amd import ssm as S
+    rows = [[0, i] if i else [0] for i in range(n)]
+    for r, length in long:
+        rows[r] = list(range(n - length, n))
+    big = 2600
+    small = _csr(rows, n, dtype, np.random.default_rng(5))
+    large = _csr(rows, big, dtype, np.random.default_rng(5))
+    w = torch.randn(big, 20, dtype=dtype, device=DEV, generator=torch.Generator(device=DEV).manual_seed(n))
+    ys = torch.full((6, n, 20), 7.0, dtype=dtype, device=DEV)
+    yl = torch.empty(6, big, 20, dtype=dtype, device=DEV)
+    precision = "fp32" if dtype == torch.float32 else "fp64"
+    S.chebyshev(small, -9.0, 9.0, precision, w[:n].contiguous(), ys)
+    S.chebyshev(large, -9.0, 9.0, precision, w, yl)
+    assert torch.equal(ys, yl[:, :n])
