@@ -62,7 +62,8 @@ __device__ __forceinline__ double vdot<f64x2>(const f64x2& u, const f64x2& v) {
 // reading the block the step before wrote), and 1024 slowed the FP64 and moment variants.
 constexpr int CS_THREADS = 256;
 
-// a acc + b x, rounded as every kernel of a step rounds it: the product with x, then one FMA
+// a acc + b x, rounded as every kernel of a step but box_step_kernel rounds it: the product with x, then
+// one FMA
 template <typename T, typename V>
 __device__ __forceinline__ V step_value(T a, const V& acc, T b, const V& x) {
   V t, u;
@@ -238,12 +239,13 @@ __global__ void __launch_bounds__(CS_THREADS)
   for (int p = row_ptr[r]; p < p1; p += 8) {
     i32x4 cols[2];
     T vals[8];
+    const uint32_t pc = (uint32_t)p * 4, pv = (uint32_t)p * (uint32_t)sizeof(T);  // bytes: past 2^31 from p = 2^29
 #pragma unroll
     for (int j = 0; j < 2; ++j)
-      cols[j] = __builtin_bit_cast(i32x4, __builtin_amdgcn_raw_buffer_load_b128(rc, 4 * p + 16 * j, 0, 0));
+      cols[j] = __builtin_bit_cast(i32x4, __builtin_amdgcn_raw_buffer_load_b128(rc, (int)(pc + 16u * j), 0, 0));
 #pragma unroll
     for (int j = 0; j < (int)sizeof(T) / 2; ++j) {
-      const auto w = __builtin_amdgcn_raw_buffer_load_b128(rv, (int)((uint32_t)p * sizeof(T)) + 16 * j, 0, 0);
+      const auto w = __builtin_amdgcn_raw_buffer_load_b128(rv, (int)(pv + 16u * j), 0, 0);
       __builtin_memcpy((char*)vals + 16 * j, &w, 16);
     }
     V g[8];

@@ -84,8 +84,8 @@ hipError_t launch_cheb_step_f32(int64_t n, int nv, const int32_t* row_ptr, const
                                 const float* xprev, const float* d, float* out, hipStream_t stream,
                                 double* dots = nullptr, const RowOrder& order = RowOrder{});
 // Blocks Y_k0 .. Y_k1 (1 <= k0 <= k1) in one launch, Y_k to slot k % ring of y, from x = Y_k0-1 and
-// xprev = Y_k0-2 (null for k0 = 1), bit for bit as launch_cheb_step forms them; x and xprev may be
-// slots that the run overwrites.  Only where cheb_run_fits.
+// xprev = Y_k0-2 (null for k0 = 1), bit for bit as launch_cheb_step forms them without box values; x
+// and xprev may be slots that the run overwrites.  Only where cheb_run_fits.
 bool cheb_run_fits(int64_t n, int64_t nnz, int nv, int is_f32);
 hipError_t launch_cheb_run(int is_f32, int64_t n, int nv, const int32_t* row_ptr, const int32_t* col_idx,
                            const void* val, int64_t nnz, double alpha, double beta, int k0, int k1, const void* x,
