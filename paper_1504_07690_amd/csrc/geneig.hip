@@ -1319,7 +1319,7 @@ hipError_t launch_ql(int np, int n, double* scratch, int64_t stride, hipStream_t
 // scalar cache instead of LDS left a wait at every eight rotations, 5.0 ms.
 template <int T>
 constexpr int vec_waves() {  // waves per SIMD that the row's 32 T registers leave room for
-  return T <= 1 ? 4 : T <= 6 ? 2 : 1;
+  return T <= 6 ? 2 : 1;
 }
 
 // x <- x (I - tau v v^T), v (16 T entries in LDS) zero up to entry k
@@ -2732,10 +2732,10 @@ hipError_t launch_reduce_t(int np, int n, const double* kw, double* scratch, int
 }
 
 // T of np points (kw null: of the padded B in their scratch, whose eigenvalues in [0, hi] count): in
-// registers up to N_v = 128
+// registers up to N_v = 128 (none at or below 48: geneig_small_kernel)
 hipError_t launch_reduce(int np, int n, const double* kw, double* scratch, int64_t stride, double hi,
                          hipStream_t stream) {
-  if (n <= GT_REG_NV) return launch_reduce_t<1>(np, n, kw, scratch, stride, hi, stream);
+  if (n <= GT_REG_NV) return launch_reduce_t<4>(np, n, kw, scratch, stride, hi, stream);
   hipLaunchKernelGGL(geneig_tri_reduce_kernel, dim3(np), dim3(GT_TH), 0, stream, n, kw, scratch, stride, hi);
   return hipGetLastError();
 }
@@ -2760,7 +2760,7 @@ hipError_t launch_tri_trace(int np, int n, const double* kz, double g_max, doubl
                             int32_t* ranks, int rank_stride, double* scratch, int64_t stride, const double* s_floor,
                             hipStream_t stream) {
   if (n <= GT_REG_NV)
-    return launch_reg_trace_t<1>(np, n, kz, g_max, tau, rho, dos, ranks, rank_stride, scratch, stride, s_floor, stream);
+    return launch_reg_trace_t<4>(np, n, kz, g_max, tau, rho, dos, ranks, rank_stride, scratch, stride, s_floor, stream);
   hipLaunchKernelGGL(geneig_tri_trace_kernel, dim3(np), dim3(GT_TH), 0, stream, n, kz, g_max, tau, rho, dos, ranks,
                      rank_stride, scratch, stride, s_floor);
   return hipGetLastError();
@@ -2780,12 +2780,9 @@ hipError_t launch_small(int np, int n, const double* kw, const double* kz, doubl
   return hipLaunchKernel(kernel, dim3(np), dim3(GT_TH), args, 0, stream);
 }
 
-// U of np points: rows in registers up to N_v = 128, in LDS above
+// U of np points (N_v above 48): rows in registers up to N_v = 128, in LDS above
 hipError_t launch_vectors(int np, int n, double* scratch, int64_t stride, hipStream_t stream) {
   switch ((n + 15) / 16) {
-    case 1: return launch_rows_t<1>(np, n, scratch, stride, stream);
-    case 2: return launch_rows_t<2>(np, n, scratch, stride, stream);
-    case 3: return launch_rows_t<3>(np, n, scratch, stride, stream);
     case 4: return launch_rows_t<4>(np, n, scratch, stride, stream);
     case 5: return launch_rows_t<5>(np, n, scratch, stride, stream);
     case 6: return launch_rows_t<6>(np, n, scratch, stride, stream);
