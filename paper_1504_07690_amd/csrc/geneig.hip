@@ -315,7 +315,7 @@ __global__ void __launch_bounds__(TH) geneig_trace_kernel(int nv, const double* 
 
   for (int idx = tid; idx < n * n; idx += TH) {
     const int r = idx / n, c = idx - r * n;
-    sh.A[r * ld + c] = kw[idx];
+    sh.A[r * ld + c] = 0.5 * (kw[idx] + kw[c * n + r]);
     sh.V[r * ld + c] = (r == c) ? 1.0 : 0.0;
   }
   __syncthreads();

@@ -35,3 +35,20 @@ def test_geneig_antisymmetric_parts_drop_out(nv):
         assert ranks[:npts].tolist() == [r[1] for r in ref]
         assert ranks[npts:].tolist() == [r[2] for r in ref]
         assert np.abs(dos.cpu().numpy() - [r[0] for r in ref]).max() <= 500 * 2.0 ** -52 * nv * scale
+
+
+@pytest.mark.parametrize("nv", [2, 17, 40])
+def test_jacobi_takes_the_symmetric_part(nv):
+    """Points out of the scale that the other kernels take go to the cyclic Jacobi kernel."""
+    from paper_1504_07690_amd import ssm as S
+    rng = np.random.default_rng(500 + nv)
+    w = rng.standard_normal((1000, nv))
+    z = w * rng.uniform(0.05, 0.95, 1000)[:, None]
+    skew = np.triu(rng.uniform(-50.0, 50.0, (nv, nv)), 1)
+    k_w, k_z = w.T @ z + (skew - skew.T), z.T @ z
+    kw, kz = np.stack([k_w, k_w * 2.0 ** -400]), np.stack([k_z, k_z * 2.0 ** -400])
+    dos = torch.full((2,), 7.0, dtype=torch.float64, device=DEV)
+    S.geneig_trace(torch.tensor(kw, device=DEV), torch.tensor(kz, device=DEV), 1.0, 1e-7, 1e-3, dos)
+    ref = O.geneig_trace(k_w, k_z, 1.0)[0]
+    sym = 0.5 * (k_w + k_w.T)
+    assert np.abs(dos.cpu().numpy() - ref).max() <= 500 * 2.0 ** -52 * nv * np.linalg.cond(sym)
