@@ -420,9 +420,11 @@ ssm_status ssm_gram_noalloc(int32_t precision, int64_t n, int32_t nv, int32_t nt
  * (k_w[i] taken as its symmetric part), keep s_j >= tau max_j s_j (nothing if
  * max s <= 0), B = S~^-1/2 U~^T k_z[i] U~ S~^-1/2, eig(B) = xi, dos[i] = sum of xi
  * in [0, (1 + rho) g_max]; ranks[i] = r1, ranks[ntb + i] = r2 (ranks may be NULL).
+ * (B by its symmetric part, so k_z[i] by its own).
  * All in FP64: a Householder reduction to tridiagonal form, implicit QL for
- * eig(k_w[i]) and Sturm counts or bisection for eig(B) (a point whose QL iterations
- * run past their limit is done by cyclic Jacobi).  k_w, k_z: ntb
+ * eig(k_w[i]) and Sturm counts or bisection for eig(B).  Cyclic Jacobi does a point
+ * whose QL iterations run past their limit, for nv <= 48 also one whose K_W or B is
+ * not finite or has its largest entry outside 1e-100 .. 1e100, and nv = 1.  k_w, k_z: ntb
  * row-major nv x nv FP64 matrices on the device; dos_dev: ntb doubles, ranks_dev:
  * 2 ntb int32 (may be NULL).  scratch: ssm_geneig_trace_scratch_doubles(nv, ntb)
  * doubles of device memory, owned by the caller, contents ignored on entry.

@@ -200,15 +200,17 @@ __global__ void __launch_bounds__(CS_THREADS) cheb_step_kernel(int64_t n, int nv
 }
 
 // The step of blocks up to 128 MiB whose rows are not whole waves.  The same lanes as above, with the
-// vector units' work cut to what the sums need (above, 310 instructions a wave, most of them 64-bit
-// divisions, addresses and masks, take 45 us of a 56 us step of N = 262144, N_v = 80 in FP32).  Rows
-// come from products by reciprocals; a row's next eight entries come in four 16-byte loads (FP32),
+// vector units' work cut to what the sums need (the kernel above has 268 vector instructions in FP32, 496
+// with tiles, many of them of 64-bit divisions, addresses and masks; this one 195).  Rows come from
+// products by reciprocals; a row's next eight entries come in four 16-byte loads (FP32),
 // which may run on into the next row's; every gather is a buffer load at a 32-bit offset, past
 // the block's end for the slots that the row does not have, which reads as zero without a request.
-// What bounds it: the three blocks moved, at a large copy's rate from 80 MB on.
+// What bounds it: the three blocks and the neighbours' rows that the L2 did not keep, 6 to 7 TB/s of
+// them, and about 5 us a launch of ramp and drain.
 // Measured per step: 5-point lattice, N_v = 40, FP32, N = 22500 5.44 to 4.61 us, N_v = 64, FP64,
 // N = 160000 49.2 to 45.1; 7-point, N_v = 80, FP32, N = 110592 24.1 to 22.5, N = 262144 56.9 to 55.1;
-// a random graph of 100000 rows and 17 entries a row, N_v = 96, FP32 99.7 to 98.4.
+// a random graph of 100000 rows and 17 entries a row, N_v = 96, FP32 99.7 to 98.4.  The other way: a
+// 27-point lattice of 32768 rows, N_v = 128, FP32 24.9 to 25.7.
 template <typename T, typename V, bool DOTS>
 __global__ void __launch_bounds__(CS_THREADS)
     cheb_slice_kernel(uint32_t total, uint32_t nvv, FastDiv per_row, uint32_t nblocks, uint32_t per_xcd,

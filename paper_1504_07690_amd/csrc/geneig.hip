@@ -10,12 +10,11 @@
 // Two eigensolvers.  The trace (with or without the hybrid term of Algorithm 6) goes through a
 // tridiagonal matrix (Householder reduction; implicit QL for step 1, Sturm counts, bisection or QL
 // for step 3): up to N_v = 48 in one kernel (geneig_small_kernel), above in kernels per group
-// of points (geneig_tri_*), as does its backward above 48.  For the backward at or below 48, and
-// for points that these give up, one workgroup per
-// point runs parallel cyclic Jacobi: sweeps in round-robin (tournament) order, so each round
-// rotates N_v/2 disjoint index pairs at once: the pair angles are computed first
-// (Golub & Van Loan, symmetric 2x2 Schur), then the rows of every pair are rotated,
-// then the columns (and the eigenvector columns).  The pivot entries are set to
+// of points (geneig_tri_*), as does its backward above 48.  For the backward at or below 48, N_v = 1,
+// and points that these give up, one workgroup per point runs parallel cyclic Jacobi: sweeps in
+// round-robin (tournament) order, so each round rotates N_v/2 disjoint index pairs at once: the pair
+// angles are computed first (Golub & Van Loan, symmetric 2x2 Schur), then the rows of every pair
+// are rotated, then the columns (and the eigenvector columns).  The pivot entries are set to
 // exactly zero.  A sweep starts only while off(A)_F > 1e-14 ||A||_F.
 // Jacobi's matrix and eigenvectors live in LDS for N_v <= 96 (2 * 96 * 97 doubles), the
 // matrix alone up to N_v = 128 (eigenvectors in the point's global scratch), both in

@@ -26,8 +26,9 @@ struct RowOrder {
   // once for several rows (launch_cheb_step, no dots, rows of whole waves)
   const void* box = nullptr;
 };
-// v / d for any 32-bit v by a product (d >= 1): on the host built once per launch, on the device five
-// instructions instead of a division's tens (scalar ones where v is uniform)
+// v / d for any 32-bit v by a product (d >= 1), Granlund and Montgomery's division by invariant integers:
+// on the host built once per launch, on the device five instructions instead of a division's tens
+// (scalar ones where v is uniform)
 struct FastDiv {
   uint32_t d = 1, m = 1, s1 = 0, s2 = 0;
   FastDiv() = default;
