@@ -28,9 +28,10 @@
 // What bounds it: the FP64 matrix cores.  Operands come straight from memory, two steps ahead of
 // the MFMAs that consume them: lane l reads column 16a + l%16 of row r + l/16 for each column
 // block a, for Z_i and W (a 4-row slab is contiguous).
-// Measured (FP32 blocks, with the reduction): N = 262144, N_v = 80, 125 points 9.39 to 8.07 ms;
-// N_v = 128, 151 points 34.0 to 25.4 ms (51 TFLOP/s on 2 N N_v^2 a point, of 72.7 for the
-// library's square product); N_v = 256, 20 points 19.5 to 12.8 ms.
+// Measured (FP32 blocks, N = 262144, with the reduction; before: a workgroup per point and segment, all
+// sixteen blocks of diagonal tiles): N_v = 80, 125 points 9.25 to 7.99 ms; N_v = 128, 151 points 34.0 to
+// 26.3 ms (49 TFLOP/s on 2 N N_v^2 a point, of 72.7 for the library's square product); N_v = 256,
+// 20 points 19.2 to 12.7 ms.
 #include <algorithm>
 
 #include "ssm_kernels.h"
@@ -467,11 +468,12 @@ hipError_t launch_t(int is_f32, GramPlan& pl, int nv, int nseg, const void* w, i
   GramShare& d = pl.diag;
   if (!share_parts(d, pl.n, seg, max_rows) || (pl.off.items && !share_parts(pl.off, pl.n, seg, max_rows)))
     return hipErrorInvalidValue;
-  // Even shares instead where the parts' last round of resident waves would leave 5% and more of the
+  // Even shares instead where the parts' last round of resident waves would leave 1% and more of the
   // waves' time idle, and parts are long beside the stores and loads of a run's end (1024 rows, a
-  // quarter of a millisecond at N_v = 80).  N = 262144, N_v = 80, 125 points: 8.94 ms in parts, 7.97 in even shares.
+  // quarter of a millisecond at N_v = 80).  N_v = 80: N = 262144, 125 points (14% idle) 8.95 ms in parts,
+  // 7.97 in even shares; N = 110592, 500 points (2.4%) 13.7, 13.4.
   const int64_t idle = (d.waves + resident - 1) / resident * resident - d.waves;
-  if (gram_even<T>() && seg / GR_WAVES >= 1024 && d.waves > resident && 20 * idle >= d.waves) {
+  if (gram_even<T>() && seg / GR_WAVES >= 1024 && d.waves > resident && 100 * idle >= d.waves) {
     GramShare even = d;
     if (share_evenly(even, resident, slots, seg / GR_WAVES, max_rows)) d = even;
   }
